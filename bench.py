@@ -36,15 +36,24 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-# Algorithmic HBM bytes per voxel of each pass of one operator apply, in units of
-# F = one real scalar field (8 B/voxel FP64, 4 B FP32; a half spectrum of one
-# component is the same size), plus the 2-byte grain id where a pass reads it.
+# HBM bytes per voxel of each pass of one operator apply, in units of F = one real scalar field
+# (8 B/voxel FP64, 4 B FP32), plus the 2-byte grain id where a pass reads it.
+PASS_FIELDS = {"y_start": 6, "z_strain": 7, "x_sigma": 16, "z_div": 9, "y_end": 9}
+PASS_ID_BYTES = {"x_sigma": 2}
+
+
+def moved_bytes_per_voxel(name, real_bytes):
+    return PASS_FIELDS[name] * real_bytes + PASS_ID_BYTES.get(name, 0)
+
+
+# The same of the operator as seven half-spectrum passes (D_x between an x-forward and an x-inverse
+# pass), the form that figures of 62 fields an apply are counted on.
 OPERATOR_PASS_FIELDS = {"x_fwd": 6, "y_deriv": 6, "z_strain": 12, "x_stress": 12, "y_div": 8, "z_div": 9,
                         "x_inv_inertia": 9}
 OPERATOR_PASS_ID_BYTES = {"x_stress": 2, "x_inv_inertia": 2}
 
 
-# HBM bytes per dispatch of the x_stress pass at 256^3 from two rocprofv3 counter runs
+# HBM bytes per dispatch of the x_stress pass of the seven-pass operator at 256^3 from two rocprofv3 counter runs
 # (profiles/hbm_traffic_256cube.md): FETCH_SIZE x 2.000 and WRITE_SIZE x 1.000, the factors a
 # 512 MiB device copy reads for those counters.  Valid only for the kernel sources they were
 # taken on (hash below); otherwise the traffic is reported as null.
@@ -151,7 +160,7 @@ def operator_rates(pb):
             med = totals[len(totals) // 2]
             passes = {k: sorted(r[k] for r in runs)[len(runs) // 2] for k in runs[0]}
             pre = nmb.profile_passes(ctx, 1, u, Au, reps=10)
-            bpv = operator_bytes_per_voxel(rb)
+            bpv = sum(moved_bytes_per_voxel(k, rb) for k in PASS_FIELDS)
             out[label] = {"apply_ms_median": med, "gvoxel_per_s": N / (med * 1e-3) / 1e9,
                           "model_bytes_per_voxel": bpv, "model_GBps": bpv * N / (med * 1e-3) / 1e9,
                           "passes_ms": passes, "precond_passes_ms": pre}
@@ -292,7 +301,7 @@ def explicit_rates(pb, steps, warmup):
     finally:
         ctx.close()
     assert np.isfinite(u).all()
-    bpv = 77 * 8 + 4  # x-forward with the displacement update 15F, operator passes 47F + 2 B, last pass 15F + 2 B
+    bpv = 65 * 8 + 4  # first pass with the displacement update 15F, three middle passes 32F + 2 B, last 18F + 2 B
     log(f"[explicit] omega_max^2 {w2:.4f} (power iteration {w2_est:.4f}, grain bound {w2_bound:.4f}); "
         f"dt {dt:.4f} vs implicit {pb.dt:.4f}; {steps} steps in {el:.3f}s -> {steps / el:.1f} steps/s")
     return {"steps_per_s": steps / el, "ms_per_step": 1e3 * el / steps, "dt": dt, "omega2_max_power_iter": w2_est,
@@ -374,7 +383,7 @@ def main():
         for label, rb in (("fp32", 4), ("fp64", 8)):
             passes = op[label]["passes_ms"]
             dom = max(passes, key=passes.get)
-            bpv = pass_bytes_per_voxel(dom, rb)
+            bpv = moved_bytes_per_voxel(dom, rb)
             achieved = bpv * pb.n_vox / (passes[dom] * 1e-3) / 1e9
             rl[label] = {"bound": "hbm", "kernel": f"{dom} ({label} operator pass)", "achieved": round(achieved, 1),
                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),

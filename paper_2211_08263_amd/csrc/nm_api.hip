@@ -23,10 +23,7 @@
 
 using namespace nm;
 
-// Padding (complex elements) of the half-spectrum plane and component strides.
-#ifndef NM_PAD_PLANE
-#define NM_PAD_PLANE 0
-#endif
+// Padding (elements) of the work buffers' component stride.
 #ifndef NM_PAD_COMP
 #define NM_PAD_COMP 1040
 #endif
@@ -35,7 +32,7 @@ struct nm_ctx {
     // problem
     int dim = 3, n1 = 0, n2 = 0, n3 = 0, nph = 0;
     long N = 0, NS = 0, ng = 0;
-    SpecLayout lay{};
+    Layout lay{};
     double dt = 0, beta = 0.25, gam = 0.5;
     std::vector<int64_t> gidx_h;
     nm_options opt{};
@@ -193,117 +190,154 @@ template <> struct Prec<float> {
     static void* spec2(nm_ctx* c) { return c->spec32b; }
 };
 
-XFwdArgs xf_args(nm_ctx* c, void* spec)
+// Arguments of the operator's passes on p (real field), work buffers S and S2 of precision T.
+template <typename T> PassArgs pass_args(nm_ctx* c, const Layout& lay, void* S, void* S2, const T* p)
 {
-    XFwdArgs a{};
-    a.spec = spec;
-    a.lay = c->lay;
-    a.scal = c->scal;
-    a.nlines = 3L * c->n2 * c->n3;
-    return a;
-}
-XInvArgs xi_args(nm_ctx* c, void* spec, void* out, const void* aux, const void* rho, const uint8_t* mask,
-                 double* partials)
-{
-    XInvArgs a{};
-    a.spec = spec;
-    a.lay = c->lay;
-    a.out = out;
-    a.aux = aux;
+    PassArgs a{};
+    a.lay = lay;
+    a.S = S;
+    a.S2 = S2;
+    a.u = const_cast<T*>(p);
+    a.p = const_cast<T*>(p);
     a.phase = c->phase;
-    a.rho = rho;
-    a.mask = mask;
-    a.partials = partials;
-    a.nlines = 3L * c->n2 * c->n3;
-    a.lines_per_comp = (long)c->n2 * c->n3;
-    a.dim = c->dim;
+    a.C21 = Prec<T>::C(c);
+    a.rho = Prec<T>::rho(c);
+    a.bdt2 = c->sp.bdt2;
     return a;
 }
+template <typename T> PassArgs pass_args(nm_ctx* c, const T* p)
+{
+    return pass_args<T>(c, c->lay, Prec<T>::spec(c), Prec<T>::spec2(c), p);
+}
 
-// The six passes of q = A p after the x-forward one (which left the x spectrum of p in S).
-// xmode: the fused stage of the last pass; bdt2 (when not NaN) replaces beta dt^2 in the
-// scale -beta dt^2 of the divergence, so that the chain yields -bdt2 div sigma (+ rho p).
-template <typename T>
-int chain_operator_rest(nm_ctx* c, const XInvArgs& ia, int xmode = XI_OPERATOR, double bdt2 = NAN)
+// The passes of q = A p between the first (which left D_y p in S) and the last: D_z, the stress
+// pass and the z part of the divergence.  partials (or null): per-block sums of p . A p; with them
+// the z part of the divergence also reduces them into the step length alpha (2D: a kernel of its
+// own), so that it is there for the last pass.
+template <typename T> int operator_middle(nm_ctx* c, PassArgs a, double* scal = nullptr, int multi = 0)
 {
     hipStream_t s = c->stream;
-    void* spec = Prec<T>::spec(c);
-    void* spec2 = Prec<T>::spec2(c);
     const void* tw = Prec<T>::tw(c);
-    const SpecLayout& lay = ia.lay;
-    SpecParams sp = c->sp;
-    sp.stop = lay.stop;
-    if (!std::isnan(bdt2)) sp.bdt2 = bdt2;
-    LCHK(c, launch_colop<T>(YOP_DERIV, sp, lay, spec, spec2, tw, s));
-    LCHK(c, launch_colop<T>(ZOP_STRAIN, sp, lay, spec, spec2, tw, s));
-    LCHK(c, launch_xstress<T>(c->n1, spec2, lay, c->phase, Prec<T>::C(c), tw, s));
-    LCHK(c, launch_colop<T>(YOP_DIV, sp, lay, spec, spec2, tw, s));
-    LCHK(c, launch_colop<T>(ZOP_DIVZ, sp, lay, spec, spec2, tw, s));
-    LCHK(c, launch_xinv<T>(xmode, c->n1, ia, tw, s));
-    return NM_OK;
-}
-
-// q = A p as seven passes: x-forward (3), D_y (3 -> 3), strain (6), x-inverse +
-// sigma = C : eps + x-forward (6), y part of the divergence, z part of the
-// divergence, x-inverse + rho p.  S and S2 are the two half-spectrum buffers.
-// The layout in fa carries the loop's stop flag (null outside a batched Krylov loop);
-// every pass of the chain gets it.
-template <typename T> int chain_operator(nm_ctx* c, int fmode, const XFwdArgs& fa, const XInvArgs& ia)
-{
-    LCHK(c, launch_xfwd<T>(fmode, c->n1, fa, Prec<T>::tw(c), c->stream));
-    return chain_operator_rest<T>(c, ia);
-}
-
-// z = M r up to the x-inverse: x/y/z forward, pointwise (beta dt^2 K + rhobar I)^-1,
-// z and y inverse; the x spectrum of z is left in S.  partials (or null): per-block
-// sums of r . z taken on the spectrum inside the z pass.
-template <typename T> int chain_precond_spec(nm_ctx* c, int fmode, const XFwdArgs& fa, double* partials)
-{
-    hipStream_t s = c->stream;
-    void* spec = Prec<T>::spec(c);
-    const void* tw = Prec<T>::tw(c);
-    const SpecLayout& lay = fa.lay;
-    SpecParams sp = c->sp;
-    sp.stop = lay.stop;
-    LCHK(c, launch_xfwd<T>(fmode, c->n1, fa, tw, s));
-    LCHK(c, launch_ypass<T>(-1, 3, lay, spec, tw, s));
-    LCHK(c, launch_zprecond<T>(sp, lay, spec, tw, s, partials));
-    LCHK(c, launch_ypass<T>(+1, 3, lay, spec, tw, s));
-    return NM_OK;
-}
-
-// z = M r: x/y/z forward, pointwise (beta dt^2 K + rhobar I)^-1, inverse.
-template <typename T> int chain_precond(nm_ctx* c, int fmode, const XFwdArgs& fa, const XInvArgs& ia)
-{
-    // with ia.partials the product r . z is summed on the spectrum inside the z pass, so
-    // the final x pass need not read r again
-    XInvArgs ib = ia;
-    if (ia.partials) {
-        ib.partials = nullptr;
-        ib.aux = nullptr;
+    const int nbx = xstress_blocks<T>(a.lay);
+    if (c->n3 > 1) LCHK(c, launch_zstrain<T>(c->sp, a, tw, s));
+    LCHK(c, launch_xstress<T>(c->sp, a, tw, s));
+    if (c->n3 > 1) {
+        if (a.partials) a.carry = Carry{a.partials, nbx, scal, RED_ALPHA, multi};
+        LCHK(c, launch_zdiv<T>(c->sp, a, tw, s));
+    } else if (a.partials) {
+        if (multi) LCHK(c, launch_reduce_multi(a.partials, nbx, a.lay.nb, scal, RED_ALPHA, s));
+        else LCHK(c, launch_reduce(a.partials, nbx, scal, RED_ALPHA, 0, s, true));
     }
-    CHK(chain_precond_spec<T>(c, fmode, fa, ia.partials));
-    LCHK(c, launch_xinv<T>(XI_PRECOND, c->n1, ib, Prec<T>::tw(c), c->stream));
+    return NM_OK;
+}
+
+// The passes of z = M r between the y-forward and the y-inverse: src holds the y spectrum of r
+// (component stride sc, field stride sb), the y spectrum of z is left in components 0..2 of S2.
+// The z passes carry the reduction of the pass before (red: r.r of the residual update, or none)
+// and that of r . z (rz_action, from partials); in 2D they are kernels of their own.
+template <typename T>
+int precond_middle(nm_ctx* c, const Layout& lay, const void* src, long sc, long sb, void* S2, const Carry& red,
+                   double* partials, int rz_action, double* scal, int multi)
+{
+    hipStream_t s = c->stream;
+    const void* tw = Prec<T>::tw(c);
+    const int nbz = xprecond_blocks<T>(lay);
+    const Carry rz{partials, nbz, scal, partials ? rz_action : (int)RED_NONE, multi};
+    const bool guarded = lay.stop != nullptr;
+    auto reduce = [&](const Carry& r) -> int {
+        if (r.action == RED_NONE) return NM_OK;
+        if (multi) LCHK(c, launch_reduce_multi(r.part, r.n, lay.nb, r.scal, r.action, s));
+        else LCHK(c, launch_reduce(r.part, r.n, r.scal, r.action, 0, s, guarded));
+        return NM_OK;
+    };
+    if (c->n3 == 1) {
+        CHK(reduce(red));
+        LCHK(c, launch_xprecond<T>(c->sp, lay, src, sc, sb, S2, tw, s, partials));
+        return reduce(rz);
+    }
+    ColFft f{};
+    f.lay = lay;
+    f.axis = 2;
+    f.dir = -1;
+    f.src = src;
+    f.sc = sc;
+    f.sb = sb;
+    f.dst = S2;
+    f.dc = lay.cs;
+    f.db = lay.bs;
+    f.carry = red;
+    LCHK(c, launch_colfft<T>(f, tw, s));
+    LCHK(c, launch_xprecond<T>(c->sp, lay, S2, lay.cs, lay.bs, S2, tw, s, partials));
+    f.dir = +1;
+    f.src = S2;
+    f.sc = lay.cs;
+    f.sb = lay.bs;
+    f.carry = rz;
+    LCHK(c, launch_colfft<T>(f, tw, s));
+    return NM_OK;
+}
+
+// The preconditioner's first pass: y-forward transform of the real field r (3 x N) in dst
+// (component stride dc, field stride db; r itself may be dst).
+template <typename T> int precond_first(nm_ctx* c, const Layout& lay, const T* r, void* dst, long dc, long db)
+{
+    ColFft f{};
+    f.lay = lay;
+    f.src = r;
+    f.sc = lay.ns;
+    f.sb = lay.bf;
+    f.dst = dst;
+    f.dc = dc;
+    f.db = db;
+    LCHK(c, launch_colfft<T>(f, Prec<T>::tw(c), c->stream));
+    return NM_OK;
+}
+
+// z = M r (Gamma entries of z zeroed with a mask).
+template <typename T> int apply_M(nm_ctx* c, const T* r, T* z, const uint8_t* mask)
+{
+    const Layout& lay = c->lay;
+    void* S2 = Prec<T>::spec2(c);
+    CHK(precond_first<T>(c, lay, r, S2, lay.cs, lay.bs));
+    CHK(precond_middle<T>(c, lay, S2, lay.cs, lay.bs, S2, Carry{}, nullptr, RED_NONE, nullptr, 0));
+    ColFft f{};
+    f.lay = lay;
+    f.dir = +1;
+    f.src = S2;
+    f.sc = lay.cs;
+    f.sb = lay.bs;
+    f.dst = z;
+    f.dc = lay.ns;
+    f.db = lay.bf;
+    f.mask = mask;
+    f.zero3 = c->dim == 2;
+    LCHK(c, launch_colfft<T>(f, Prec<T>::tw(c), c->stream));
     return NM_OK;
 }
 
 // q = A x (optionally masked), no reduction.
 template <typename T> int apply_A(nm_ctx* c, const T* x, T* out, const uint8_t* mask)
 {
-    XFwdArgs fa = xf_args(c, Prec<T>::spec(c));
-    fa.src = x;
-    XInvArgs ia = xi_args(c, Prec<T>::spec(c), out, x, Prec<T>::rho(c), mask, nullptr);
-    return chain_operator<T>(c, XF_PLAIN, fa, ia);
+    PassArgs a = pass_args<T>(c, x);
+    a.out = out;
+    a.mask = mask;
+    LCHK(c, launch_ystart<T>(YS_APPLY, c->sp, a, Prec<T>::tw(c), c->stream));
+    CHK(operator_middle<T>(c, a));
+    LCHK(c, launch_yend<T>(YE_OUT, c->sp, a, Prec<T>::tw(c), c->stream));
+    return NM_OK;
 }
 
 // out = scale * div(C : grad^s x) (FP64, no inertia term, no Gamma projection).
 int div_stress(nm_ctx* c, const double* x, double* out, double scale)
 {
-    XFwdArgs fa = xf_args(c, c->spec64);
-    fa.src = x;
-    XInvArgs ia = xi_args(c, c->spec64, out, x, c->rho64, nullptr, nullptr);
-    LCHK(c, launch_xfwd<double>(XF_PLAIN, c->n1, fa, c->tw64, c->stream));
-    return chain_operator_rest<double>(c, ia, XI_PLAIN, -scale);
+    PassArgs a = pass_args<double>(c, x);
+    a.out = out;
+    a.rho = nullptr;
+    a.bdt2 = -scale;
+    LCHK(c, launch_ystart<double>(YS_APPLY, c->sp, a, c->tw64, c->stream));
+    CHK(operator_middle<double>(c, a));
+    LCHK(c, launch_yend<double>(YE_OUT, c->sp, a, c->tw64, c->stream));
+    return NM_OK;
 }
 
 int read_scalars(nm_ctx* c)
@@ -334,8 +368,9 @@ struct PcgResult {
 // Preconditioned conjugate gradients (Hestenes-Stiefel) on real-space vectors.
 // x: initial guess / solution.  With masked, P A P and P M P on the free dofs.
 // rr_known >= 0: r already holds P (rhs - A x) with r.r = rr_known (no initial apply;
-// rhs may then be null).  The preconditioned residual z lives only as the x spectrum
-// between the preconditioner's z pass and the next direction update.
+// rhs may then be null).  From the first preconditioner apply on, r holds the y spectrum of the
+// residual; the preconditioned residual z lives only as its y spectrum between the preconditioner
+// and the next direction update.
 template <typename T>
 int pcg(nm_ctx* c, const T* rhs, T* x, T* r, T* p, T* q, bool masked, bool x_zero, double bref, double tol,
         int max_iter, int fixed_iters, bool allow_unconverged, PcgResult* res, double rr_known = -1.0,
@@ -344,7 +379,7 @@ int pcg(nm_ctx* c, const T* rhs, T* x, T* r, T* p, T* q, bool masked, bool x_zer
     hipStream_t s = c->stream;
     const uint8_t* mk = masked ? c->mask : nullptr;
     const long n = 3 * c->N;
-    void* spec = Prec<T>::spec(c);
+    void* S2 = Prec<T>::spec2(c);
     // r = P (b - A x)
     double rr = rr_known;
     if (rr_known < 0 && !rhs) return fail(c, NM_EINVAL, "PCG needs the right-hand side or the initial residual");
@@ -366,15 +401,10 @@ int pcg(nm_ctx* c, const T* rhs, T* x, T* r, T* p, T* q, bool masked, bool x_zer
         res->converged = true;
         return NM_OK;
     }
-    const int nb = xinv_blocks(c->n1, 3L * c->n2 * c->n3);
-    const int nbz = zprecond_blocks<T>(c->sp);
-    // z = P M r as its x spectrum (the x-inverse is fused into the first p update), rz = r.z
-    {
-        XFwdArgs fa = xf_args(c, spec);
-        fa.src = r;
-        CHK(chain_precond_spec<T>(c, XF_PLAIN, fa, c->part_b));
-        LCHK(c, launch_reduce(c->part_b, nbz, c->scal, RED_RZ_INIT, 0, s));
-    }
+    // z = P M r as its y spectrum (the y-inverse is fused into the first p update), rz = r.z
+    const long ns = c->lay.ns;
+    CHK(precond_first<T>(c, c->lay, r, r, ns, 0));
+    CHK(precond_middle<T>(c, c->lay, r, ns, 0, S2, Carry{}, c->part_b, RED_RZ_INIT, c->scal, 0));
     // Iterations run in batches on the device: the residual reduction of each iteration
     // counts it and raises the stop flag when the loop is done, after which every
     // guarded kernel returns at once; the host reads the scalars once per batch and sizes
@@ -395,40 +425,26 @@ int pcg(nm_ctx* c, const T* rhs, T* x, T* r, T* p, T* q, bool masked, bool x_zer
     }
     double rr_prev = rr;
     int it_prev = 0;
+    PassArgs a = pass_args<T>(c, p);
+    a.lay.stop = stop;
+    a.x = x;
+    a.r = r;
+    a.mask = mk;
+    a.scal = c->scal;
+    const void* tw = Prec<T>::tw(c);
     for (;;) {
         for (int k = 0; k < batch; k++) {
-            // z = P x-inv(Z); p = z + beta p (x += alpha p_old) with its x spectrum;
-            // q = P A p ; alpha = rz / p.q
-            {
-                XInvArgs pa = xi_args(c, spec, nullptr, nullptr, nullptr, mk, nullptr);
-                pa.lay.stop = stop;
-                pa.p = p;
-                pa.x = x;
-                pa.scal = c->scal;
-                LCHK(c, launch_xpupdate<T>(c->n1, pa, Prec<T>::tw(c), s));
-                XInvArgs ia = xi_args(c, spec, q, p, Prec<T>::rho(c), mk, c->part_b);
-                ia.lay.stop = stop;
-                CHK(chain_operator_rest<T>(c, ia));
-                LCHK(c, launch_reduce(c->part_b, nb, c->scal, RED_ALPHA, 0, s, true));
-            }
-            // r -= alpha q ; r.r (iteration count, stop test) ; Z = M r with r.z on the
-            // spectrum ; beta = r.z_new / r.z_old   (x += alpha p follows in the next p update)
-            {
-                XFwdArgs fa = xf_args(c, spec);
-                fa.lay.stop = stop;
-                fa.r = r;
-                fa.q = q;
-                fa.partials = c->part_a;
-                LCHK(c, launch_xfwd<T>(XF_UPDATE, c->n1, fa, Prec<T>::tw(c), s));
-                LCHK(c, launch_reduce(c->part_a, xfwd_blocks(c->n1, 3L * c->n2 * c->n3), c->scal, RED_RR_CHECK, 0,
-                                      s, true));
-                SpecParams sp = c->sp;
-                sp.stop = stop;
-                LCHK(c, launch_ypass<T>(-1, 3, fa.lay, spec, Prec<T>::tw(c), s));
-                LCHK(c, launch_zprecond<T>(sp, fa.lay, spec, Prec<T>::tw(c), s, c->part_b));
-                LCHK(c, launch_ypass<T>(+1, 3, fa.lay, spec, Prec<T>::tw(c), s));
-                LCHK(c, launch_reduce(c->part_b, nbz, c->scal, RED_BETA, 0, s, true));
-            }
+            // z = P y-inv(Z); p = z + beta p (x += alpha p_old) and D_y p; the rest of q = P A p with
+            // alpha = rz / p.q known before its last pass, which updates r -= alpha q ; r.r (iteration
+            // count, stop test) ; Z = M r with r.z on the spectrum ; beta = r.z_new / r.z_old
+            // (x += alpha p follows in the next p update)
+            LCHK(c, launch_ystart<T>(YS_PCG, c->sp, a, tw, s));
+            a.partials = c->part_b;
+            CHK(operator_middle<T>(c, a, c->scal));
+            a.partials = c->part_a;
+            LCHK(c, launch_yend<T>(YE_UPDATE, c->sp, a, tw, s));
+            const Carry rr_check{c->part_a, yend_blocks<T>(a.lay), c->scal, RED_RR_CHECK, 0};
+            CHK(precond_middle<T>(c, a.lay, r, ns, 0, S2, rr_check, c->part_b, RED_BETA, c->scal, 0));
         }
         CHK(read_scalars(c));
         it = (int)c->hscal[S_ITER];
@@ -676,8 +692,7 @@ int green_solve(nm_ctx* c, const double* rhs, double* x, double bref, double tol
 
 // Fields solved together by the Green route's unit-force solves: enough to give the kernels
 // about 8M voxels of work (small grids are bound by launches, not by memory traffic), at most
-// 16; options.green_batch overrides (1: one at a time).  1 when the launch layout does not keep
-// every field's partial sums apart.
+// 16; options.green_batch overrides (1: one at a time).
 int green_batch_size(nm_ctx* c)
 {
     int nb = c->opt.green_batch;
@@ -686,11 +701,7 @@ int green_batch_size(nm_ctx* c)
         while (nb < 16 && (long)nb * 2 * c->N <= (8L << 20)) nb *= 2;
     }
     if (nb > 64) nb = 64;
-    const long lpf = 3L * c->n2 * c->n3;
-    if (nb < 2 || (long)xfwd_blocks(c->n1, nb * lpf) != (long)nb * xfwd_blocks(c->n1, lpf) ||
-        (long)xinv_blocks(c->n1, nb * lpf) != (long)nb * xinv_blocks(c->n1, lpf))
-        return 1;
-    return nb;
+    return nb < 2 ? 1 : nb;
 }
 
 // Buffers of nb fields side by side in one precision: real fields [b][3][N], spectra
@@ -700,50 +711,15 @@ template <typename T> struct MultiBufs {
     cx_t<T>*S, *S2;
 };
 
-// Launch layout of nb fields side by side (3-component passes, the 6-component stress pass,
-// the column passes).
-struct MultiLayout {
-    SpecLayout lay3, lay6;
-    SpecParams sp;
-    long lpf;
-};
-MultiLayout multi_layout(nm_ctx* c, int nb)
+// Launch layout of nb fields side by side (one grid layer per field).
+Layout multi_layout(nm_ctx* c, int nb)
 {
-    MultiLayout m;
-    m.lpf = 3L * c->n2 * c->n3;
-    m.lay3 = c->lay;
-    m.lay3.stop = nullptr;
-    m.lay3.nb = nb;
-    m.lay3.bc = 3;
-    m.lay3.bs = 6 * c->lay.cs;
-    m.lay6 = m.lay3;
-    m.lay6.bc = 1;
-    m.sp = c->sp;
-    m.sp.stop = nullptr;
-    m.sp.bs = 6 * c->lay.cs;
-    m.sp.bk = nb;
-    return m;
-}
-
-// The six passes of q = A p after the x-forward one, for nb fields (S holds their x spectra).
-// partials (or null): per-block sums of p.q, field after field.
-template <typename T>
-int multi_operator_rest(nm_ctx* c, const MultiLayout& L, int nb, const MultiBufs<T>& m, const T* p, T* q,
-                        double* partials)
-{
-    hipStream_t s = c->stream;
-    const void* tw = Prec<T>::tw(c);
-    LCHK(c, launch_colop<T>(YOP_DERIV, L.sp, L.lay3, m.S, m.S2, tw, s));
-    LCHK(c, launch_colop<T>(ZOP_STRAIN, L.sp, L.lay3, m.S, m.S2, tw, s));
-    LCHK(c, launch_xstress<T>(c->n1, m.S2, L.lay6, c->phase, Prec<T>::C(c), tw, s));
-    LCHK(c, launch_colop<T>(YOP_DIV, L.sp, L.lay3, m.S, m.S2, tw, s));
-    LCHK(c, launch_colop<T>(ZOP_DIVZ, L.sp, L.lay3, m.S, m.S2, tw, s));
-    XInvArgs ia = xi_args(c, m.S, q, p, Prec<T>::rho(c), nullptr, partials);
-    ia.lay = L.lay3;
-    ia.nlines = nb * L.lpf;
-    ia.lines_per_batch = L.lpf;
-    LCHK(c, launch_xinv<T>(XI_OPERATOR, c->n1, ia, tw, s));
-    return NM_OK;
+    Layout l = c->lay;
+    l.stop = nullptr;
+    l.nb = nb;
+    l.bf = 3 * c->lay.ns;
+    l.bs = 6 * c->lay.cs;
+    return l;
 }
 
 // nb independent unmasked PCG loops in precision T through one chain of kernels, from x_b = 0
@@ -758,53 +734,32 @@ int pcg_multi_core(nm_ctx* c, int nb, const MultiBufs<T>& m, const double* thr2,
 {
     hipStream_t s = c->stream;
     const long n = 3 * c->N;
-    const MultiLayout L = multi_layout(c, nb);
-    const int nbx = xinv_blocks(c->n1, L.lpf), nbf = xfwd_blocks(c->n1, L.lpf), nbz = zprecond_blocks<T>(c->sp);
+    const Layout L = multi_layout(c, nb);
     const void* tw = Prec<T>::tw(c);
     for (int b = 0; b < nb; b++) {
         LCHK(c, launch_loop_init(c->mscal + b * S_COUNT, thr2[b], max_iter, 0, s));
         if (frozen[b]) LCHK(c, launch_fill<double>(c->mscal + b * S_COUNT + S_STOP, 1.0, 1, s));
     }
     LCHK(c, launch_fill<T>(m.x, (T)0, nb * n, s));
-    // z = M r as its x spectrum, r.z
-    XFwdArgs fa{};
-    fa.spec = m.S;
-    fa.lay = L.lay3;
-    fa.scal = c->mscal;
-    fa.nlines = nb * L.lpf;
-    fa.lines_per_batch = L.lpf;
-    fa.src = m.r;
-    LCHK(c, launch_xfwd<T>(XF_PLAIN, c->n1, fa, tw, s));
-    LCHK(c, launch_ypass<T>(-1, 3 * nb, L.lay3, m.S, tw, s));
-    LCHK(c, launch_zprecond<T>(L.sp, L.lay3, m.S, tw, s, c->mpb));
-    LCHK(c, launch_ypass<T>(+1, 3 * nb, L.lay3, m.S, tw, s));
-    LCHK(c, launch_reduce_multi(c->mpb, nbz, nb, c->mscal, RED_RZ_INIT, s));
-    XInvArgs pa = xi_args(c, m.S, nullptr, nullptr, nullptr, nullptr, nullptr);
-    pa.lay = L.lay3;
-    pa.nlines = nb * L.lpf;
-    pa.lines_per_batch = L.lpf;
-    pa.p = m.p;
-    pa.x = m.x;
-    pa.scal = c->mscal;
-    XFwdArgs fu = fa;
-    fu.src = nullptr;
-    fu.r = m.r;
-    fu.q = m.q;
-    fu.partials = c->mpa;
+    // z = M r as its y spectrum, r.z
+    CHK(precond_first<T>(c, L, m.r, m.r, L.ns, L.bf));
+    CHK(precond_middle<T>(c, L, m.r, L.ns, L.bf, m.S2, Carry{}, c->mpb, RED_RZ_INIT, c->mscal, 1));
+    PassArgs a = pass_args<T>(c, L, m.S, m.S2, m.p);
+    a.x = m.x;
+    a.r = m.r;
+    a.scal = c->mscal;
     int it = 0;
     for (;;) {
         for (int k = 0; k < 4; k++) {
-            // p = z + beta p (x += alpha p_old); q = A p; alpha
-            LCHK(c, launch_xpupdate<T>(c->n1, pa, tw, s));
-            CHK(multi_operator_rest<T>(c, L, nb, m, m.p, m.q, c->mpb));
-            LCHK(c, launch_reduce_multi(c->mpb, nbx, nb, c->mscal, RED_ALPHA, s));
-            // r -= alpha q, r.r (stop test); z = M r, r.z; beta
-            LCHK(c, launch_xfwd<T>(XF_UPDATE, c->n1, fu, tw, s));
-            LCHK(c, launch_reduce_multi(c->mpa, nbf, nb, c->mscal, RED_RR_CHECK, s));
-            LCHK(c, launch_ypass<T>(-1, 3 * nb, L.lay3, m.S, tw, s));
-            LCHK(c, launch_zprecond<T>(L.sp, L.lay3, m.S, tw, s, c->mpb));
-            LCHK(c, launch_ypass<T>(+1, 3 * nb, L.lay3, m.S, tw, s));
-            LCHK(c, launch_reduce_multi(c->mpb, nbz, nb, c->mscal, RED_BETA, s));
+            // p = z + beta p (x += alpha p_old); q = A p; alpha; r -= alpha q, r.r (stop test); z = M r,
+            // r.z; beta
+            LCHK(c, launch_ystart<T>(YS_PCG, c->sp, a, tw, s));
+            a.partials = c->mpb;
+            CHK(operator_middle<T>(c, a, c->mscal, 1));
+            a.partials = c->mpa;
+            LCHK(c, launch_yend<T>(YE_UPDATE, c->sp, a, tw, s));
+            const Carry rr_check{c->mpa, yend_blocks<T>(L), c->mscal, RED_RR_CHECK, 1};
+            CHK(precond_middle<T>(c, L, m.r, L.ns, L.bf, m.S2, rr_check, c->mpb, RED_BETA, c->mscal, 1));
         }
         HIPCHK(c, hipMemcpyAsync(c->mhscal, c->mscal, nb * S_COUNT * sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
@@ -839,16 +794,12 @@ int solve_multi(nm_ctx* c, int nb, double tol, int* iters_max)
     auto residuals = [&](bool x_zero) -> int {
         // R = rhs - A X (FP64; the zero start's residual is rhs itself), its FP32 copy, r.r
         if (!x_zero) {
-            const MultiLayout L = multi_layout(c, nb);
-            XFwdArgs fa{};
-            fa.spec = m64.S;
-            fa.lay = L.lay3;
-            fa.scal = c->mscal;
-            fa.nlines = nb * L.lpf;
-            fa.lines_per_batch = L.lpf;
-            fa.src = c->mX;
-            LCHK(c, launch_xfwd<double>(XF_PLAIN, c->n1, fa, c->tw64, s));
-            CHK(multi_operator_rest<double>(c, L, nb, m64, c->mX, c->mQ, nullptr));
+            const Layout L = multi_layout(c, nb);
+            PassArgs a = pass_args<double>(c, L, m64.S, m64.S2, c->mX);
+            a.out = c->mQ;
+            LCHK(c, launch_ystart<double>(YS_APPLY, c->sp, a, c->tw64, s));
+            CHK(operator_middle<double>(c, a));
+            LCHK(c, launch_yend<double>(YE_OUT, c->sp, a, c->tw64, s));
         } else {
             LCHK(c, launch_fill<double>(c->mQ, 0.0, nb * n, s));
         }
@@ -940,10 +891,9 @@ int build_green(nm_ctx* c, const double* G_in)
         const bool mixed = c->opt.precision == NM_PREC_MIXED;
         if (c->mnb < nb) {
             const long cs = c->lay.cs;
-            const long lpf = 3L * c->n2 * c->n3;
-            const int npa = xfwd_blocks(c->n1, lpf);
-            const int npb = std::max({xinv_blocks(c->n1, lpf), zprecond_blocks<double>(c->sp),
-                                      zprecond_blocks<float>(c->sp)});
+            const int npa = std::max(yend_blocks<double>(c->lay), yend_blocks<float>(c->lay));
+            const int npb = std::max({xstress_blocks<double>(c->lay), xstress_blocks<float>(c->lay),
+                                      xprecond_blocks<double>(c->lay), xprecond_blocks<float>(c->lay)});
             for (double** f : {&c->mX, &c->mR, &c->mP, &c->mQ, &c->mB}) CHK(dalloc(c, f, nb * n));
             CHK(dalloc(c, &c->mU, 3 * (size_t)nb));
             CHK(dalloc(c, &c->mS, nb * 6 * cs));
@@ -1035,23 +985,6 @@ void fill_twiddles(std::vector<double2>& t64)
         }
 }
 
-template <typename T> int precond_impl(nm_ctx* c, const T* r, T* z)
-{
-    XFwdArgs fa = xf_args(c, Prec<T>::spec(c));
-    fa.src = r;
-    XInvArgs ia = xi_args(c, Prec<T>::spec(c), z, r, Prec<T>::rho(c), nullptr, nullptr);
-    return chain_precond<T>(c, XF_PLAIN, fa, ia);
-}
-
-// z = P M r (Gamma voxels of the output zeroed), FP64.
-int precond_masked(nm_ctx* c, const double* r, double* z)
-{
-    XFwdArgs fa = xf_args(c, Prec<double>::spec(c));
-    fa.src = r;
-    XInvArgs ia = xi_args(c, Prec<double>::spec(c), z, r, Prec<double>::rho(c), c->mask, nullptr);
-    return chain_precond<double>(c, XF_PLAIN, fa, ia);
-}
-
 // x . y of two 3 x N FP64 fields (deterministic), on the host.
 int dot64(nm_ctx* c, const double* x, const double* y, double* out)
 {
@@ -1067,36 +1000,45 @@ int dot64(nm_ctx* c, const double* x, const double* y, double* out)
 template <typename T> int profile_impl(nm_ctx* c, int which, const T* in, T* out, int reps, double* ms)
 {
     hipStream_t s = c->stream;
-    void* spec = Prec<T>::spec(c);
     const void* tw = Prec<T>::tw(c);
-    const int np = which == 0 ? 7 : 5;
+    const int np = 5;
     hipEvent_t ev[10];
     for (int i = 0; i <= np; i++) HIPCHK(c, hipEventCreate(&ev[i]));
     std::vector<double> acc(np, 0.0);
-    XFwdArgs fa = xf_args(c, spec);
-    fa.src = in;
-    const uint8_t* nomask = nullptr;
-    XInvArgs ia = xi_args(c, spec, out, in, Prec<T>::rho(c), nomask, nullptr);
+    PassArgs a = pass_args<T>(c, in);
+    a.out = out;
+    const Layout& lay = c->lay;
+    void* S2 = a.S2;
+    ColFft f{}; // y-forward from r, z transforms in place, y-inverse to z
+    f.lay = lay;
+    f.src = f.dst = S2;
+    f.sc = f.dc = lay.cs;
+    const bool z3 = c->n3 > 1;
     int rc = NM_OK;
     for (int rep = 0; rep < reps && rc == NM_OK; rep++) {
         int k = 0;
         auto mark = [&]() { return hipEventRecord(ev[k++], s) == hipSuccess ? 0 : -2; };
         rc = mark();
         if (which == 0) {
-            void* spec2 = Prec<T>::spec2(c);
-            rc |= launch_xfwd<T>(XF_PLAIN, c->n1, fa, tw, s) | mark();
-            rc |= launch_colop<T>(YOP_DERIV, c->sp, c->lay, spec, spec2, tw, s) | mark();
-            rc |= launch_colop<T>(ZOP_STRAIN, c->sp, c->lay, spec, spec2, tw, s) | mark();
-            rc |= launch_xstress<T>(c->n1, spec2, c->lay, c->phase, Prec<T>::C(c), tw, s) | mark();
-            rc |= launch_colop<T>(YOP_DIV, c->sp, c->lay, spec, spec2, tw, s) | mark();
-            rc |= launch_colop<T>(ZOP_DIVZ, c->sp, c->lay, spec, spec2, tw, s) | mark();
-            rc |= launch_xinv<T>(XI_OPERATOR, c->n1, ia, tw, s) | mark();
+            rc |= launch_ystart<T>(YS_APPLY, c->sp, a, tw, s) | mark();
+            rc |= (z3 ? launch_zstrain<T>(c->sp, a, tw, s) : 0) | mark();
+            rc |= launch_xstress<T>(c->sp, a, tw, s) | mark();
+            rc |= (z3 ? launch_zdiv<T>(c->sp, a, tw, s) : 0) | mark();
+            rc |= launch_yend<T>(YE_OUT, c->sp, a, tw, s) | mark();
         } else {
-            rc |= launch_xfwd<T>(XF_PLAIN, c->n1, fa, tw, s) | mark();
-            rc |= launch_ypass<T>(-1, 3, c->lay, spec, tw, s) | mark();
-            rc |= launch_zprecond<T>(c->sp, c->lay, spec, tw, s) | mark();
-            rc |= launch_ypass<T>(+1, 3, c->lay, spec, tw, s) | mark();
-            rc |= launch_xinv<T>(XI_PRECOND, c->n1, ia, tw, s) | mark();
+            ColFft y0 = f, z0 = f, z1 = f, y1 = f;
+            y0.src = in;
+            y0.sc = lay.ns;
+            z0.axis = z1.axis = 2;
+            z1.dir = y1.dir = +1;
+            y1.dst = out;
+            y1.dc = lay.ns;
+            y1.zero3 = c->dim == 2;
+            rc |= launch_colfft<T>(y0, tw, s) | mark();
+            rc |= (z3 ? launch_colfft<T>(z0, tw, s) : 0) | mark();
+            rc |= launch_xprecond<T>(c->sp, lay, S2, lay.cs, 0, S2, tw, s, nullptr) | mark();
+            rc |= (z3 ? launch_colfft<T>(z1, tw, s) : 0) | mark();
+            rc |= launch_colfft<T>(y1, tw, s) | mark();
         }
         if (rc != 0) break;
         if (hipEventSynchronize(ev[np]) != hipSuccess) {
@@ -1192,17 +1134,16 @@ static int init_impl(nm_ctx* c, const nm_problem* pb, const nm_options* op)
     c->N = (long)c->n1 * c->n2 * c->n3;
     c->NS = c->N / 2;
     {
-        int l2 = 0;
-        while ((1 << l2) < c->n2) l2++;
-        c->lay.M = c->n1 / 2;
-        c->lay.n2 = c->n2;
-        c->lay.n3 = c->n3;
-        c->lay.log2n2 = l2;
-        // pad the plane and component strides of large spectra (power-of-two strides
-        // make the strided z pass collide in the memory system)
-        const long plane = (long)c->n2 * c->lay.M;
-        c->lay.ps = plane + (c->n3 > 1 && plane >= 4096 ? NM_PAD_PLANE : 0);
-        c->lay.cs = (long)c->n3 * c->lay.ps + (c->N >= (1L << 20) ? NM_PAD_COMP : 0);
+        Layout& l = c->lay;
+        l.M = c->n1 / 2;
+        while ((1 << l.log2M) < l.M) l.log2M++;
+        l.n1 = c->n1;
+        l.n2 = c->n2;
+        l.n3 = c->n3;
+        l.dim = c->dim;
+        l.ns = c->NS;
+        // pad the component stride of large work buffers off the powers of two
+        l.cs = c->NS + (c->N >= (1L << 20) ? NM_PAD_COMP : 0);
     }
     if (pb->n_phases < 1 || pb->n_phases > 65536) return fail(c, NM_EINVAL, "n_phases out of range");
     c->nph = pb->n_phases;
@@ -1363,8 +1304,9 @@ static int init_impl(nm_ctx* c, const nm_problem* pb, const nm_options* op)
     CHK(dalloc(c, &c->scal, S_COUNT));
     HIPCHK(c, hipMemset(c->scal, 0, S_COUNT * sizeof(double)));
     HIPCHK(c, hipHostMalloc((void**)&c->hscal, S_COUNT * sizeof(double), hipHostMallocDefault));
-    c->npart = std::max({xfwd_blocks(c->n1, 3L * c->n2 * c->n3), vec_blocks(n), zprecond_blocks<double>(c->sp),
-                         zprecond_blocks<float>(c->sp)});
+    c->npart = std::max({vec_blocks(n), yend_blocks<double>(c->lay), yend_blocks<float>(c->lay),
+                         xstress_blocks<double>(c->lay), xstress_blocks<float>(c->lay), xprecond_blocks<double>(c->lay),
+                         xprecond_blocks<float>(c->lay)});
     CHK(dalloc(c, &c->part_a, c->npart));
     CHK(dalloc(c, &c->winc, vec_blocks(3 * c->N)));
     CHK(dalloc(c, &c->part_b, c->npart));
@@ -1662,19 +1604,18 @@ static int explicit_impl(nm_ctx* c, const double* Udot, int per_point, int n_ste
     auto t0 = std::chrono::steady_clock::now();
     const double dt = c->dt;
     for (int k = 0; k < n_steps; k++) {
-        // u_n = u + dt v + dt^2/2 a, and its x spectrum
-        XFwdArgs fa = xf_args(c, c->spec64);
-        fa.u = c->u;
-        fa.v = c->v;
-        fa.a = c->a;
-        fa.dt = dt;
-        LCHK(c, launch_xfwd<double>(XF_EXPLICIT, c->n1, fa, c->tw64, s));
-        // (dt/2) div sigma(u_n) -> v <- v + dt/2 a + (dt/2) div sigma / rho, a <- div sigma / rho
-        XInvArgs ia = xi_args(c, c->spec64, nullptr, nullptr, c->rho64, nullptr, nullptr);
-        ia.p = c->v;
-        ia.x = c->a;
-        ia.dt = dt;
-        CHK(chain_operator_rest<double>(c, ia, XI_EXPLICIT, -0.5 * dt));
+        // u_n = u + dt v + dt^2/2 a, and its derivatives; (dt/2) div sigma(u_n)
+        // -> v <- v + dt/2 a + (dt/2) div sigma / rho, a <- div sigma / rho
+        PassArgs pa = pass_args<double>(c, c->u);
+        pa.v = c->v;
+        pa.a = c->a;
+        pa.dt = dt;
+        pa.bdt2 = -0.5 * dt;
+        LCHK(c, launch_ystart<double>(YS_EXPLICIT, c->sp, pa, c->tw64, s));
+        pa.rho = nullptr; // no inertia term
+        CHK(operator_middle<double>(c, pa));
+        pa.rho = c->rho64;
+        LCHK(c, launch_yend<double>(YE_EXPLICIT, c->sp, pa, c->tw64, s));
         // Gamma: the force that gives the prescribed velocity
         if (c->ng > 0)
             LCHK(c, launch_explicit_gamma(c->v, c->a, c->phase, c->rho64, c->gidx, c->ng, c->ubatch + (size_t)row * k,
@@ -1746,8 +1687,8 @@ int nm_precond_apply(nm_ctx* c, const void* r_dev, void* z_dev, int dtype)
     if (!c) return NM_EINVAL;
     if (c->explicit_scheme) return fail(c, NM_EINVAL, "the explicit scheme has no preconditioner");
     if (!r_dev || !z_dev || r_dev == z_dev) return fail(c, NM_EINVAL, "bad buffers");
-    if (dtype == NM_FP64) return precond_impl<double>(c, (const double*)r_dev, (double*)z_dev);
-    if (dtype == NM_FP32) return precond_impl<float>(c, (const float*)r_dev, (float*)z_dev);
+    if (dtype == NM_FP64) return apply_M<double>(c, (const double*)r_dev, (double*)z_dev, nullptr);
+    if (dtype == NM_FP32) return apply_M<float>(c, (const float*)r_dev, (float*)z_dev, nullptr);
     return fail(c, NM_EINVAL, "dtype must be NM_FP64 or NM_FP32");
 }
 
@@ -1917,7 +1858,7 @@ int nm_ws_residual_sample(nm_ctx* c, const double* U_next, int per_point, void* 
     double bref;
     CHK(projected_bref(c, c->w, &bref)); // leaves r_bar = P (b - A u_bar) in c->r
     if (crefM_out) {
-        CHK(precond_masked(c, c->r, c->z));
+        CHK(apply_M<double>(c, c->r, c->z, c->mask));
         CHK(dot64(c, c->r, c->z, crefM_out));
     }
     HIPCHK(c, hipMemcpyAsync(s_out, c->wscale, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1948,7 +1889,7 @@ int nm_ws_train_residual(nm_ctx* c, const void* feat_dev, const void* rp_dev, do
         CHK(norm2<double>(c, c->r, &val));
     } else {
         // L = r0 . (P M P r0) / cref
-        CHK(precond_masked(c, c->r, c->w));
+        CHK(apply_M<double>(c, c->r, c->w, c->mask));
         CHK(dot64(c, c->r, c->w, &val));
         wvec = c->w;
     }

@@ -9,6 +9,9 @@
 // (the Stockham autosort formulation), so the output lands in natural order
 // and the last stage writes straight back into the same register slots.
 // Radix R stages come first; a final smaller radix covers L / R^k.
+//
+// K sequences may be transformed together (v[K][R], one LDS area each): their stages share the
+// synchronisations and the twiddle reads, and their LDS latencies overlap.
 #pragma once
 #include "nm_common.h"
 
@@ -108,21 +111,26 @@ template <int DIR, typename V> struct Dft<16, DIR, V> {
     }
 };
 
-// LDS address maps.  Lines (one group of lanes per line, stride-1 reads and
-// stride-R writes in the first stages) use an XOR swizzle of the element index
-// inside aligned groups of 8 (16-byte elements) or 16 (8-byte elements), so
-// that both patterns spread over all banks without padding.
-template <int R, int ESIZE> struct LineAddr {
+// LDS layouts of the exchange between a stage (span Ns, radix Rs) and the next.  The stage's
+// thread j writes elements (j / Ns) Ns Rs + j mod Ns + r Ns, the next reads with stride 1.
+//
+// Lines (the lanes of a group are neighbours in one sequence): where Ns is below 16, Ns elements of
+// padding follow every Ns Rs, so that neighbouring lanes' writes fall on different banks (Ns (Rs + 1)
+// is an odd multiple of Ns); every access is one register plus a constant.  Sequence q of a batch
+// lies AREA elements behind sequence q - 1.
+template <int AREA> struct LineAddr {
     int base;
-    __device__ __forceinline__ int operator()(int p) const
-    {
-        constexpr int S = ESIZE >= 16 ? 3 : 4, MASK = (1 << S) - 1;
-        return base + (p ^ ((p >> S) & MASK));
-    }
+    static constexpr int pad(int Ns, int Rs) { return Ns < 16 && Rs >= 4 ? Ns : 0; }
+    __device__ __forceinline__ int operator()(int q, int p) const { return base + p + q * AREA; }
 };
-template <int R, int TX> struct ColAddr {
+// Elements of a padded line of L points (a stage of radix 2 is not padded).
+constexpr int line_elems(int L) { return L + L / 4; }
+// Column tiles: element p of column c at p * TX + c.  With TX >= 8 complex elements each group of
+// 8 consecutive lanes covers all banks, so no padding is needed.
+template <int TX> struct ColAddr {
     int c;
-    __device__ __forceinline__ int operator()(int p) const { return p * TX + c + p / R; }
+    static constexpr int pad(int, int) { return 0; }
+    __device__ __forceinline__ int operator()(int, int p) const { return p * TX + c; }
 };
 
 // Synchronisation between the stages' LDS writes and reads.  A group that
@@ -140,137 +148,91 @@ template <bool WAVE> __device__ __forceinline__ void group_sync()
     }
 }
 
-template <int L, int R> struct FftShape {
-    static constexpr int G = L / R;
-    static_assert(L % R == 0, "L must be a multiple of R");
-};
+// Ownership of the sequence outside the transform.  FFT_PLAIN: thread t owns t + m G.
+// FFT_PAIR_IN / FFT_PAIR_OUT: on entry / on exit slot b + 2 m holds element 2 t + b + 2 G m (b = 0, 1):
+// neighbouring elements come in pairs, as a thread that loads pairs of voxels has them.  The
+// stage at that end then has radix R / 2 and runs butterflies 2 t and 2 t + 1.
+enum FftEnds { FFT_PLAIN = 0, FFT_PAIR_IN = 1, FFT_PAIR_OUT = 2 };
 
-// Twiddle sources.  The stage of span Ns and radix Rs multiplies input r of butterfly
-// b (j = t + b G, k = j mod Ns) by w_L^(r k L / (Ns Rs)), w_L = exp(-2 pi i / L); the
-// inverse transform takes the conjugate.
-// TwTable reads the table w_L^i, i < L (in LDS); TwRegs holds the values a thread needs
-// for all stages in registers, read once from the table, for kernels that run many
-// transforms of one length.
-template <typename V> struct TwTable {
-    const V* p;
-    template <int L, int Ns, int Rs> __device__ __forceinline__ V get(int, int r, int k) const
-    {
-        return p[r * k * (L / (Ns * Rs))];
+// Radix of the stage of span Ns.
+template <int L, int R, int ENDS> constexpr int stage_radix(int Ns)
+{
+    if (ENDS == FFT_PAIR_IN && Ns == 1) return R / 2;
+    if (ENDS == FFT_PAIR_OUT) {
+        const int rest = L / (R / 2) / Ns; // before the last stage
+        return rest > 1 ? (rest < R ? rest : R) : R / 2;
     }
-};
+    return Ns * R <= L ? R : L / Ns;
+}
 
-template <int L, int R> struct FftPlan {
-    // twiddles per thread of the stages from span Ns on
-    static constexpr int count_from(int Ns)
-    {
-        int c = 0;
-        while (Ns < L) {
-            const int Rs = (Ns * R <= L) ? R : (L / Ns);
-            if (Ns > 1) c += (R / Rs) * (Rs - 1);
-            Ns *= Rs;
-        }
-        return c;
-    }
-    static constexpr int count() { return count_from(1); }
-    // index of the first twiddle of the stage of span Ns
-    static constexpr int offset(int Ns) { return count() - count_from(Ns); }
-};
-
-template <int L, int R, typename V> struct TwRegs {
-    using Plan = FftPlan<L, R>;
-    using S = decltype(V{}.x);
-    // clang vector element (an array of HIP's vector structs would stay in scratch memory)
-    typedef S E __attribute__((ext_vector_type(2)));
-    static constexpr int NT = Plan::count() > 0 ? Plan::count() : 1;
-    E w[NT];
-    template <int Ns> __device__ __forceinline__ void load_from(int t, const V* __restrict__ tab)
-    {
-        if constexpr (Ns < L) {
-            constexpr int Rs = (Ns * R <= L) ? R : (L / Ns);
-            constexpr int G = L / R, NB = R / Rs;
-            if constexpr (Ns > 1) {
-                constexpr int o = Plan::offset(Ns);
-#pragma unroll
-                for (int b = 0; b < NB; b++) {
-                    const int k = (t + b * G) & (Ns - 1);
-#pragma unroll
-                    for (int r = 1; r < Rs; r++) {
-                        const V x = tab[r * k * (L / (Ns * Rs))];
-                        w[o + b * (Rs - 1) + r - 1] = E{x.x, x.y};
-                    }
-                }
-            }
-            load_from<Ns * Rs>(t, tab);
-        }
-    }
-    __device__ __forceinline__ void load(int t, const V* __restrict__ tab) { load_from<1>(t, tab); }
-    template <int LL, int Ns, int Rs> __device__ __forceinline__ V get(int b, int r, int) const
-    {
-        static_assert(LL == L, "twiddle cache of another length");
-        constexpr int o = Plan::offset(Ns);
-        const E x = w[o + b * (Rs - 1) + r - 1];
-        return V{x.x, x.y};
-    }
-};
-
-// One Stockham stage (radix chosen from Ns) followed by the remaining stages.
-template <int L, int R, int DIR, int Ns, bool WAVE, typename V, typename Addr, typename Tw>
-__device__ __forceinline__ void fft_stage(V (&v)[R], int t, V* lds, const Addr& addr, const Tw& tw)
+// One Stockham stage (radix chosen from Ns) followed by the remaining stages; the exchange before
+// it was written with padding PAD after every Ns elements.
+template <int L, int R, int DIR, int Ns, int PAD, bool WAVE, int ENDS, int K, typename V, typename Addr>
+__device__ __forceinline__ void fft_stage(V (&v)[K][R], int t, V* lds, const Addr& addr, const V* tw)
 {
     if constexpr (Ns < L) {
-        constexpr int Rs = (Ns * R <= L) ? R : (L / Ns);
+        constexpr int Rs = stage_radix<L, R, ENDS>(Ns);
         constexpr int G = L / R;
         constexpr int NB = R / Rs;
         constexpr bool first = (Ns == 1);
         constexpr bool last = (Ns * Rs == L);
+        constexpr bool pair = (ENDS == FFT_PAIR_IN && first) || (ENDS == FFT_PAIR_OUT && last);
+        static_assert(!pair || NB == 2, "a paired end has two butterflies per thread");
         if constexpr (!first) {
+            // element j + r L / Rs of butterfly j; L / Rs is a multiple of Ns, and so are the steps
+            // G of j unless all of j's range lies within one span
+            constexpr int LR = L / Rs, step = LR + LR / Ns * PAD, bstep = G + G / Ns * PAD;
+            const int j0 = pair ? 2 * t : t;
+            const int p0 = j0 + j0 / Ns * PAD;
 #pragma unroll
-            for (int m = 0; m < R; m++) v[m] = lds[addr(t + m * G)];
+            for (int q = 0; q < K; q++)
+#pragma unroll
+                for (int b = 0; b < NB; b++)
+#pragma unroll
+                    for (int r = 0; r < Rs; r++) v[q][b + r * NB] = lds[addr(q, p0 + (pair ? b : b * bstep) + r * step)];
             group_sync<WAVE>();
         }
+        constexpr int WP = Addr::pad(Ns, Rs);
 #pragma unroll
         for (int b = 0; b < NB; b++) {
-            const int j = t + b * G;
+            const int j = pair ? 2 * t + b : t + b * G;
             const int k = j & (Ns - 1);
-            V a[Rs];
 #pragma unroll
-            for (int r = 0; r < Rs; r++) a[r] = v[b + r * NB];
-            if constexpr (Ns > 1) {
+            for (int q = 0; q < K; q++) {
+                V a[Rs];
 #pragma unroll
-                for (int r = 1; r < Rs; r++) {
-                    const V w = tw.template get<L, Ns, Rs>(b, r, k);
-                    a[r] = DIR > 0 ? cmulc(a[r], w) : cmul(a[r], w);
+                for (int r = 0; r < Rs; r++) a[r] = v[q][b + r * NB];
+                if constexpr (Ns > 1) {
+#pragma unroll
+                    for (int r = 1; r < Rs; r++) {
+                        const V w = tw[r * k * (L / (Ns * Rs))];
+                        a[r] = DIR > 0 ? cmulc(a[r], w) : cmul(a[r], w);
+                    }
                 }
-            }
-            Dft<Rs, DIR, V>::run(a);
-            if constexpr (last) {
+                Dft<Rs, DIR, V>::run(a);
+                if constexpr (last) {
 #pragma unroll
-                for (int r = 0; r < Rs; r++) v[b + r * NB] = a[r];
-            } else {
-                const int base = (j / Ns) * Ns * Rs + k;
+                    for (int r = 0; r < Rs; r++) v[q][b + r * NB] = a[r];
+                } else {
+                    const int base = (j / Ns) * (Ns * Rs + WP) + k;
 #pragma unroll
-                for (int r = 0; r < Rs; r++) lds[addr(base + r * Ns)] = a[r];
+                    for (int r = 0; r < Rs; r++) lds[addr(q, base + r * Ns)] = a[r];
+                }
             }
         }
         if constexpr (!last) group_sync<WAVE>();
-        fft_stage<L, R, DIR, Ns * Rs, WAVE>(v, t, lds, addr, tw);
+        fft_stage<L, R, DIR, Ns * Rs, WP, WAVE, ENDS, K>(v, t, lds, addr, tw);
     }
 }
 
-// Length-L transform of the group's sequence (see file comment).  tw is a twiddle
-// source (group_fft_tw) or points at the table w_L^i = exp(-2 pi i i / L), i < L.  Every
-// thread of the block must call it (it contains block barriers); on exit the LDS
-// area is free.
-template <int L, int R, int DIR, bool WAVE = false, typename V, typename Addr, typename Tw>
-__device__ __forceinline__ void group_fft_tw(V (&v)[R], int t, V* lds, const Addr& addr, const Tw& tw)
+// Length-L transforms of the group's K sequences (see file comment).  tw points at the table
+// w_L^i = exp(-2 pi i i / L), i < L (the inverse takes the conjugate).  Every thread of the block
+// (WAVE: of the wavefront) must call it; on exit the LDS area is free.
+template <int L, int R, int DIR, bool WAVE, int ENDS, int K, typename V, typename Addr>
+__device__ __forceinline__ void group_fft(V (&v)[K][R], int t, V* lds, const Addr& addr, const V* tw)
 {
     // The last stage's LDS reads are followed by a sync, so no trailing one is needed.
-    if constexpr (L > 1) fft_stage<L, R, DIR, 1, WAVE>(v, t, lds, addr, tw);
-}
-template <int L, int R, int DIR, bool WAVE = false, typename V, typename Addr>
-__device__ __forceinline__ void group_fft(V (&v)[R], int t, V* lds, const Addr& addr, const V* tw)
-{
-    group_fft_tw<L, R, DIR, WAVE>(v, t, lds, addr, TwTable<V>{tw});
+    if constexpr (L > 1) fft_stage<L, R, DIR, 1, 0, WAVE, ENDS, K>(v, t, lds, addr, tw);
 }
 
 // Offset of the table of length L (L = 2, 4, ..., 1024) inside the packed

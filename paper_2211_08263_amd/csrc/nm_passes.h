@@ -16,60 +16,27 @@ struct SpecParams {
     double bdt2;      // beta dt^2
     double rhobar;    // volume-averaged density
     double Cbar[21];  // volume-averaged Voigt stiffness (upper triangle, row major)
-    const double* stop = nullptr; // device flag: when non-zero, kernels given this struct exit at once
     // Finite-difference differentiation rules: device table of the frequency each bin's
     // derivative uses in place of the spectral xi (n1 + n2 + n3 entries, axis after axis, indexed
     // by bin), or null for the spectral derivative.
     const double* mfreq = nullptr;
-    // Several independent fields at once (multi-right-hand-side solves): bk fields whose
-    // spectra lie bs elements apart; the column passes take the field from blockIdx.z.
-    long bs = 0;
-    int bk = 1;
 };
 
-
-// Layout of a half-spectrum buffer: element (c, kz, ky, kx) at
-// c * cs + kz * ps + ky * M + kx.  The plane and component strides may carry
-// padding so that the strided z pass does not hit power-of-two strides.
-struct SpecLayout {
-    int M;          // n1 / 2
-    int n2, n3;
-    int log2n2;
-    long ps;        // kz (plane) stride, >= n2 * M
-    long cs;        // component stride, >= n3 * ps
-    const double* stop = nullptr; // device flag: when non-zero, kernels given this layout exit at once
-    // Several fields at once: nb fields of bc components each, bs elements apart (bc == 0: one
-    // field, components cs apart).
+// Geometry of one launch.  Every buffer is a set of components of n3 x n2 rows of M = n1/2
+// elements; an element V is a pair of neighbouring voxels (x, x + 1) in real space, or what the y
+// and z transforms make of it (the transforms of a pair run as one complex transform).
+// Several fields at once (multi-right-hand-side solves): nb fields, the real ones bf elements
+// apart, the work buffers bs elements apart, device scalars S_COUNT apart.
+struct Layout {
+    int M = 0, log2M = 0;
+    int n1 = 0, n2 = 0, n3 = 0;
+    int dim = 3;
+    long ns = 0; // component stride of the real fields (n1 n2 n3 / 2 elements)
+    long cs = 0; // component stride of the work buffers, >= ns (padded off powers of two)
+    long bf = 0, bs = 0;
     int nb = 1;
-    int bc = 0;
-    long bs = 0;
-    __host__ __device__ __forceinline__ long comp(long c) const { return bc ? (c / bc) * bs + (c % bc) * cs : c * cs; }
-    __host__ __device__ __forceinline__ long line(long l) const
-    {
-        // x line l = (component, kz, ky) in row-major order
-        const long yz = l % ((long)n2 * n3), c = l / ((long)n2 * n3);
-        return comp(c) + (yz >> log2n2) * ps + (yz & (n2 - 1)) * (long)M;
-    }
+    const double* stop = nullptr; // device flag: when non-zero, kernels given this layout exit at once
 };
-
-// Fused stage in front of the x-direction real-to-complex transform.
-// XF_UPDATE: r -= alpha q with the partial sums of r.r (the direction update is fused into
-// the preconditioner's last pass instead, launch_xpupdate).
-// XF_EXPLICIT: the displacement update u <- u + dt v + dt^2/2 a of the central-difference
-// scheme (written back to u) before the transform.
-enum XFwdMode { XF_PLAIN = 0, XF_UPDATE = 2, XF_EXPLICIT = 3 };
-// Fused stage after the x-direction complex-to-real transform.
-// XI_EXPLICIT: with o = (dt/2) div sigma from the transform, v <- v + dt/2 a + o/rho and
-// a <- 2 o / (dt rho) (central-difference velocity before the Gamma force; eq.
-// Explicit_linear_momentum_arranged_3D).
-enum XInvMode { XI_PLAIN = 0, XI_OPERATOR = 1, XI_PRECOND = 2, XI_EXPLICIT = 3 };
-// Axis-wise derivative stages of the operator on x-spectral (kx, y, z) data:
-//   YOP_DERIV : S[3+j] = D_y S[j], j < 3
-//   ZOP_STRAIN: S2 = Voigt strain (eps11, eps22, eps33, g23, g13, g12) / n1 from
-//               U = S[0..2] and D_y U = S[3..5] (D_x = i xi1, D_z by a z round trip)
-//   YOP_DIV   : S[0..2] = (i xi1 s11 + D_y s12, i xi1 s12 + D_y s22, i xi1 s13 + D_y s23), sigma in S2
-//   ZOP_DIVZ  : S[j] = -beta dt^2 / n1 (S[j] + D_z sigma_j3)
-enum ColOp { YOP_DERIV = 0, YOP_DIV = 1, ZOP_STRAIN = 2, ZOP_DIVZ = 3 };
 
 // Device scalar block shared by the Krylov kernels (all double).
 // S_STOP .. S_MODE drive a Krylov loop that runs several iterations between host checks:
@@ -80,68 +47,92 @@ enum ScalarSlot {
     S_STOP = 8, S_ITER = 9, S_THR2 = 10, S_LIMIT = 11, S_MODE = 12, S_COUNT = 16
 };
 
-struct XFwdArgs {
-    const void* src;      // XF_PLAIN: input field
-    void* u = nullptr;        // XF_EXPLICIT: displacement (in/out)
-    const void* v = nullptr;  // XF_EXPLICIT: velocity
-    const void* a = nullptr;  // XF_EXPLICIT: acceleration
-    double dt = 0.0;          // XF_EXPLICIT: time increment
-    void* r;              // XF_UPDATE: r (in/out)
-    const void* q;        // XF_UPDATE: q (in)
-    const double* scal;   // device scalars
-    double* partials;     // XF_UPDATE: per-block partial sums of r.r
-    void* spec;           // output half spectrum
-    SpecLayout lay;
-    long nlines;          // number of x lines (components x n2 x n3)
-    long lines_per_batch = 0; // several fields: x lines per field (their device scalars lie S_COUNT apart)
+// What a sum of per-block partials does to the scalar block.
+enum ReduceAction {
+    RED_NONE = -1, RED_STORE_RR = 0, RED_ALPHA = 1, RED_RZ_INIT = 2, RED_BETA = 3, RED_STORE_SLOT = 4, RED_RR_CHECK = 5
 };
 
-struct XInvArgs {
-    const void* spec;     // input half spectrum
-    SpecLayout lay;
-    void* out;            // output real field
-    const void* aux;      // XI_OPERATOR: p ; XI_PRECOND: r
-    const uint16_t* phase;
-    const void* rho;      // per-phase density (T)
-    const uint8_t* mask;  // Gamma voxel mask or null
-    double* partials;     // per-block partial dot products or null
-    long nlines;
-    long lines_per_comp;  // n2 * n3
-    int dim;
-    void* p = nullptr;            // launch_xpupdate: search direction (in/out); XI_EXPLICIT: velocity (in/out)
-    void* x = nullptr;            // launch_xpupdate: iterate (in/out); XI_EXPLICIT: acceleration (in/out)
-    double dt = 0.0;              // XI_EXPLICIT: time increment
-    const double* scal = nullptr; // launch_xpupdate: device scalars (alpha, beta, first)
-    long lines_per_batch = 0;     // several fields: x lines per field (their scalars lie S_COUNT apart)
+// A reduction carried by a column pass: its first block (one per field) sums n partials of the
+// pass before, field b's at part + b n, into scal + b S_COUNT.  multi: a loop whose S_STOP is set
+// is frozen (alpha = beta = 0) instead of skipped.
+struct Carry {
+    const double* part = nullptr;
+    int n = 0;
+    double* scal = nullptr;
+    int action = RED_NONE;
+    int multi = 0;
 };
 
-// Number of blocks a launch uses (sizes the partials array).
-int xfwd_blocks(int n1, long nlines);
-int xinv_blocks(int n1, long nlines);
+// First pass of the operator, y columns: D_y of the three components into work components 0..2.
+//   YS_APPLY    the field u as it is
+//   YS_EXPLICIT u <- u + dt v + dt^2/2 a first (central differences, eq. Central_diff_rule)
+//   YS_PCG      z = mask(y-inverse of Z), p = z + beta p, x += alpha p_old (p = z, x untouched while
+//               S_FIRST is set), then D_y p: the preconditioner's last pass, the direction update
+//               and the operator's first pass in one
+enum YStartMode { YS_APPLY = 0, YS_EXPLICIT = 1, YS_PCG = 2 };
+// Last pass of the operator, y columns: q_j = Q_j - beta dt^2 D_y sigma_2j.
+//   YE_OUT      q (masked) to out
+//   YE_UPDATE   R_j -= alpha y-forward(mask q_j), R the y spectrum of the residual, with the partial
+//               sums of r.r (Parseval)
+//   YE_EXPLICIT o = q: v <- v + dt/2 a + o / rho, a <- 2 o / (dt rho)
+enum YEndMode { YE_OUT = 0, YE_UPDATE = 1, YE_EXPLICIT = 2 };
 
-template <typename T> int launch_xfwd(int mode, int n1, const XFwdArgs& a, const void* tw, hipStream_t s);
-template <typename T> int launch_xinv(int mode, int n1, const XInvArgs& a, const void* tw, hipStream_t s);
-// In place on the half spectrum a.spec: z = mask(x-inverse), p = z + beta p with the
-// deferred x += alpha p_old (p = z while scal[S_FIRST] is set), spectrum <- x-forward(p).
-template <typename T> int launch_xpupdate(int n1, const XInvArgs& a, const void* tw, hipStream_t s);
-// In-place x-inverse, Voigt stress sigma = C_g : eps, x-forward on 6 components.
+struct PassArgs {
+    Layout lay;
+    void* S = nullptr;         // work buffer (6 components): derivatives, then stresses
+    void* S2 = nullptr;        // work buffer: preconditioner spectrum (0..2), inertia and divergence Q (3..5)
+    void* u = nullptr;         // YS_APPLY: field (in); YS_EXPLICIT: displacement (in/out)
+    void* p = nullptr;         // YS_PCG: search direction (in/out); z and x passes: the field derived
+    void* x = nullptr;         // YS_PCG: iterate (in/out)
+    void* v = nullptr;         // explicit scheme: velocity
+    void* a = nullptr;         // explicit scheme: acceleration
+    void* r = nullptr;         // YE_UPDATE: y spectrum of the residual (in/out)
+    void* out = nullptr;       // YE_OUT
+    const uint8_t* mask = nullptr;   // Gamma voxel mask or null
+    const uint16_t* phase = nullptr; // grain ids
+    const void* C21 = nullptr;       // per-grain stiffness
+    const void* rho = nullptr;       // per-grain density, or null (no inertia term)
+    double bdt2 = 0.0;               // the divergence is scaled by -bdt2
+    double dt = 0.0;                 // explicit scheme
+    const double* scal = nullptr;    // device scalars
+    double* partials = nullptr;      // per-block partial sums or null
+    Carry carry;
+};
+
+// One transform along a column axis, component by component: src (component stride sc, field stride
+// sb) to dst (dc, db), possibly in place; axis 1 = y, 2 = z; dir -1 forward, +1 inverse.  mask and
+// zero3 (the third component becomes zero) apply to real results.
+struct ColFft {
+    Layout lay;
+    const void* src = nullptr;
+    void* dst = nullptr;
+    long sc = 0, sb = 0, dc = 0, db = 0;
+    int axis = 1, dir = -1;
+    const uint8_t* mask = nullptr;
+    int zero3 = 0;
+    Carry carry;
+};
+
+// Number of partial sums per field that a pass leaves.
+template <typename T> int xstress_blocks(const Layout& lay);
+template <typename T> int yend_blocks(const Layout& lay);
+template <typename T> int xprecond_blocks(const Layout& lay);
+
+template <typename T> int launch_ystart(int mode, const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s);
+// z columns (3D only): S3 = D_z p_1, S2 <- D_z p_2 + S2, S4 = D_z p_3 (components of S).
+template <typename T> int launch_zstrain(const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s);
+// x lines: D_x p, strain, sigma = C : eps (in place on S), Q_j = rho p_j - bdt2 D_x sigma_1j;
+// partials: p . A p = sum rho p.p + bdt2 eps:sigma.
+template <typename T> int launch_xstress(const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s);
+// z columns (3D only): Q_j -= bdt2 D_z sigma_3j.
+template <typename T> int launch_zdiv(const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s);
+template <typename T> int launch_yend(int mode, const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s);
+template <typename T> int launch_colfft(const ColFft& f, const void* tw, hipStream_t s);
+// x lines of the preconditioner on the (y, z) spectrum src (component stride sc, field stride sb),
+// result to S2 components 0..2: x-forward, (beta dt^2 K + rhobar I)^-1 / (n1 n2 n3), x-inverse;
+// partials (or null): per-block sums of r . z (Parseval).
 template <typename T>
-int launch_xstress(int n1, void* spec, const SpecLayout& lay, const uint16_t* phase, const void* C21, const void* tw,
-                   hipStream_t s);
-// In-place transform of ncomp components along y (dir -1 forward, +1 inverse).
-template <typename T>
-int launch_ypass(int dir, int ncomp, const SpecLayout& lay, void* spec, const void* tw, hipStream_t s);
-// (the y pass reads lay.stop)
-// Axis-wise derivative stages of the operator (ColOp); S and S2 are two 6-component spectra.
-template <typename T>
-int launch_colop(int op, const SpecParams& sp, const SpecLayout& lay, void* S, void* S2, const void* tw,
-                 hipStream_t s);
-// Preconditioner z pass in place: z-forward, (beta dt^2 K + rhobar I)^-1, z-inverse.
-// partials (or null): per-block sums of r . z taken on the spectrum (Parseval), one per
-// block of zprecond_blocks<T>(sp).
-template <typename T>
-int launch_zprecond(const SpecParams& sp, const SpecLayout& lay, void* spec, const void* tw, hipStream_t s,
-                    double* partials = nullptr);
-template <typename T> int zprecond_blocks(const SpecParams& sp);
+int launch_xprecond(const SpecParams& sp, const Layout& lay, const void* src, long sc, long sb, void* S2, const void* tw,
+                    hipStream_t s, double* partials);
 
 } // namespace nm

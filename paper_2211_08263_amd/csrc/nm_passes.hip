@@ -1,154 +1,86 @@
 // FFT pass kernels of the operator of eq. (Fourier_ND_A) and of the
 // reference-medium preconditioner of eqs. (precond)-(acous), for gfx950.
 //
-// Data layout.  Real fields are SoA [component][z][y][x] with x fastest.
-// Half spectra are [component][kz][ky][kx] complex with kx in [0, n1/2):
-// slot kx = 0 holds X(0) + i X(n1/2) (both real after the x transform).
-// Because the discrete frequency of the Nyquist bin is taken as zero, the
-// kx = 0 and kx = n1/2 planes see the same multiplier, every multiplier is
-// Hermitian in (ky, kz), and the packed slot goes through the y/z passes
-// and the pointwise operators unchanged.  Forward transforms are
-// unnormalized, inverse ones too; 1/(n1 n2 n3) is folded into the spectral
-// multipliers.
+// Data layout.  Real fields are SoA [component][z][y][x] with x fastest and are read as pairs of
+// neighbouring voxels, V = (x, x + 1).  A transform along y or z of a pair is one complex transform
+// that carries two real columns, so the derivatives D_y and D_z (forward transform, i xi / n,
+// inverse transform) need no real-to-complex unpacking.  Along x, two neighbouring rows (y, y + 1)
+// form one complex line.  Forward transforms are unnormalized.
 //
-// Passes of one operator apply q = A p (7 kernels; the derivatives are taken
-// axis by axis, D_x as i xi1 on x spectra, D_y and D_z by single-axis round
-// trips, and every pointwise stage is fused into a transform pass):
-//   x-fwd (3) | y: U -> D_y U (3 -> 6) | z: strain (6 -> 6) |
-//   x-inv, sigma = C : eps, x-fwd (6) | y: D_y and i xi1 terms of div (5 -> 3) |
-//   z: D_z terms, -beta dt^2 scale (6 -> 3) | x-inv + rho p (3).
-// The preconditioner z = M r is x-fwd | y-fwd | z-fwd, (beta dt^2 K + rhobar I)^-1,
-// z-inv | y-inv | x-inv (3 components throughout).  Inside PCG its x-inv is fused with
-// the direction update and the x-fwd of the next operator apply (k_xpupdate), and the
-// residual update r -= alpha q rides on the preconditioner's x-fwd (XF_UPDATE).
+// Passes of one operator apply q = A p.  Every pass is one axis; the derivatives stay in real
+// space, and the x pass holds all six strains of its voxels, so D_x never goes to memory:
+//   y: D_y p_j (3 -> 3) | z: D_z p_j, joined with D_y p_3 to g23 (4 -> 3) |
+//   x: D_x p, strain, sigma = C : eps, Q_j = rho p_j - bdt2 D_x sigma_1j (8 -> 8) |
+//   z: Q_j -= bdt2 D_z sigma_3j (6 -> 3) | y: q_j = Q_j - bdt2 D_y sigma_2j (6 -> 3):
+// 47 fields moved.  (Taking D_x on x half-spectra instead, with the y and z derivatives between an
+// x-forward and an x-inverse pass, moves 62 in seven passes; at 256^3 that took 0.80 ms in FP32 and
+// 1.63 ms in FP64.)
+// The x pass also leaves p . A p = sum rho p.p + bdt2 eps : sigma (D is antisymmetric), so the step
+// length is known before the last pass, which then updates the residual instead of storing q.
+// The residual lives as its y spectrum R: the preconditioner z = M r goes on from there with
+//   z-forward | x: x-forward, (beta dt^2 K + rhobar I)^-1, x-inverse | z-inverse,
+// and its y-inverse is the next iteration's first pass (YS_PCG).  One iteration: eight passes, 80
+// fields (eleven passes and 104 fields before).
+// In 2D (n3 == 1) the z passes drop out: D_z = 0.
 #include "nm_common.h"
 #include "nm_fft.h"
 #include "nm_passes.h"
 
-// Strain components whose loads the stress pass keeps in flight ahead of its transforms
-// (FP64 holds fewer: its registers limit the occupancy).
-#ifndef NM_STRESS_PF64
-#define NM_STRESS_PF64 2
+#include <type_traits>
+
+// Nontemporal (streaming) loads (bit 0) and stores (bit 1), per pass and precision: what a whole solve
+// runs fastest with, as a pass's setting also moves the pass that reads its output.  Measured at
+// 256^3 (FP32: mixed step; FP64: PCG iteration): all plain 19.2 ms / 2.14 ms, all streaming 19.5 / 2.08,
+// stores only 19.2 / 2.14, loads only 18.6 / 2.09, these settings 17.7 / 1.96.
+#ifndef NM_NT_YS64
+#define NM_NT_YS64 3
 #endif
-// The stress pass keeps its twiddles in registers across its twelve transforms (measured at
-// 256^3: 6% faster in FP64; in FP32, 132 -> 136 VGPRs at the same occupancy, 1-2% faster with
-// the streaming accesses below, 5% slower before them).
-#ifndef NM_STRESS_TWREG64
-#define NM_STRESS_TWREG64 1
+#ifndef NM_NT_YS32
+#define NM_NT_YS32 3
 #endif
-#ifndef NM_STRESS_TWREG32
-#define NM_STRESS_TWREG32 1
+#ifndef NM_NT_ZS64
+#define NM_NT_ZS64 1
 #endif
-// Column passes address their tiles as a uniform base plus 32-bit lane offsets.
-#ifndef NM_COL_OFF32
-#define NM_COL_OFF32 1
+#ifndef NM_NT_ZS32
+#define NM_NT_ZS32 1
 #endif
-#ifndef NM_STRESS_PF32
-#define NM_STRESS_PF32 6
+#ifndef NM_NT_XS64
+#define NM_NT_XS64 3
 #endif
-// FP64 stress pass on 512-long x lines: one strain component's loads in flight instead of two
-// (measured at 512^3: 4.34 -> 3.17 ms; twiddles from LDS instead of registers 3.38 ms, radix 8
-// 4.07 ms)
-#ifndef NM_STRESS512_TWREG64
-#define NM_STRESS512_TWREG64 NM_STRESS_TWREG64
+#ifndef NM_NT_XS32
+#define NM_NT_XS32 3
 #endif
-#ifndef NM_STRESS512_PF64
-#define NM_STRESS512_PF64 1
+#ifndef NM_NT_ZD64
+#define NM_NT_ZD64 1
 #endif
-#ifndef NM_STRESS512_R64
-#define NM_STRESS512_R64 NM_STRESS_R64
+#ifndef NM_NT_ZD32
+#define NM_NT_ZD32 1
 #endif
-// Nontemporal (streaming) loads (bit 0) and stores (bit 1) of the spectra and fields that a
-// pass reads or writes once, per pass family and precision.  Measured at 256^3 (500 grains):
-// FP64 operator 1.72 -> 1.63 ms, preconditioner 0.91 -> 0.84 ms, Newmark step 40.7 -> 38.0 ms;
-// the FP32 passes gain less and lose where the preconditioner's column passes stream their
-// loads (0.43 -> 0.48 ms), so FP32 streams only the x passes and the column operators' stores
-// (mixed-precision step 24.3 -> 23.2 ms).
-#ifndef NM_STRESS_NT64
-#define NM_STRESS_NT64 3
+#ifndef NM_NT_YE64
+#define NM_NT_YE64 3
 #endif
-#ifndef NM_STRESS_NT32
-#define NM_STRESS_NT32 3
+#ifndef NM_NT_YE32
+#define NM_NT_YE32 3
 #endif
-#ifndef NM_XFWD_NT64
-#define NM_XFWD_NT64 3
+#ifndef NM_NT_CF64
+#define NM_NT_CF64 1
 #endif
-#ifndef NM_XFWD_NT32
-#define NM_XFWD_NT32 3
+#ifndef NM_NT_CF32
+#define NM_NT_CF32 1
 #endif
-#ifndef NM_XINV_NT64
-#define NM_XINV_NT64 3
+#ifndef NM_NT_XP64
+#define NM_NT_XP64 2
 #endif
-#ifndef NM_XINV_NT32
-#define NM_XINV_NT32 3
+#ifndef NM_NT_XP32
+#define NM_NT_XP32 0
 #endif
-#ifndef NM_XPUP_NT64
-#define NM_XPUP_NT64 3
-#endif
-#ifndef NM_XPUP_NT32
-#define NM_XPUP_NT32 3
-#endif
-#ifndef NM_YPASS_NT64
-#define NM_YPASS_NT64 2
-#endif
-#ifndef NM_YPASS_NT32
-#define NM_YPASS_NT32 0
-#endif
-#ifndef NM_COLOP_NT64
-#define NM_COLOP_NT64 3
-#endif
-#ifndef NM_COLOP_NT32
-#define NM_COLOP_NT32 2
-#endif
-#ifndef NM_ZPRE_NT64
-#define NM_ZPRE_NT64 2
-#endif
-#ifndef NM_ZPRE_NT32
-#define NM_ZPRE_NT32 0
-#endif
-#define NM_NT(FAM, T) (sizeof(T) == 8 ? NM_##FAM##_NT64 : NM_##FAM##_NT32)
-// FP32 x passes: a line group past the last line reads line 0 instead of skipping its loads, so
-// the loads carry no branch (measured: FP32 stress pass 214 -> 206 us at 256^3; the same in FP64
-// costs 30%, so FP64 keeps the guarded loads).
-#define NM_TAIL_LOADS(T) (sizeof(T) == 4)
-// per column operator (ColOp 0..3), defaulting to the family's setting.  The FP32 strain pass
-// (ZOP_STRAIN) streams its loads as well: 170 -> 151 us at 256^3, FP32 operator 0.856 -> 0.838 ms
-// (the same pass's setting moves the FP64 stress pass after it by up to 20 us either way, and the
-// FP64 operator by no more than the noise, so FP64 keeps the family setting).
-#ifndef NM_COLOP2_NT32
-#define NM_COLOP2_NT32 3
-#endif
-#ifndef NM_COLOP0_NT64
-#define NM_COLOP0_NT64 NM_COLOP_NT64
-#endif
-#ifndef NM_COLOP0_NT32
-#define NM_COLOP0_NT32 NM_COLOP_NT32
-#endif
-#ifndef NM_COLOP1_NT64
-#define NM_COLOP1_NT64 NM_COLOP_NT64
-#endif
-#ifndef NM_COLOP1_NT32
-#define NM_COLOP1_NT32 NM_COLOP_NT32
-#endif
-#ifndef NM_COLOP2_NT64
-#define NM_COLOP2_NT64 NM_COLOP_NT64
-#endif
-#ifndef NM_COLOP2_NT32
-#define NM_COLOP2_NT32 NM_COLOP_NT32
-#endif
-#ifndef NM_COLOP3_NT64
-#define NM_COLOP3_NT64 NM_COLOP_NT64
-#endif
-#ifndef NM_COLOP3_NT32
-#define NM_COLOP3_NT32 NM_COLOP_NT32
-#endif
-#define NM_COLOP_OP_NT(OP, T)                                                                                          \
-    ((OP) == 0   ? (sizeof(T) == 8 ? NM_COLOP0_NT64 : NM_COLOP0_NT32)                                                     \
-     : (OP) == 1 ? (sizeof(T) == 8 ? NM_COLOP1_NT64 : NM_COLOP1_NT32)                                                     \
-     : (OP) == 2 ? (sizeof(T) == 8 ? NM_COLOP2_NT64 : NM_COLOP2_NT32)                                                     \
-                 : (sizeof(T) == 8 ? NM_COLOP3_NT64 : NM_COLOP3_NT32))
+#define NM_NT(FAM, T) (sizeof(T) == 8 ? NM_NT_##FAM##64 : NM_NT_##FAM##32)
 
 namespace nm {
+
+// Wavefronts per SIMD that the register allocation of a pass aims at.
+constexpr int kXStressWaves64 = 2, kXStressWaves32 = 3, kXPrecondWaves64 = 2, kXPrecondWaves32 = 3, kColWaves64 = 2,
+              kColWaves32 = 3;
 
 // Early exit of a guarded kernel once the Krylov loop has stopped (uniform branch).
 __device__ __forceinline__ bool stopped(const double* stop) { return stop && *stop != 0.0; }
@@ -163,350 +95,422 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Block sum for 256-thread blocks, valid in thread 0.
-__device__ __forceinline__ double block_sum256(double v)
+// Block sum, valid in thread 0 (blocks of whole wavefronts).
+__device__ __forceinline__ double block_sum(double v)
 {
-    __shared__ double sh[kBlock / 64];
+    __shared__ double sh[16];
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
     double s = 0.0;
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int i = 0; i < kBlock / 64; i++) s += sh[i];
-    }
+    if (threadIdx.x == 0)
+        for (int i = 0; i < (int)blockDim.x / 64; i++) s += sh[i];
     return s;
 }
 
-// R2C post-processing: from Z = FFT_M(x[2n] + i x[2n+1]) to the packed
-// half spectrum X(k), k < M, with X(0) + i X(M) in slot 0.  zk = Z[k],
-// zm = Z[(M-k) mod M], wk = exp(-2 pi i k / N1).
-template <typename V> __device__ __forceinline__ V r2c_post(int k, V zk, V zm, V wk)
+// The reduction a pass carries (see Carry): run by the first block of every field, beside the
+// pass's own blocks, so that it costs no launch of its own.
+__device__ __forceinline__ void carry_reduce(const Carry& c, int field)
 {
-    using S = decltype(zk.x);
-    if (k == 0) return V{zk.x + zk.y, zk.x - zk.y};
-    V zc = conjv(zm);
-    V e = cscale(cadd(zk, zc), (S)0.5);
-    V d = csub(zk, zc);
-    V o = V{(S)0.5 * d.y, (S)-0.5 * d.x}; // (zk - conj zm) / (2 i)
-    return cadd(e, cmul(wk, o));
-}
-
-// C2R pre-processing: Z[k] = (X[k] + conj X[M-k]) + i w^k (X[k] - conj X[M-k]),
-// w = exp(+2 pi i / N1); slot 0 carries X(0) + i X(M).
-template <typename V> __device__ __forceinline__ V c2r_pre(int k, V xk, V xm, V wk_fwd)
-{
-    if (k == 0) return V{xk.x + xk.y, xk.x - xk.y};
-    V xc = conjv(xm);
-    V a = cadd(xk, xc);
-    V b = csub(xk, xc);
-    V wb = cmul(conjv(wk_fwd), b);
-    return V{a.x - wb.y, a.y + wb.x};
+    const double* part = c.part + (long)field * c.n;
+    double* scal = c.scal + (long)field * S_COUNT;
+    double v = 0.0;
+    for (int i = threadIdx.x; i < c.n; i += blockDim.x) v += part[i];
+    const double s = block_sum(v);
+    if (threadIdx.x != 0) return;
+    const bool frozen = c.multi && scal[S_STOP] != 0.0;
+    switch (c.action) {
+    case RED_RR_CHECK: {
+        if (frozen) break;
+        scal[S_RR] = s;
+        const double it = scal[S_ITER] + 1.0;
+        scal[S_ITER] = it;
+        const bool done = scal[S_MODE] != 0.0 ? it >= scal[S_LIMIT]
+                                              : (s <= scal[S_THR2] || it >= scal[S_LIMIT] || !(s < 1e300));
+        if (done) scal[S_STOP] = 1.0;
+        break;
+    }
+    case RED_ALPHA:
+        scal[S_PQ] = s;
+        scal[S_ALPHA] = frozen ? 0.0 : scal[S_RZ] / s;
+        break;
+    case RED_RZ_INIT:
+        scal[S_RZ] = s;
+        scal[S_FIRST] = 1.0;
+        break;
+    case RED_BETA:
+        scal[S_BETA] = frozen ? 0.0 : s / scal[S_RZ];
+        scal[S_RZ] = s;
+        scal[S_FIRST] = 0.0;
+        break;
+    default: break;
+    }
 }
 
 // Copy the twiddle table of length L into LDS (block-cooperative; the caller
 // synchronizes the block before use).
 template <int L, typename V> __device__ __forceinline__ void stage_twiddles(V* dst, const V* __restrict__ tw)
 {
-    if constexpr (L >= 2) {
-        for (int i = threadIdx.x; i < L; i += blockDim.x) dst[i] = tw[tw_offset(L) + i];
-    }
+    for (int i = threadIdx.x; i < L; i += blockDim.x) dst[i] = tw[tw_offset(L) + i];
 }
+
+// Frequency (times 1/n, the round trip's normalization) of the bins of one axis.
+struct AxisFreq {
+    const double* mf; // table of the finite-difference rules, or null
+    double k, inv_n;
+    int n;
+    __device__ __forceinline__ double at(int b) const { return (mf ? mf[b] : k * freq_index(b, n)) * inv_n; }
+};
+
+// The axis frequencies in LDS, beside the twiddles: computed per point in registers they would put a
+// branch (table or formula) and a conversion in front of every multiplication.
+template <int L, typename T> __device__ __forceinline__ void stage_freq(T* dst, const AxisFreq& f)
+{
+    for (int i = threadIdx.x; i < L; i += blockDim.x) dst[i] = (T)f.at(i);
+}
+
+// multiply by i s
+template <typename V, typename S> __device__ __forceinline__ V iscale(V a, S s) { return V{-a.y * s, a.x * s}; }
 
 // ---------------------------------------------------------------------------
-// x direction: real lines of N1 points, M = N1/2 complex points per line
+// y and z directions: tiles of TX consecutive columns of L points, one component per block.
+// A thread holds R points of one column and the block L / R threads per column, so that every row
+// of a tile is TX elements (128 bytes in FP32, 256 in FP64) wide.  Bound by HBM: 256^3 FP32 / FP64, us
+// and TB/s: y start (6 fields) 78 / 149, 5.2 / 5.4; z strain (7) 96 / 157, 4.9 / 6.0; z divergence (9)
+// 109 / 202, 5.5 / 6.0; y end (9) 98 / 204, 6.2 / 5.9; transforms alone (6) 66 / 150, 6.1 / 5.4.
+// One component per block keeps two operands in registers at most, so that the loads of other
+// blocks cover a block's transforms.  Rows half as wide (radix 8 or 128 threads): FP32 y start 106-113,
+// z divergence 157-162 us, FP64 1.30 against 1.24 ms for the operator.  Radix 8 with 512 threads is no
+// different from radix 16 with 256.
 // ---------------------------------------------------------------------------
-template <typename T, int N1, int R, int MODE>
-__global__ __launch_bounds__(kBlock) void k_xfwd(XFwdArgs a, const cx_t<T>* __restrict__ tw)
-{
-    if (stopped(a.lay.stop)) return;
-    using V = cx_t<T>;
-    constexpr int M = N1 / 2, G = M / R, LPB = kBlock / G, LP = M;
-    static_assert(G <= 64, "an x line must live inside one wavefront");
-    __shared__ V lds[LPB * LP];
-    __shared__ V twsm[M + N1];
-    stage_twiddles<M>(twsm, tw);
-    stage_twiddles<N1>(twsm + M, tw);
-    __syncthreads();
-    const V* twM = twsm;
-    const V* twN = twsm + M;
-    const int tid = threadIdx.x, ll = tid / G, t = tid % G;
-    const long line = (long)blockIdx.x * LPB + ll;
-    const bool valid = line < a.nlines;
-    const long off = line * M;
-    V v[R];
-    double part = 0.0;
-#pragma unroll
-    for (int m = 0; m < R; m++) v[m] = V{0, 0};
-    if (valid) {
-        if constexpr (MODE == XF_PLAIN) {
-            const V* src = (const V*)a.src + off;
-#pragma unroll
-            for (int m = 0; m < R; m++) v[m] = ld_nt<NM_NT(XFWD, T)>(src + t + m * G);
-        } else if constexpr (MODE == XF_EXPLICIT) {
-            // u_n = u_{n-1} + dt v_{n-1} + dt^2/2 a_{n-1}   (eq. Central_diff_rule)
-            const T dt = (T)a.dt, h2 = (T)(0.5 * a.dt * a.dt);
-            V* u = (V*)a.u + off;
-            const V* vv = (const V*)a.v + off;
-            const V* aa = (const V*)a.a + off;
-#pragma unroll
-            for (int m = 0; m < R; m++) {
-                const int i = t + m * G;
-                const V uo = ld_nt<NM_NT(XFWD, T)>(u + i), vo = ld_nt<NM_NT(XFWD, T)>(vv + i),
-                        ao = ld_nt<NM_NT(XFWD, T)>(aa + i);
-                const V un = V{uo.x + dt * vo.x + h2 * ao.x, uo.y + dt * vo.y + h2 * ao.y};
-                st_nt<NM_NT(XFWD, T)>(u + i, un);
-                v[m] = un;
-            }
-        } else {
-            // r -= alpha q and the partial sums of r.r
-            const T alpha = (T)a.scal[(a.lines_per_batch ? line / a.lines_per_batch : 0) * S_COUNT + S_ALPHA];
-            V* r = (V*)a.r + off;
-            const V* q = (const V*)a.q + off;
-#pragma unroll
-            for (int m = 0; m < R; m++) {
-                const int i = t + m * G;
-                V qq = ld_nt<NM_NT(XFWD, T)>(q + i), rr = ld_nt<NM_NT(XFWD, T)>(r + i);
-                rr = V{rr.x - alpha * qq.x, rr.y - alpha * qq.y};
-                st_nt<NM_NT(XFWD, T)>(r + i, rr);
-                part += (double)rr.x * (double)rr.x + (double)rr.y * (double)rr.y;
-                v[m] = rr;
-            }
-        }
-    }
-    LineAddr<R, (int)sizeof(V)> addr{ll * LP};
-    group_fft<M, R, -1, true>(v, t, lds, addr, twM);
-#pragma unroll
-    for (int m = 0; m < R; m++) lds[addr(t + m * G)] = v[m];
-    group_sync<true>();
-    V mir[R];
-#pragma unroll
-    for (int m = 0; m < R; m++) mir[m] = lds[addr((M - (t + m * G)) & (M - 1))];
-    if (valid) {
-        V* out = (V*)a.spec + a.lay.line(line);
-#pragma unroll
-        for (int m = 0; m < R; m++) {
-            const int k = t + m * G;
-            st_nt<NM_NT(XFWD, T)>(out + k, r2c_post(k, v[m], mir[m], twN[k]));
-        }
-    }
-    if constexpr (MODE == XF_UPDATE) {
-        double s = block_sum256(part);
-        if (threadIdx.x == 0) a.partials[blockIdx.x] = s;
-    }
-}
+// Columns of an axis: column c starts at (c >> sh) * hi + (c & mask), its points lie step apart.
+struct Cols {
+    int ncols, sh, mask;
+    long hi, step;
+};
 
-template <typename T, int N1, int R, int MODE>
-__global__ __launch_bounds__(kBlock) void k_xinv(XInvArgs a, const cx_t<T>* __restrict__ tw)
-{
-    if (stopped(a.lay.stop)) return;
-    using V = cx_t<T>;
-    constexpr int M = N1 / 2, G = M / R, LPB = kBlock / G, LP = M;
-    static_assert(G <= 64, "an x line must live inside one wavefront");
-    __shared__ V lds[LPB * LP];
-    __shared__ V twsm[M + N1];
-    stage_twiddles<M>(twsm, tw);
-    stage_twiddles<N1>(twsm + M, tw);
-    __syncthreads();
-    const V* twM = twsm;
-    const V* twN = twsm + M;
-    const int tid = threadIdx.x, ll = tid / G, t = tid % G;
-    const long line = (long)blockIdx.x * LPB + ll;
-    const bool valid = line < a.nlines;
-    const bool ld_ok = NM_TAIL_LOADS(T) || valid;
-    const long lineA = NM_TAIL_LOADS(T) && !valid ? 0 : line;
-    const long off = lineA * M;
-    V v[R];
-    const long soff = a.lay.line(lineA);
-#pragma unroll
-    for (int m = 0; m < R; m++) v[m] = ld_ok ? ld_nt<NM_NT(XINV, T)>((const V*)a.spec + soff + t + m * G) : V{0, 0};
-    // the real-space operands of the fused stage are fetched before the transform
-    V au[R];
-    uint32_t ph[R];
-    uint16_t mk[R];
-    const long vline = lineA % a.lines_per_comp;
-    V ao[R];
-    if constexpr (MODE == XI_EXPLICIT) {
-        const V* vp = (const V*)a.p + off;
-        const V* ap = (const V*)a.x + off;
-#pragma unroll
-        for (int m = 0; m < R; m++) {
-            const int n = t + m * G;
-            au[m] = ld_ok ? ld_nt<NM_NT(XINV, T)>(vp + n) : V{0, 0};
-            ao[m] = ld_ok ? ld_nt<NM_NT(XINV, T)>(ap + n) : V{0, 0};
-            ph[m] = ld_ok ? ((const uint32_t*)a.phase)[vline * M + n] : 0u;
-            mk[m] = 0;
-        }
-    } else if constexpr (MODE != XI_PLAIN) {
-        const V* aux = (const V*)a.aux + off;
-#pragma unroll
-        for (int m = 0; m < R; m++) {
-            const int n = t + m * G;
-            au[m] = (ld_ok && a.aux) ? ld_nt<NM_NT(XINV, T)>(aux + n) : V{0, 0};
-            ph[m] = (ld_ok && MODE == XI_OPERATOR) ? ((const uint32_t*)a.phase)[vline * M + n] : 0u;
-            mk[m] = (ld_ok && a.mask) ? ((const uint16_t*)a.mask)[vline * M + n] : (uint16_t)0;
-        }
-    }
-    LineAddr<R, (int)sizeof(V)> addr{ll * LP};
-#pragma unroll
-    for (int m = 0; m < R; m++) lds[addr(t + m * G)] = v[m];
-    group_sync<true>();
-#pragma unroll
-    for (int m = 0; m < R; m++) {
-        const int k = t + m * G;
-        V xm = lds[addr((M - k) & (M - 1))];
-        v[m] = c2r_pre(k, v[m], xm, twN[k]);
-    }
-    group_sync<true>();
-    group_fft<M, R, +1, true>(v, t, lds, addr, twM);
-    double part = 0.0;
-    if (valid) {
-        V* out = (V*)a.out + off;
-        if constexpr (MODE == XI_PLAIN) {
-#pragma unroll
-            for (int m = 0; m < R; m++) st_nt<NM_NT(XINV, T)>(out + t + m * G, v[m]);
-        } else if constexpr (MODE == XI_EXPLICIT) {
-            // o = dt/2 div sigma: v <- v + dt/2 a + o / rho, a <- (2/dt) o / rho
-            const bool zero_comp = (a.dim == 2) && ((line / a.lines_per_comp) % 3 == 2);
-            const T* rho = (const T*)a.rho;
-            const T hdt = (T)(0.5 * a.dt), idt2 = (T)(2.0 / a.dt);
-            V* vp = (V*)a.p + off;
-            V* ap = (V*)a.x + off;
-#pragma unroll
-            for (int m = 0; m < R; m++) {
-                const int n = t + m * G;
-                const T r0 = rho[ph[m] & 0xffffu], r1 = rho[ph[m] >> 16];
-                const V o = v[m];
-                V vn = V{au[m].x + hdt * ao[m].x + o.x / r0, au[m].y + hdt * ao[m].y + o.y / r1};
-                V an = V{idt2 * o.x / r0, idt2 * o.y / r1};
-                if (zero_comp) {
-                    vn = V{0, 0};
-                    an = V{0, 0};
-                }
-                st_nt<NM_NT(XINV, T)>(vp + n, vn);
-                st_nt<NM_NT(XINV, T)>(ap + n, an);
-            }
-        } else {
-            const bool zero_comp = (a.dim == 2) && ((line / a.lines_per_comp) % 3 == 2);
-            const T* rho = (const T*)a.rho;
-#pragma unroll
-            for (int m = 0; m < R; m++) {
-                const int n = t + m * G;
-                V o = v[m];
-                if constexpr (MODE == XI_OPERATOR) {
-                    o.x += rho[ph[m] & 0xffffu] * au[m].x;
-                    o.y += rho[ph[m] >> 16] * au[m].y;
-                }
-                if (mk[m] & 0x00ffu) o.x = 0;
-                if (mk[m] & 0xff00u) o.y = 0;
-                if (zero_comp) o = V{0, 0};
-                part += (double)au[m].x * (double)o.x + (double)au[m].y * (double)o.y;
-                st_nt<NM_NT(XINV, T)>(out + n, o);
-            }
-        }
-    }
-    if constexpr (MODE != XI_PLAIN && MODE != XI_EXPLICIT) {
-        double s = block_sum256(part);
-        if (threadIdx.x == 0 && a.partials) a.partials[blockIdx.x] = s;
-    }
-}
+template <typename T, int L> struct ColShape {
+    static constexpr int R = L <= 16 ? L : (L <= 64 ? 8 : 16);
+    static constexpr int G = L / R;
+    static constexpr int BLK = (L == 512 && sizeof(T) == 4) ? 512 : 256;
+    static constexpr int W = sizeof(T) == 8 ? kColWaves64 : kColWaves32; // wavefronts per SIMD
+    static constexpr int TX = BLK / G;
+};
 
-// Last pass of the preconditioner fused with the first pass of the next operator apply
-// (in place on the half spectrum): z = P x-inv(Z) (the preconditioned residual, masked
-// on Gamma), p = z + beta p and the deferred x += alpha p_old (p = z on the first
-// iteration), then the x-forward transform of the new p overwrites the line.  The
-// preconditioned residual never goes to memory.
-template <typename T, int N1, int R>
-__global__ __launch_bounds__(kBlock) void k_xpupdate(XInvArgs a, const cx_t<T>* __restrict__ tw)
+template <typename T, int L> struct ColTile {
+    using V = cx_t<T>;
+    using Sh = ColShape<T, L>;
+    static constexpr int R = Sh::R, G = Sh::G, TX = Sh::TX;
+    int t;
+    bool valid;
+    uint32_t lane, mstep; // byte offsets: of the thread's first point; between its points (uniform)
+    ColAddr<TX> addr;
+    __device__ __forceinline__ ColTile(const Cols& g, int tile)
+    {
+        const int c = threadIdx.x % TX;
+        t = threadIdx.x / TX;
+        addr.c = c;
+        const int col = tile * TX + c;
+        valid = col < g.ncols;
+        const int cc = valid ? col : 0; // surplus lanes read column 0 and store nothing
+        const long off = (long)(cc >> g.sh) * g.hi + (cc & g.mask) + (long)t * g.step;
+        lane = (uint32_t)(off * sizeof(V));
+        mstep = (uint32_t)(G * g.step * sizeof(V));
+    }
+    // element index of point m within the component
+    __device__ __forceinline__ uint32_t elem(int m) const { return (lane + (uint32_t)m * mstep) / (uint32_t)sizeof(V); }
+    // point m of the column (a scalar base, the thread's offset and nothing else per lane)
+    template <typename P> __device__ __forceinline__ P* at(P* base, int m) const
+    {
+        using C = std::conditional_t<std::is_const_v<P>, const char, char>;
+        return (P*)((C*)base + (uint64_t)m * mstep + lane);
+    }
+    template <int NT> __device__ __forceinline__ void ld(const V* base, V (&v)[R]) const
+    {
+#pragma unroll
+        for (int m = 0; m < R; m++) v[m] = ld_nt<NT>(at(base, m));
+    }
+    template <int NT> __device__ __forceinline__ void st(V* base, const V (&v)[R]) const
+    {
+        if (!valid) return;
+#pragma unroll
+        for (int m = 0; m < R; m++) st_nt<NT>(at(base, m), v[m]);
+    }
+    template <int DIR> __device__ __forceinline__ void fft(V (&v)[R], V* lds, const V* tw) const
+    {
+        group_fft<L, R, DIR, false, FFT_PLAIN, 1>((V(&)[1][R])v, t, lds, addr, tw);
+    }
+    // v <- D v
+    __device__ __forceinline__ void deriv(V (&v)[R], V* lds, const V* tw, const T* fr) const
+    {
+        fft<-1>(v, lds, tw);
+#pragma unroll
+        for (int m = 0; m < R; m++) v[m] = iscale(v[m], fr[t + m * G]);
+        fft<+1>(v, lds, tw);
+    }
+    __device__ __forceinline__ void masked(const uint8_t* mask, V (&v)[R]) const
+    {
+#pragma unroll
+        for (int m = 0; m < R; m++) {
+            const uint16_t k = ((const uint16_t*)mask)[elem(m)];
+            if (k & 0x00ffu) v[m].x = 0;
+            if (k & 0xff00u) v[m].y = 0;
+        }
+    }
+};
+// Component and tile of a block: in FP32 the three components of a tile are neighbours, in FP64 one
+// component follows the other (256^3: FP32 mixed step 18.2 -> 17.9 ms, FP64 iteration 1.96 against
+// 1.99 ms with the FP32 order).
+template <typename T> __device__ __forceinline__ int col_comp(int blk, int ntiles)
+{
+    return sizeof(T) == 4 ? blk % 3 : blk / ntiles;
+}
+template <typename T> __device__ __forceinline__ int col_tile(int blk, int ntiles)
+{
+    return sizeof(T) == 4 ? blk / 3 : blk % ntiles;
+}
+#define NM_COL_LDS(L)                                                                                                  \
+    __shared__ V lds[ColShape<T, L>::G > 1 ? ColShape<T, L>::BLK * ColShape<T, L>::R : 1];                             \
+    __shared__ V tws[L];                                                                                               \
+    if constexpr (ColShape<T, L>::G > 1) stage_twiddles<L>(tws, tw);
+// the same with the axis frequencies, published to the block
+#define NM_COL_LDS_FREQ(L)                                                                                             \
+    NM_COL_LDS(L)                                                                                                      \
+    __shared__ T frs[L];                                                                                               \
+    stage_freq<L>(frs, f);                                                                                             \
+    __syncthreads();
+
+template <typename T, int L, int MODE>
+__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_ystart(PassArgs a, Cols g, AxisFreq f, int ntiles,
+                                                                  const cx_t<T>* __restrict__ tw)
 {
     if (stopped(a.lay.stop)) return;
     using V = cx_t<T>;
-    constexpr int M = N1 / 2, G = M / R, LPB = kBlock / G, LP = M;
-    static_assert(G <= 64, "an x line must live inside one wavefront");
-    __shared__ V lds[LPB * LP];
-    __shared__ V twsm[M + N1];
-    stage_twiddles<M>(twsm, tw);
-    stage_twiddles<N1>(twsm + M, tw);
-    __syncthreads();
-    const V* twM = twsm;
-    const V* twN = twsm + M;
-    const int tid = threadIdx.x, ll = tid / G, t = tid % G;
-    const long line = (long)blockIdx.x * LPB + ll;
-    const bool valid = line < a.nlines;
-    const bool ld_ok = NM_TAIL_LOADS(T) || valid;
-    const long lineA = NM_TAIL_LOADS(T) && !valid ? 0 : line;
-    const long off = lineA * M;
-    const long soff = a.lay.line(lineA);
-    V* spec = (V*)a.spec;
+    constexpr int R = ColShape<T, L>::R, NT = NM_NT(YS, T);
+    NM_COL_LDS_FREQ(L)
+    const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
+    const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
+    const long fo = (long)fld * a.lay.bf + j * a.lay.ns;
+    V* const dst = (V*)a.S + (long)fld * a.lay.bs + j * a.lay.cs;
+    const bool zero_comp = a.lay.dim == 2 && j == 2;
     V v[R];
+    if constexpr (MODE == YS_APPLY) {
+        c.template ld<NT>((const V*)a.u + fo, v);
+    } else if constexpr (MODE == YS_EXPLICIT) {
+        const T dt = (T)a.dt, h2 = (T)(0.5 * a.dt * a.dt);
+        V vo[R], ao[R];
+        c.template ld<NT>((const V*)a.u + fo, v);
+        c.template ld<NT>((const V*)a.v + fo, vo);
+        c.template ld<NT>((const V*)a.a + fo, ao);
 #pragma unroll
-    for (int m = 0; m < R; m++) v[m] = ld_ok ? ld_nt<NM_NT(XPUP, T)>(spec + soff + t + m * G) : V{0, 0};
-    // the real-space operands are fetched before the transforms
-    const double* sc = a.scal + ((a.lines_per_batch && valid) ? line / a.lines_per_batch : 0) * S_COUNT;
-    const bool first = sc[S_FIRST] != 0.0;
-    const T beta = (T)sc[S_BETA];
-    const T alpha = (T)sc[S_ALPHA];
-    V* p = (V*)a.p + off;
-    V* x = (V*)a.x + off;
-    V po[R], xo[R];
-    uint16_t mk[R];
-    const long vline = lineA % a.lines_per_comp;
-#pragma unroll
-    for (int m = 0; m < R; m++) {
-        const int n = t + m * G;
-        po[m] = (ld_ok && !first) ? ld_nt<NM_NT(XPUP, T)>(p + n) : V{0, 0};
-        xo[m] = (ld_ok && !first) ? ld_nt<NM_NT(XPUP, T)>(x + n) : V{0, 0};
-        mk[m] = (ld_ok && a.mask) ? ((const uint16_t*)a.mask)[vline * M + n] : (uint16_t)0;
-    }
-    LineAddr<R, (int)sizeof(V)> addr{ll * LP};
-#pragma unroll
-    for (int m = 0; m < R; m++) lds[addr(t + m * G)] = v[m];
-    group_sync<true>();
-#pragma unroll
-    for (int m = 0; m < R; m++) {
-        const int k = t + m * G;
-        V xm = lds[addr((M - k) & (M - 1))];
-        v[m] = c2r_pre(k, v[m], xm, twN[k]);
-    }
-    group_sync<true>();
-    group_fft<M, R, +1, true>(v, t, lds, addr, twM);
-    const bool zero_comp = (a.dim == 2) && ((line / a.lines_per_comp) % 3 == 2);
-#pragma unroll
-    for (int m = 0; m < R; m++) {
-        V z = v[m];
-        if (mk[m] & 0x00ffu) z.x = 0;
-        if (mk[m] & 0xff00u) z.y = 0;
-        if (zero_comp) z = V{0, 0};
+        for (int m = 0; m < R; m++)
+            v[m] = V{v[m].x + dt * vo[m].x + h2 * ao[m].x, v[m].y + dt * vo[m].y + h2 * ao[m].y};
+        c.template st<NT>((V*)a.u + fo, v);
+    } else {
+        const double* sc = a.scal + (long)fld * S_COUNT;
+        const bool first = sc[S_FIRST] != 0.0;
+        const T beta = (T)sc[S_BETA], alpha = (T)sc[S_ALPHA];
+        c.template ld<NT>((const V*)a.S2 + (long)fld * a.lay.bs + j * a.lay.cs, v);
+        V po[R];
         if (!first) {
-            xo[m] = V{xo[m].x + alpha * po[m].x, xo[m].y + alpha * po[m].y};
-            z = V{z.x + beta * po[m].x, z.y + beta * po[m].y};
+            // the deferred x += alpha p_old goes first, so that its operand is not held over the transform
+            V xo[R];
+            c.template ld<NT>((const V*)a.p + fo, po);
+            c.template ld<NT>((const V*)a.x + fo, xo);
+#pragma unroll
+            for (int m = 0; m < R; m++) xo[m] = V{xo[m].x + alpha * po[m].x, xo[m].y + alpha * po[m].y};
+            c.template st<NT>((V*)a.x + fo, xo);
+        } else {
+#pragma unroll
+            for (int m = 0; m < R; m++) po[m] = V{0, 0};
         }
-        v[m] = z;
-    }
-    if (valid) {
+        c.template fft<+1>(v, lds, tws);
+        if (a.mask) c.masked(a.mask, v);
+        if (!first) {
 #pragma unroll
-        for (int m = 0; m < R; m++) {
-            const int n = t + m * G;
-            st_nt<NM_NT(XPUP, T)>(p + n, v[m]);
-            if (!first) st_nt<NM_NT(XPUP, T)>(x + n, xo[m]);
+            for (int m = 0; m < R; m++) v[m] = V{v[m].x + beta * po[m].x, v[m].y + beta * po[m].y};
         }
+        if (zero_comp) {
+#pragma unroll
+            for (int m = 0; m < R; m++) v[m] = V{0, 0};
+        }
+        c.template st<NT>((V*)a.p + fo, v);
     }
-    group_fft<M, R, -1, true>(v, t, lds, addr, twM);
+    c.deriv(v, lds, tws, frs);
+    c.template st<NT>(dst, v);
+}
+
+template <typename T, int L>
+__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_zstrain(PassArgs a, Cols g, AxisFreq f, int ntiles,
+                                                                   const cx_t<T>* __restrict__ tw)
+{
+    if (stopped(a.lay.stop)) return;
+    using V = cx_t<T>;
+    constexpr int R = ColShape<T, L>::R, NT = NM_NT(ZS, T);
+    NM_COL_LDS_FREQ(L)
+    const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
+    const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
+    V* const S = (V*)a.S + (long)fld * a.lay.bs;
+    V* const dst = S + (j == 0 ? 3 : j == 1 ? 2 : 4) * a.lay.cs;
+    V v[R], w[R];
+    c.template ld<NT>((const V*)a.p + (long)fld * a.lay.bf + j * a.lay.ns, v);
+    if (j == 1) c.template ld<NT>(dst, w); // D_y p_3
+    c.deriv(v, lds, tws, frs);
+    if (j == 1) {
+        // g23 = D_z p_2 + D_y p_3
 #pragma unroll
-    for (int m = 0; m < R; m++) lds[addr(t + m * G)] = v[m];
-    group_sync<true>();
-    V mir[R];
+        for (int m = 0; m < R; m++) v[m] = cadd(v[m], w[m]);
+    }
+    c.template st<NT>(dst, v);
+}
+
+template <typename T, int L>
+__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_zdiv(PassArgs a, Cols g, AxisFreq f, int ntiles,
+                                                                const cx_t<T>* __restrict__ tw)
+{
+    if (stopped(a.lay.stop)) return;
+    using V = cx_t<T>;
+    constexpr int R = ColShape<T, L>::R, NT = NM_NT(ZD, T);
+    const int fld = blockIdx.z;
+    int blk = blockIdx.x;
+    if (a.carry.action != RED_NONE) {
+        if (blk == 0) {
+            carry_reduce(a.carry, fld);
+            return;
+        }
+        blk--;
+    }
+    NM_COL_LDS_FREQ(L)
+    const int j = col_comp<T>(blk, ntiles);
+    const ColTile<T, L> c(g, col_tile<T>(blk, ntiles));
+    // sigma_31, sigma_32, sigma_33
+    const V* src = (const V*)a.S + (long)fld * a.lay.bs + (j == 0 ? 3 : j == 1 ? 2 : 4) * a.lay.cs;
+    V* const Q = (V*)a.S2 + (long)fld * a.lay.bs + (3 + j) * a.lay.cs;
+    V v[R], w[R];
+    c.template ld<NT>(src, v);
+    c.template ld<NT>(Q, w);
+    c.deriv(v, lds, tws, frs);
+    const T cd = (T)-a.bdt2;
 #pragma unroll
-    for (int m = 0; m < R; m++) mir[m] = lds[addr((M - (t + m * G)) & (M - 1))];
-    if (valid) {
+    for (int m = 0; m < R; m++) v[m] = V{w[m].x + cd * v[m].x, w[m].y + cd * v[m].y};
+    c.template st<NT>(Q, v);
+}
+
+template <typename T, int L, int MODE>
+__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_yend(PassArgs a, Cols g, AxisFreq f, int ntiles,
+                                                                const cx_t<T>* __restrict__ tw)
+{
+    if (stopped(a.lay.stop)) return;
+    using V = cx_t<T>;
+    constexpr int R = ColShape<T, L>::R, NT = NM_NT(YE, T);
+    NM_COL_LDS_FREQ(L)
+    const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
+    const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
+    const long fo = (long)fld * a.lay.bf + j * a.lay.ns;
+    // sigma_21, sigma_22, sigma_23
+    const V* src = (const V*)a.S + (long)fld * a.lay.bs + j * a.lay.cs;
+    const V* Q = (const V*)a.S2 + (long)fld * a.lay.bs + (3 + j) * a.lay.cs;
+    const bool zero_comp = a.lay.dim == 2 && j == 2;
+    V v[R], w[R];
+    c.template ld<NT>(src, v);
+    c.template ld<NT>(Q, w);
+    c.deriv(v, lds, tws, frs);
+    const T cd = (T)-a.bdt2;
 #pragma unroll
-        for (int m = 0; m < R; m++) {
-            const int k = t + m * G;
-            st_nt<NM_NT(XPUP, T)>(spec + soff + k, r2c_post(k, v[m], mir[m], twN[k]));
+    for (int m = 0; m < R; m++) {
+        v[m] = V{w[m].x + cd * v[m].x, w[m].y + cd * v[m].y};
+        if (zero_comp) v[m] = V{0, 0};
+    }
+    if constexpr (MODE == YE_EXPLICIT) {
+        // o = dt/2 div sigma: v <- v + dt/2 a + o / rho, a <- (2/dt) o / rho
+        const T* rho = (const T*)a.rho;
+        const T hdt = (T)(0.5 * a.dt), idt2 = (T)(2.0 / a.dt);
+        // (fetched here and a few points at a time: held over the transforms they would spill)
+        constexpr int H = R < 4 ? R : 4;
+#pragma unroll
+        for (int q = 0; q < R; q += H) {
+            V vo[H], ao[H];
+            uint32_t ph[H];
+#pragma unroll
+            for (int m = 0; m < H; m++) {
+                vo[m] = ld_nt<NT>(c.at((const V*)a.v + fo, q + m));
+                ao[m] = ld_nt<NT>(c.at((const V*)a.a + fo, q + m));
+                ph[m] = ((const uint32_t*)a.phase)[c.elem(q + m)];
+            }
+#pragma unroll
+            for (int m = 0; m < H; m++) {
+                const V o = V{v[q + m].x / rho[ph[m] & 0xffffu], v[q + m].y / rho[ph[m] >> 16]};
+                vo[m] = V{vo[m].x + hdt * ao[m].x + o.x, vo[m].y + hdt * ao[m].y + o.y};
+                ao[m] = V{idt2 * o.x, idt2 * o.y};
+                if (zero_comp) vo[m] = ao[m] = V{0, 0};
+            }
+            if (c.valid) {
+#pragma unroll
+                for (int m = 0; m < H; m++) {
+                    st_nt<NT>(c.at((V*)a.v + fo, q + m), vo[m]);
+                    st_nt<NT>(c.at((V*)a.a + fo, q + m), ao[m]);
+                }
+            }
+        }
+    } else {
+        if (a.mask) c.masked(a.mask, v);
+        if constexpr (MODE == YE_OUT) {
+            c.template st<NT>((V*)a.out + fo, v);
+        } else {
+            // the residual's y spectrum R -= alpha y-forward(q); r.r by Parseval
+            V* const rp = (V*)a.r + fo;
+            const T alpha = (T)a.scal[(long)fld * S_COUNT + S_ALPHA];
+            c.template ld<NT>(rp, w);
+            c.template fft<-1>(v, lds, tws);
+            double part = 0.0;
+#pragma unroll
+            for (int m = 0; m < R; m++) {
+                w[m] = V{w[m].x - alpha * v[m].x, w[m].y - alpha * v[m].y};
+                part += (double)w[m].x * (double)w[m].x + (double)w[m].y * (double)w[m].y;
+            }
+            c.template st<NT>(rp, w);
+            const double s = block_sum(c.valid ? part : 0.0);
+            if (threadIdx.x == 0) a.partials[(long)fld * gridDim.x + blockIdx.x] = s * f.inv_n;
         }
     }
 }
 
+template <typename T, int L, int DIR>
+__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_colfft(ColFft a, Cols g, int ntiles,
+                                                                  const cx_t<T>* __restrict__ tw)
+{
+    if (stopped(a.lay.stop)) return;
+    using V = cx_t<T>;
+    constexpr int R = ColShape<T, L>::R, NT = NM_NT(CF, T);
+    const int fld = blockIdx.z;
+    int blk = blockIdx.x;
+    if (a.carry.action != RED_NONE) {
+        if (blk == 0) {
+            carry_reduce(a.carry, fld);
+            return;
+        }
+        blk--;
+    }
+    NM_COL_LDS(L)
+    __syncthreads();
+    const int j = col_comp<T>(blk, ntiles);
+    const ColTile<T, L> c(g, col_tile<T>(blk, ntiles));
+    V v[R];
+    c.template ld<NT>((const V*)a.src + (long)fld * a.sb + j * a.sc, v);
+    c.template fft<DIR>(v, lds, tws);
+    if constexpr (DIR > 0) {
+        if (a.mask) c.masked(a.mask, v);
+        if (a.zero3 && j == 2) {
+#pragma unroll
+            for (int m = 0; m < R; m++) v[m] = V{0, 0};
+        }
+    }
+    c.template st<NT>((V*)a.dst + (long)fld * a.db + j * a.dc, v);
+}
+
+// ---------------------------------------------------------------------------
+// x direction
+// ---------------------------------------------------------------------------
 // sigma_v = C_v eps_v for one voxel (Voigt, engineering shear; 21 = upper triangle).
 template <typename T> __device__ __forceinline__ void voigt_stress(const T* __restrict__ c, const T e[6], T s[6])
 {
@@ -519,308 +523,310 @@ template <typename T> __device__ __forceinline__ void voigt_stress(const T* __re
     s[5] = c[5] * e[0] + c[10] * e[1] + c[14] * e[2] + c[17] * e[3] + c[19] * e[4] + c[20] * e[5];
 }
 
-template <typename T, int N1, int R>
-__global__ __launch_bounds__(kBlock) void k_xstress(cx_t<T>* spec, SpecLayout lay, const uint16_t* __restrict__ phase,
-                                                    const T* __restrict__ C21, const cx_t<T>* __restrict__ tw)
+// Streaming access of one real.
+template <int NT, typename T> __device__ __forceinline__ T ld_s(const T* p)
 {
-    if (stopped(lay.stop)) return;
+    if constexpr ((NT & 1) != 0) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <int NT, typename T> __device__ __forceinline__ void st_s(T* p, T v)
+{
+    if constexpr ((NT & 2) != 0) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
+constexpr int kXR = 4; // elements per thread of a pair of x lines in the stress pass
+
+// The stress pass: 16 fields and the grain ids, 256^3: 0.217 ms in FP32 (5.1 TB/s), 0.458 in FP64
+// (4.8); the x pass it replaces moved 12 fields in 0.20 and 0.36 ms.  HBM bounds it in FP32, and in FP64
+// the registers too (two wavefronts per SIMD).  A group of N1 / 4 lanes holds the rows (y, y + 1) of one z plane as a complex
+// line of N1 points, in all three components at once (one synchronisation per stage for the three).
+template <typename T, int N1>
+__global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? kXStressWaves64 : kXStressWaves32) void k_xstress(PassArgs a, AxisFreq f, int npairs, const cx_t<T>* __restrict__ tw)
+{
+    if (stopped(a.lay.stop)) return;
     using V = cx_t<T>;
-    constexpr int M = N1 / 2, G = M / R, LPB = kBlock / G, LP = M;
-    static_assert(G <= 64, "an x line must live inside one wavefront");
-    __shared__ V lds[LPB * LP];
-    __shared__ V twsm[M + N1];
-    stage_twiddles<M>(twsm, tw);
-    stage_twiddles<N1>(twsm + M, tw);
+    constexpr int R = kXR, G = N1 / R, LPB = kBlock / G, NT = NM_NT(XS, T);
+    constexpr int EARLY = sizeof(T) == 8 ? 0 : 3; // strains fetched ahead of the first transform
+    constexpr bool WAVE = G <= 64;
+    constexpr int LP = line_elems(N1), AREA = LPB * LP;
+    __shared__ V lds[3 * AREA];
+    __shared__ V tws[N1];
+    __shared__ T frs[N1];
+    stage_twiddles<N1>(tws, tw);
+    stage_freq<N1>(frs, f);
     __syncthreads();
-    const V* twM = twsm;
-    const V* twN = twsm + M;
-    const int tid = threadIdx.x, ll = tid / G, t = tid % G;
-    const long line = (long)blockIdx.x * LPB + ll;
-    const long lpf = (long)lay.n2 * lay.n3; // x lines per component of one field
-    const bool valid = line < lpf * lay.nb;
-    LineAddr<R, (int)sizeof(V)> addr{ll * LP};
-    // the twelve transforms share their twiddles: with TWR they are read once into registers
-    constexpr bool TWR = sizeof(T) == 8 ? (N1 == 512 ? NM_STRESS512_TWREG64 : NM_STRESS_TWREG64) : NM_STRESS_TWREG32;
-    TwRegs<M, R, V> twr;
-    V twn[R];
-    if constexpr (TWR) {
-        twr.load(t, twM);
-#pragma unroll
-        for (int m = 0; m < R; m++) twn[m] = twN[t + m * G];
-    }
-    auto fft_inv = [&](V (&x)[R]) {
-        if constexpr (TWR) group_fft_tw<M, R, +1, true>(x, t, lds, addr, twr);
-        else group_fft<M, R, +1, true>(x, t, lds, addr, twM);
+    const int ll = threadIdx.x / G, t = threadIdx.x % G, fld = blockIdx.z;
+    const int pr = blockIdx.x * LPB + ll;
+    const bool valid = pr < npairs;
+    // the two rows are neighbours in memory: reals [2 N1 pr, 2 N1 (pr + 1))
+    const uint32_t base = (uint32_t)(valid ? pr : 0) * (2u * N1) + t, bb = base * (uint32_t)sizeof(T);
+    const LineAddr<AREA> addr{ll * LP};
+    const T* const p = (const T*)((const V*)a.p + (long)fld * a.lay.bf);
+    T* const S = (T*)((V*)a.S + (long)fld * a.lay.bs);
+    T* const Q = (T*)((V*)a.S2 + (long)fld * a.lay.bs + 3 * a.lay.cs);
+    const long ps = 2 * a.lay.ns, cs = 2 * a.lay.cs;
+    const bool has_z = a.lay.n3 > 1;
+    // the lane's byte offset, hidden from the optimizer at each use: otherwise it keeps one 64-bit
+    // address per buffer in registers instead of scalar bases
+    auto lane_off = [&]() {
+        uint32_t o = bb;
+        asm("" : "+v"(o));
+        return o;
     };
-    auto fft_fwd = [&](V (&x)[R]) {
-        if constexpr (TWR) group_fft_tw<M, R, -1, true>(x, t, lds, addr, twr);
-        else group_fft<M, R, -1, true>(x, t, lds, addr, twM);
-    };
-    auto twk = [&](int m, int k) -> V {
-        if constexpr (TWR) return twn[m];
-        else return twN[k];
-    };
-    const bool ld_ok = NM_TAIL_LOADS(T) || valid;
-    const long lineA = NM_TAIL_LOADS(T) && !valid ? 0 : line;
-    const long off = lay.line(lineA), NS = lay.cs;
-    // keep the global loads of the next PF strain components in flight while a
-    // component is transformed: the fences of the LDS exchanges would otherwise hold
-    // each component's loads back until the previous transform is done
-    constexpr int PFQ = sizeof(T) == 8 ? (N1 == 512 ? NM_STRESS512_PF64 : NM_STRESS_PF64) : NM_STRESS_PF32;
-    constexpr int PF = PFQ < 6 ? PFQ : 6;
-    V raw[6][R];
-#pragma unroll
-    for (int c = 0; c < PF; c++)
-#pragma unroll
-        for (int m = 0; m < R; m++) raw[c][m] = ld_ok ? ld_nt<NM_NT(STRESS, T)>(spec + c * NS + off + t + m * G) : V{0, 0};
-    uint32_t phw[R];
-    {
-        const uint32_t* ph2 = (const uint32_t*)phase + (valid ? line % lpf : 0) * M;
-#pragma unroll
-        for (int m = 0; m < R; m++) phw[m] = ph2[t + m * G];
-    }
-    T e[6][2 * R];
-#pragma unroll
-    for (int c = 0; c < 6; c++) {
-        V v[R];
-#pragma unroll
-        for (int m = 0; m < R; m++) v[m] = raw[c][m];
-        if (c + PF < 6) {
-#pragma unroll
-            for (int m = 0; m < R; m++) raw[c + PF][m] = ld_ok ? ld_nt<NM_NT(STRESS, T)>(spec + (c + PF) * NS + off + t + m * G) : V{0, 0};
-        }
-#pragma unroll
-        for (int m = 0; m < R; m++) lds[addr(t + m * G)] = v[m];
-        group_sync<true>();
+    auto ld = [&](const T* q, V (&v)[R]) {
+        const uint32_t o = lane_off();
 #pragma unroll
         for (int m = 0; m < R; m++) {
-            const int k = t + m * G;
-            v[m] = c2r_pre(k, v[m], lds[addr((M - k) & (M - 1))], twk(m, k));
+            v[m].x = ld_s<NT>((const T*)((const char*)q + o) + m * G);
+            v[m].y = ld_s<NT>((const T*)((const char*)q + o) + (m * G + N1));
         }
-        group_sync<true>();
-        fft_inv(v);
+    };
+    auto st = [&](T* q, const V (&v)[R]) {
+        const uint32_t o = lane_off();
 #pragma unroll
         for (int m = 0; m < R; m++) {
-            e[c][2 * m] = v[m].x;
-            e[c][2 * m + 1] = v[m].y;
+            st_s<NT>((T*)((char*)q + o) + m * G, v[m].x);
+            st_s<NT>((T*)((char*)q + o) + (m * G + N1), v[m].y);
         }
-    }
-    if (valid) {
+    };
+    V d[3][R], w[5][R]; // displacement and its x derivative; D_y p1, D_y p2, g23, D_z p1, D_z p3
 #pragma unroll
-        for (int m = 0; m < R; m++) {
-            const uint32_t ph = phw[m];
+    for (int j = 0; j < 3; j++) ld(p + j * ps, d[j]);
 #pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const T* cg = C21 + 21 * (h ? (ph >> 16) : (ph & 0xffffu));
-                T ee[6], ss[6];
+    for (int c = 0; c < EARLY; c++) ld(S + c * cs, w[c]);
+    uint32_t ph[R];
 #pragma unroll
-                for (int q = 0; q < 6; q++) ee[q] = e[q][2 * m + h];
-                voigt_stress(cg, ee, ss);
-#pragma unroll
-                for (int q = 0; q < 6; q++) e[q][2 * m + h] = ss[q];
-            }
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 6; c++) {
-        V v[R];
-#pragma unroll
-        for (int m = 0; m < R; m++) v[m] = V{e[c][2 * m], e[c][2 * m + 1]};
-        fft_fwd(v);
-#pragma unroll
-        for (int m = 0; m < R; m++) lds[addr(t + m * G)] = v[m];
-        group_sync<true>();
-        V mir[R];
-#pragma unroll
-        for (int m = 0; m < R; m++) mir[m] = lds[addr((M - (t + m * G)) & (M - 1))];
-        group_sync<true>();
-        if (valid) {
-#pragma unroll
-            for (int m = 0; m < R; m++) {
-                const int k = t + m * G;
-                st_nt<NM_NT(STRESS, T)>(spec + c * NS + off + k, r2c_post(k, v[m], mir[m], twk(m, k)));
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// y and z directions: tiles of TX consecutive kx columns, L points each.
-// ---------------------------------------------------------------------------
-// Column tiles: element p of column c at p * TX + c.  With TX >= 8 complex
-// (16-byte elements) each group of 8 consecutive lanes covers all banks, so no
-// padding is needed; a compile-time TX (TXC > 0) lets the offsets fold into
-// the LDS instructions' immediate fields.  TXC == 0: runtime TX (small grids).
-template <int TXC> struct ColAddrT {
-    int c, tx;
-    __device__ __forceinline__ int operator()(int p) const { return p * (TXC > 0 ? TXC : tx) + c; }
-};
-
-template <typename T, int L, int R, int DIR, int BLK, int TXC>
-__global__ __launch_bounds__(BLK) void k_ypass(cx_t<T>* __restrict__ data, long colstride, long planestride, long cs,
-                                               int TXr, const cx_t<T>* __restrict__ tw, const double* stop, long bs)
-{
-    if (stopped(stop)) return;
-    using V = cx_t<T>;
-    constexpr int G = L / R;
-    const int TX = TXC > 0 ? TXC : TXr;
-    __shared__ V lds[BLK * R]; // TX * L <= BLK R
-    __shared__ V twsm[L];
-    stage_twiddles<L>(twsm, tw);
-    __syncthreads();
-    const int tid = threadIdx.x, c = tid % TX, t = tid / TX;
-    // component blockIdx.z (of three per field when several fields lie bs apart)
-    const long zc = bs ? (long)(blockIdx.z / 3) * bs + (long)(blockIdx.z % 3) * cs : (long)blockIdx.z * cs;
-    V* col = data + zc + blockIdx.y * planestride + (long)blockIdx.x * TX + c;
-    V v[R];
-#pragma unroll
-    for (int m = 0; m < R; m++) v[m] = ld_nt<NM_NT(YPASS, T)>(col + (long)(t + m * G) * colstride);
-    ColAddrT<TXC> addr{c, TX};
-    group_fft<L, R, DIR>(v, t, lds, addr, twsm);
-#pragma unroll
-    for (int m = 0; m < R; m++) st_nt<NM_NT(YPASS, T)>(col + (long)(t + m * G) * colstride, v[m]);
-}
-
-// Frequency of x bin kx (0 <= kx < n1/2; slot 0 also carries the Nyquist bin, zero under every
-// rule), of y bin ky and of z bin kz, in the same units as k1 kx.
-__device__ __forceinline__ double freq_x(const SpecParams& sp, int kx)
-{
-    return sp.mfreq ? sp.mfreq[kx] : sp.k1 * kx;
-}
-__device__ __forceinline__ double freq_y(const SpecParams& sp, int ky)
-{
-    return sp.mfreq ? sp.mfreq[sp.n1 + ky] : sp.k2 * freq_index(ky, sp.n2);
-}
-__device__ __forceinline__ double freq_z(const SpecParams& sp, int kz)
-{
-    return sp.mfreq ? sp.mfreq[sp.n1 + sp.n2 + kz] : sp.k3 * freq_index(kz, sp.n3);
-}
-
-// Pointwise operators at frequency (xi1, xi2, xi3).
-template <typename T> struct ZOps {
-    using V = cx_t<T>;
-    // i s (a): multiply by i and a real scale
-    static __device__ __forceinline__ V iscale(V a, T s) { return V{-a.y * s, a.x * s}; }
-};
-
-// Preconditioner z pass: forward z transforms of the three components, the pointwise
-// inverse of beta dt^2 K(xi) + rhobar I (K_ij = Cbar_ikjm xi_k xi_m, eqs. (precond),
-// (acous)) scaled by 1 / (n1 n2 n3), inverse z transforms.  Columns of TX kx bins
-// at one ky; data in place.
-template <typename T, int L, int R, int BLK, int TXC>
-__global__ __launch_bounds__(BLK) void k_zprecond(cx_t<T>* __restrict__ data, long NS, long colstride, int TXr,
-                                                  SpecParams sp, const cx_t<T>* __restrict__ tw,
-                                                  double* __restrict__ partials)
-{
-    if (stopped(sp.stop)) return;
-    using V = cx_t<T>;
-    constexpr int G = L / R;
-    const int TX = TXC > 0 ? TXC : TXr;
-    __shared__ V lds[BLK * R]; // TX * L <= BLK R
-    __shared__ V twsm[L > 1 ? L : 2];
-    const int tid = threadIdx.x, c = tid % TX, t = tid / TX;
-    const int M = sp.n1 / 2;
-    const int kx = blockIdx.x * TX + c, ky = blockIdx.y;
-    // uniform column-tile base (scalar registers) plus 32-bit per-lane byte offsets
-    V* const cb = data + (long)blockIdx.z * sp.bs + (long)ky * M + (long)blockIdx.x * TX;
-    const uint32_t lane = (uint32_t)(c * sizeof(V)) + (uint32_t)t * (uint32_t)(colstride * sizeof(V));
-    const uint32_t mstep = (uint32_t)(G * colstride * sizeof(V));
-    auto at = [&](int j, int m) -> V& { return *(V*)((char*)(cb + j * NS) + (lane + (uint32_t)m * mstep)); };
-    // all three components' loads go out before the first transform (the barriers of
-    // the LDS exchanges would otherwise hold each load back behind the previous transform)
-    auto load3 = [&](V (&v)[3][R]) {
+    for (int m = 0; m < R; m++)
+        ph[m] = (uint32_t)a.phase[base + m * G] | ((uint32_t)a.phase[base + m * G + N1] << 16);
+    auto deriv3 = [&](V (&v)[3][R], auto between) {
+        group_fft<N1, R, -1, WAVE, FFT_PLAIN, 3>(v, t, lds, addr, tws);
+        between();
 #pragma unroll
         for (int j = 0; j < 3; j++)
 #pragma unroll
-            for (int m = 0; m < R; m++) v[j][m] = ld_nt<NM_NT(ZPRE, T)>(&at(j, m));
+            for (int m = 0; m < R; m++) v[j][m] = iscale(v[j][m], frs[t + m * G]);
+        group_fft<N1, R, +1, WAVE, FFT_PLAIN, 3>(v, t, lds, addr, tws);
     };
-    V u[3][R];
-    if constexpr (TXC > 0 && L >= 2 && sizeof(T) == 4) {
-        // full FP32 blocks: the twiddle loads go out first and the operands right behind
-        // them, so that only the twiddles are waited for before the barrier that publishes
-        // them (FP64, at one wave per SIMD, measured faster with the operands loaded after
-        // that barrier)
-        constexpr int NT = (L + BLK - 1) / BLK;
-        V twv[NT];
+    // the remaining strains are fetched between the two transforms: all of them ahead of the first
+    // would take more registers than the occupancy leaves
+    deriv3(d, [&]() {
 #pragma unroll
-        for (int q = 0; q < NT; q++)
-            if (tid + q * BLK < L) twv[q] = tw[tw_offset(L) + tid + q * BLK];
-        load3(u);
+        for (int c = EARLY; c < 5; c++) {
+            if (c < 3 || has_z) {
+                ld(S + c * cs, w[c]);
+            } else {
 #pragma unroll
-        for (int q = 0; q < NT; q++)
-            if (tid + q * BLK < L) twsm[tid + q * BLK] = twv[q];
-        __syncthreads();
-    } else {
-        stage_twiddles<L>(twsm, tw);
-        __syncthreads();
-        load3(u);
-    }
-    ColAddrT<TXC> addr{c, TX};
-    const V* twL = twsm;
-    const T xi1 = (T)freq_x(sp, kx);
-    const T bdt2 = (T)sp.bdt2, rb = (T)sp.rhobar, s = (T)sp.inv_ntot;
-    // beta dt^2 K(xi) + rhobar I with K = N(xi)^T Cbar N(xi), N the Voigt strain of a plane
-    // wave.  At fixed (xi1, xi2) it is quadratic in xi3: N = N12 + xi3 E3 (N12 holds the
-    // xi1, xi2 entries, E3 the unit entries that xi3 multiplies), so
-    //   beta dt^2 K + rhobar I = A0 + xi3 (A1 + xi3 A2)
-    // with A0 = beta dt^2 N12^T C N12 + rhobar I, A1 = beta dt^2 (N12^T C E3 + E3^T C N12),
-    // A2 = beta dt^2 E3^T C E3, formed once per thread (symmetric; upper triangles kept).
-    auto form = [&](T x1, T x2, T (&A0)[6], T (&A1)[6], T (&A2)[6]) {
-        T C[6][6];
-        int o = 0;
-#pragma unroll
-        for (int a = 0; a < 6; a++)
-#pragma unroll
-            for (int b = a; b < 6; b++) {
-                C[a][b] = (T)sp.Cbar[o];
-                C[b][a] = (T)sp.Cbar[o];
-                o++;
+                for (int m = 0; m < R; m++) w[c][m] = V{0, 0};
             }
-        T CN[6][3], CE[6][3];
-#pragma unroll
-        for (int a = 0; a < 6; a++) {
-            CN[a][0] = C[a][0] * x1 + C[a][5] * x2;
-            CN[a][1] = C[a][1] * x2 + C[a][5] * x1;
-            CN[a][2] = C[a][3] * x2 + C[a][4] * x1;
-            CE[a][0] = C[a][4];
-            CE[a][1] = C[a][3];
-            CE[a][2] = C[a][2];
         }
-        // rows of N12^T X and E3^T X for a 6 x 3 X
-        auto n12 = [&](const T (&X)[6][3], int i, int j) -> T {
-            return i == 0 ? x1 * X[0][j] + x2 * X[5][j] : i == 1 ? x2 * X[1][j] + x1 * X[5][j] : x2 * X[3][j] + x1 * X[4][j];
-        };
-        auto e3 = [&](const T (&X)[6][3], int i, int j) -> T { return i == 0 ? X[4][j] : i == 1 ? X[3][j] : X[2][j]; };
-        int q = 0;
-#pragma unroll
-        for (int i = 0; i < 3; i++)
-#pragma unroll
-            for (int j = i; j < 3; j++) {
-                A0[q] = bdt2 * n12(CN, i, j) + (i == j ? rb : (T)0);
-                A1[q] = bdt2 * (n12(CE, i, j) + e3(CN, i, j));
-                A2[q] = bdt2 * e3(CE, i, j);
-                q++;
-            }
-    };
-#pragma unroll
-    for (int j = 0; j < 3; j++) group_fft<L, R, -1>(u[j], t, lds, addr, twL);
-    T A0[6], A1[6], A2[6]; // order 00 01 02 11 12 22
-    form(xi1, (T)freq_y(sp, ky), A0, A1, A2);
-    // per-thread part of r . z in the working precision (24 products at most), summed in
-    // FP64 across threads
-    T part = 0;
+    });
+    double part = 0.0;
+    const T b2 = (T)a.bdt2;
 #pragma unroll
     for (int m = 0; m < R; m++) {
-        const T x3 = (T)freq_z(sp, t + m * G);
-        T K[6];
 #pragma unroll
-        for (int q = 0; q < 6; q++) K[q] = A0[q] + x3 * (A1[q] + x3 * A2[q]);
-        const T k00 = K[0], k01 = K[1], k02 = K[2], k11 = K[3], k12 = K[4], k22 = K[5];
+        for (int h = 0; h < 2; h++) {
+            auto at = [h](const V& q) { return h ? q.y : q.x; };
+            auto put = [h](V& q, T x) { (h ? q.y : q.x) = x; };
+            const T* cg = (const T*)a.C21 + 21 * (h ? (ph[m] >> 16) : (ph[m] & 0xffffu));
+            // Voigt order 11 22 33 23 13 12
+            T e[6] = {at(d[0][m]), at(w[1][m]), at(w[4][m]), at(w[2][m]), at(w[3][m]) + at(d[2][m]),
+                      at(w[0][m]) + at(d[1][m])};
+            T s[6];
+            voigt_stress(cg, e, s);
+            part += (double)(b2 * (e[0] * s[0] + e[1] * s[1] + e[2] * s[2] + e[3] * s[3] + e[4] * s[4] + e[5] * s[5]));
+            put(d[0][m], s[0]);
+            put(d[1][m], s[5]);
+            put(d[2][m], s[4]);
+            put(w[0][m], s[5]);
+            put(w[1][m], s[1]);
+            put(w[2][m], s[3]);
+            put(w[3][m], s[4]);
+            put(w[4][m], s[2]);
+        }
+        // the sum is due here: sunk to its only use, it would keep every strain and stress in registers
+        asm volatile("" : "+v"(part));
+        __builtin_amdgcn_sched_barrier(0); // one element's stiffness at a time in registers
+    }
+#pragma unroll
+    for (int c = 0; c < 3; c++) st(S + c * cs, w[c]); // s12 s22 s23
+    if (has_z) {
+        st(S + 3 * cs, w[3]); // s13
+        st(S + 4 * cs, w[4]); // s33
+    }
+    // p again for the inertia term: its second read comes from the caches, and held over the
+    // transforms it would cost a wave of occupancy
+    V po[3][R];
+    deriv3(d, [&]() {
+#pragma unroll
+        for (int j = 0; j < 3; j++) ld(p + j * ps, po[j]);
+    });
+    T rh[R][2];
+#pragma unroll
+    for (int m = 0; m < R; m++) rh[m][0] = rh[m][1] = (T)0;
+    if (a.rho) {
+#pragma unroll
+        for (int m = 0; m < R; m++) {
+            rh[m][0] = ((const T*)a.rho)[ph[m] & 0xffffu];
+            rh[m][1] = ((const T*)a.rho)[ph[m] >> 16];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+#pragma unroll
+        for (int m = 0; m < R; m++) {
+            const V q = V{rh[m][0] * po[j][m].x, rh[m][1] * po[j][m].y};
+            part += (double)(q.x * po[j][m].x + q.y * po[j][m].y);
+            d[j][m] = V{q.x - b2 * d[j][m].x, q.y - b2 * d[j][m].y};
+        }
+        asm volatile("" : "+v"(part));
+        if (valid) st(Q + j * cs, d[j]);
+    }
+    if (a.partials) {
+        const double s = block_sum(valid ? part : 0.0);
+        if (threadIdx.x == 0) a.partials[(long)fld * gridDim.x + blockIdx.x] = s;
+    }
+}
+
+// The preconditioner's middle pass on the (y, z) spectrum C of the packed pairs.  The spectra of
+// the even and odd voxels of a row come apart with the mirrored row,
+//   r^(2x', k) = (C(x', k) + conj C(x', -k)) / 2,  r^(2x'+1, k) = (C(x', k) - conj C(x', -k)) / (2 i),
+// so a group takes the rows k = (ky, kz) and -k together: one complex line of N1 points whose
+// x transform, multiplier and inverse serve both rows (z^(-k) = conj z^(k) in real space).  Rows
+// that are their own mirror are done once.
+// The multiplier beta dt^2 K(xi) + rhobar I in working precision: K[q][v] xi xi sums entry q (00 01 02
+// 11 12 22) over the products v = 11 22 33 23 13 12 of the frequencies.
+template <typename T> struct PrecondParams {
+    T K[6][6];
+    T rhobar, inv_ntot;
+    double k1, k2, k3;
+    const double* mfreq;
+    int n1, n2, n3, dim;
+};
+
+template <typename T> static PrecondParams<T> precond_params(const SpecParams& sp)
+{
+    PrecondParams<T> p;
+    double C[6][6];
+    for (int a = 0, o = 0; a < 6; a++)
+        for (int b = a; b < 6; b++, o++) C[a][b] = C[b][a] = sp.Cbar[o];
+    static const int V[3][3] = {{0, 5, 4}, {5, 1, 3}, {4, 3, 2}}; // Voigt index of a pair
+    static const int P[6][2] = {{0, 0}, {1, 1}, {2, 2}, {1, 2}, {0, 2}, {0, 1}};
+    for (int i = 0, q = 0; i < 3; i++)
+        for (int j = i; j < 3; j++, q++)
+            for (int v = 0; v < 6; v++) {
+                // K_ij = Cbar_ikjm xi_k xi_m (eq. acous)
+                const int k = P[v][0], m = P[v][1];
+                const double c = C[V[i][k]][V[j][m]] + (k != m ? C[V[i][m]][V[j][k]] : 0.0);
+                p.K[q][v] = (T)(sp.bdt2 * c);
+            }
+    p.rhobar = (T)sp.rhobar;
+    p.inv_ntot = (T)sp.inv_ntot;
+    p.k1 = sp.k1;
+    p.k2 = sp.k2;
+    p.k3 = sp.k3;
+    p.mfreq = sp.mfreq;
+    p.n1 = sp.n1;
+    p.n2 = sp.n2;
+    p.n3 = sp.n3;
+    p.dim = sp.dim;
+    return p;
+}
+
+template <typename T, int N1> struct XPShape {
+    static constexpr int R = 8, G = N1 / R;
+    static constexpr int BLK = 256;
+};
+
+template <typename T, int N1>
+__global__ __launch_bounds__((XPShape<T, N1>::BLK), sizeof(T) == 8 ? kXPrecondWaves64 : kXPrecondWaves32) void k_xprecond(PrecondParams<T> sp, Layout lay, const cx_t<T>* __restrict__ src,
+                                                                    long sc, long sb, cx_t<T>* __restrict__ dst, int nlines,
+                                                                    int nfull, const cx_t<T>* __restrict__ tw,
+                                                                    double* __restrict__ partials)
+{
+    if (stopped(lay.stop)) return;
+    using V = cx_t<T>;
+    using Sh = XPShape<T, N1>;
+    constexpr int R = Sh::R, G = Sh::G, LPB = Sh::BLK / G, M = N1 / 2, NT = NM_NT(XP, T);
+    constexpr int LP = line_elems(N1), AREA = LPB * LP;
+    __shared__ V lds[AREA];
+    __shared__ V tws[N1];
+    stage_twiddles<N1>(tws, tw);
+    __syncthreads();
+    const int ll = threadIdx.x / G, t = threadIdx.x % G, fld = blockIdx.z;
+    const int ln = blockIdx.x * LPB + ll;
+    const bool valid = ln < nlines;
+    // kz in (0, n3/2): every ky; kz = 0 and n3/2: ky <= n2/2
+    int ky, kz;
+    if (ln < nfull) {
+        kz = 1 + ln / lay.n2;
+        ky = ln & (lay.n2 - 1);
+    } else {
+        const int i = valid ? ln - nfull : 0, half = lay.n2 / 2 + 1;
+        kz = i < half ? 0 : lay.n3 / 2;
+        ky = i < half ? i : i - half;
+    }
+    const int my = (lay.n2 - ky) & (lay.n2 - 1), mz = (lay.n3 - kz) & (lay.n3 - 1);
+    const bool self = my == ky && mz == kz;
+    const uint32_t o1 = ((uint32_t)kz * lay.n2 + ky) * M + t, o2 = ((uint32_t)mz * lay.n2 + my) * M + t;
+    const V* const in = src + (long)fld * sb;
+    V* const out = dst + (long)fld * lay.bs;
+    const LineAddr<AREA> addr{ll * LP};
+    V v[3][R];
+    {
+        V ca[3][R / 2], cb[3][R / 2];
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+#pragma unroll
+            for (int m = 0; m < R / 2; m++) {
+                ca[j][m] = ld_nt<NT>(in + j * sc + (o1 + m * G));
+                cb[j][m] = ld_nt<NT>(in + j * sc + (o2 + m * G));
+            }
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+#pragma unroll
+            for (int m = 0; m < R / 2; m++) {
+                const V x = ca[j][m], y = cb[j][m];
+                v[j][2 * m] = V{(T)0.5 * (x.x + y.x), (T)0.5 * (x.y - y.y)};
+                v[j][2 * m + 1] = V{(T)0.5 * (x.y + y.y), (T)-0.5 * (x.x - y.x)};
+            }
+    }
+    // one component at a time: three together (one synchronisation per stage) need 64 KB of LDS per
+    // block, which left two blocks per compute unit (FP32, 256^3: 0.0857 against 0.0718 ms)
+#pragma unroll
+    for (int j = 0; j < 3; j++) group_fft<N1, R, -1, true, FFT_PAIR_IN, 1>((V(&)[1][R])v[j], t, lds, addr, tws);
+    // beta dt^2 K(xi) + rhobar I at fixed (xi2, xi3) is quadratic in xi1: A0 + xi1 (A1 + xi1 A2), formed
+    // once per thread (symmetric; upper triangles kept, order 00 01 02 11 12 22)
+    T A0[6], A1[6];
+    {
+        const T x2 = (T)(sp.mfreq ? sp.mfreq[sp.n1 + ky] : sp.k2 * freq_index(ky, sp.n2));
+        const T x3 = (T)(sp.mfreq ? sp.mfreq[sp.n1 + sp.n2 + kz] : sp.k3 * freq_index(kz, sp.n3));
+#pragma unroll
+        for (int q = 0; q < 6; q++) {
+            A0[q] = x2 * (sp.K[q][1] * x2 + sp.K[q][3] * x3) + sp.K[q][2] * x3 * x3;
+            A1[q] = sp.K[q][5] * x2 + sp.K[q][4] * x3;
+        }
+        A0[0] += sp.rhobar;
+        A0[3] += sp.rhobar;
+        A0[5] += sp.rhobar;
+    }
+    // per-thread part of r . z: products of one bin in the working precision, summed in FP64
+    double part = 0.0;
+#pragma unroll
+    for (int m = 0; m < R; m++) {
+        const int kx = t + m * G;
+        const T x1 = (T)(sp.mfreq ? sp.mfreq[kx] : sp.k1 * freq_index(kx, N1));
+        T Kx[6];
+#pragma unroll
+        for (int q = 0; q < 6; q++) Kx[q] = A0[q] + x1 * (A1[q] + x1 * sp.K[q][0]);
+        const T k00 = Kx[0], k01 = Kx[1], k02 = Kx[2], k11 = Kx[3], k12 = Kx[4], k22 = Kx[5];
+        const V r0 = v[0][m], r1 = v[1][m], r2 = v[2][m];
         V z0, z1, z2;
         if (sp.dim == 2) {
-            const T id = s / (k00 * k11 - k01 * k01);
-            z0 = cscale(csub(cscale(u[0][m], k11), cscale(u[1][m], k01)), id);
-            z1 = cscale(csub(cscale(u[1][m], k00), cscale(u[0][m], k01)), id);
+            const T id = sp.inv_ntot / (k00 * k11 - k01 * k01);
+            z0 = cscale(csub(cscale(r0, k11), cscale(r1, k01)), id);
+            z1 = cscale(csub(cscale(r1, k00), cscale(r0, k01)), id);
             z2 = V{0, 0};
         } else {
             // inverse of the symmetric 3x3 by cofactors
@@ -830,332 +836,40 @@ __global__ __launch_bounds__(BLK) void k_zprecond(cx_t<T>* __restrict__ data, lo
             const T c11 = k00 * k22 - k02 * k02;
             const T c12 = k02 * k01 - k00 * k12;
             const T c22 = k00 * k11 - k01 * k01;
-            const T id = s / (k00 * c00 + k01 * c01 + k02 * c02);
-            const V r0 = u[0][m], r1 = u[1][m], r2 = u[2][m];
+            const T id = sp.inv_ntot / (k00 * c00 + k01 * c01 + k02 * c02);
             z0 = cscale(cadd(cadd(cscale(r0, c00), cscale(r1, c01)), cscale(r2, c02)), id);
             z1 = cscale(cadd(cadd(cscale(r0, c01), cscale(r1, c11)), cscale(r2, c12)), id);
             z2 = cscale(cadd(cadd(cscale(r0, c02), cscale(r1, c12)), cscale(r2, c22)), id);
         }
-        // r . z by Parseval on the half spectrum: bins 0 < kx < n1/2 stand for themselves
-        // and their mirrors (weight 2); the packed slot kx = 0 holds the kx = 0 and
-        // kx = n1/2 planes, whose cross terms are imaginary (weight 1, real part)
-        part += u[0][m].x * z0.x + u[0][m].y * z0.y + u[1][m].x * z1.x + u[1][m].y * z1.y + u[2][m].x * z2.x +
-                u[2][m].y * z2.y;
-        u[0][m] = z0;
-        u[1][m] = z1;
-        u[2][m] = z2;
+        part += (double)(r0.x * z0.x + r0.y * z0.y + r1.x * z1.x + r1.y * z1.y + r2.x * z2.x + r2.y * z2.y);
+        asm volatile("" : "+v"(part)); // due here, not where it is used
+        __builtin_amdgcn_sched_barrier(0);
+        v[0][m] = z0;
+        v[1][m] = z1;
+        v[2][m] = z2;
     }
 #pragma unroll
-    for (int j = 0; j < 3; j++) {
-        group_fft<L, R, +1>(u[j], t, lds, addr, twL);
+    for (int j = 0; j < 3; j++) group_fft<N1, R, +1, true, FFT_PAIR_OUT, 1>((V(&)[1][R])v[j], t, lds, addr, tws);
+    if (valid) {
 #pragma unroll
-        for (int m = 0; m < R; m++) st_nt<NM_NT(ZPRE, T)>(&at(j, m), u[j][m]);
+        for (int j = 0; j < 3; j++)
+#pragma unroll
+            for (int m = 0; m < R / 2; m++) {
+                const V x = v[j][2 * m], y = v[j][2 * m + 1];
+                st_nt<NT>(out + j * lay.cs + (o1 + m * G), V{x.x - y.y, x.y + y.x});
+                if (!self) st_nt<NT>(out + j * lay.cs + (o2 + m * G), V{x.x + y.y, y.x - x.y});
+            }
     }
     if (partials) {
-        const double pd = (kx == 0 ? 1.0 : 2.0) * (double)part;
-        double tot = 0.0;
-        if (blockDim.x >= 64) {
-            __shared__ double red[BLK / 64 > 0 ? BLK / 64 : 1];
-            const double w = wave_sum(pd);
-            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
-            __syncthreads();
-            if (threadIdx.x == 0)
-                for (int i = 0; i < (int)(blockDim.x / 64); i++) tot += red[i];
-        } else {
-            // a block narrower than a wavefront (small 2D grids): no cross-lane shuffles
-            __shared__ double red1[64];
-            red1[threadIdx.x] = pd;
-            __syncthreads();
-            if (threadIdx.x == 0)
-                for (int i = 0; i < (int)blockDim.x; i++) tot += red1[i];
-        }
-        if (threadIdx.x == 0)
-            partials[((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = tot;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Axis-wise derivative stages of the operator (see ColOp).  Data are x-spectral
-// and real in y and z, so D_x is the multiplier i xi1 and D_y, D_z are round
-// trips along one axis: forward FFT, i xi / n, inverse FFT.  Every element is
-// read and written by the thread that owns its row in the FFT register layout.
-// ---------------------------------------------------------------------------
-template <typename T, int L, int R, int OP, int BLK, int TXC, bool PF>
-__global__ __launch_bounds__(BLK) void k_colop(cx_t<T>* __restrict__ S, cx_t<T>* __restrict__ S2, long rowstride,
-                                               long cs, int TXr, SpecParams sp, const cx_t<T>* __restrict__ tw)
-{
-    if (stopped(sp.stop)) return;
-    using V = cx_t<T>;
-    constexpr int G = L / R;
-    constexpr bool YAX = (OP == YOP_DERIV || OP == YOP_DIV);
-    const int TX = TXC > 0 ? TXC : TXr;
-    __shared__ V lds[BLK * R];
-    __shared__ V twsm[L > 1 ? L : 2];
-    stage_twiddles<L>(twsm, tw);
-    __syncthreads();
-    const int tid = threadIdx.x, c = tid % TX, t = tid / TX;
-    const int M = sp.n1 / 2;
-    const int kx = blockIdx.x * TX + c;
-    // y stages: block = (kx tile, z plane), rows along y at stride M;
-    // z stages: block = (kx tile, y row), rows along z at the plane stride.
-    // rowstride is the plane (kz) stride of the layout
-    const long start = YAX ? (long)blockIdx.y * rowstride : (long)blockIdx.y * M;
-    const long step = YAX ? (long)M : rowstride;
-#if NM_COL_OFF32
-    // uniform tile bases (scalar registers) plus 32-bit per-lane byte offsets
-    // several fields at once: field blockIdx.z, spectra sp.bs elements apart
-    V* const s1 = S + (long)blockIdx.z * sp.bs + start + (long)blockIdx.x * TX;
-    V* const s2 = S2 + (long)blockIdx.z * sp.bs + start + (long)blockIdx.x * TX;
-    const uint32_t lane = (uint32_t)(c * sizeof(V)) + (uint32_t)t * (uint32_t)(step * sizeof(V));
-    const uint32_t mstep = (uint32_t)(G * step * sizeof(V));
-#else
-    V* s1 = S + (long)blockIdx.z * sp.bs + start + kx;
-    V* s2 = S2 + (long)blockIdx.z * sp.bs + start + kx;
-#endif
-    ColAddrT<TXC> addr{c, TX};
-    const V* twL = twsm;
-    const T xi1 = (T)freq_x(sp, kx);
-    const int n = YAX ? sp.n2 : sp.n3;
-    const double kax = YAX ? sp.k2 * sp.inv_n2 : sp.k3 * sp.inv_n3;
-    T mul[R];
-    if (sp.mfreq) {
-        const double* mf = sp.mfreq + sp.n1 + (YAX ? 0 : sp.n2);
-        const double inv_n = YAX ? sp.inv_n2 : sp.inv_n3;
-#pragma unroll
-        for (int m = 0; m < R; m++) mul[m] = (T)(mf[t + m * G] * inv_n);
-    } else {
-#pragma unroll
-        for (int m = 0; m < R; m++) mul[m] = (T)(kax * freq_index(t + m * G, n));
-    }
-#if NM_COL_OFF32
-    auto ld = [&](const V* base, int comp, V (&v)[R]) {
-        const char* p = (const char*)(base + comp * cs);
-#pragma unroll
-        for (int m = 0; m < R; m++) v[m] = ld_nt<NM_COLOP_OP_NT(OP, T)>((const V*)(p + (lane + (uint32_t)m * mstep)));
-    };
-    auto st = [&](V* base, int comp, const V (&v)[R]) {
-        char* p = (char*)(base + comp * cs);
-#pragma unroll
-        for (int m = 0; m < R; m++) st_nt<NM_COLOP_OP_NT(OP, T)>((V*)(p + (lane + (uint32_t)m * mstep)), v[m]);
-    };
-#else
-    auto ld = [&](const V* col, int comp, V (&v)[R]) {
-#pragma unroll
-        for (int m = 0; m < R; m++) v[m] = ld_nt<NM_COLOP_OP_NT(OP, T)>(col + comp * cs + (long)(t + m * G) * step);
-    };
-    auto st = [&](V* col, int comp, const V (&v)[R]) {
-#pragma unroll
-        for (int m = 0; m < R; m++) st_nt<NM_COLOP_OP_NT(OP, T)>(col + comp * cs + (long)(t + m * G) * step, v[m]);
-    };
-#endif
-    // v <- D v along the column (forward FFT, i xi / n, inverse FFT)
-    auto deriv = [&](V (&v)[R]) {
-        group_fft<L, R, -1>(v, t, lds, addr, twL);
-#pragma unroll
-        for (int m = 0; m < R; m++) v[m] = ZOps<T>::iscale(v[m], mul[m]);
-        group_fft<L, R, +1>(v, t, lds, addr, twL);
-    };
-    // Software-pipelined order (PF): the loads of the next operands are issued before a
-    // transform so that they are in flight while it runs (the LDS barriers of the
-    // transforms do not wait on global loads); it holds up to three operand tiles.
-    if constexpr (PF && OP == YOP_DERIV) {
-        V cur[R], nxt[R];
-        ld(s1, 0, nxt);
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-#pragma unroll
-            for (int m = 0; m < R; m++) cur[m] = nxt[m];
-            if (j < 2) ld(s1, j + 1, nxt);
-            deriv(cur);
-            st(s1, 3 + j, cur);
-        }
-    } else if constexpr (PF && OP == YOP_DIV) {
-        // sigma Voigt 0..5 = s11 s22 s33 s23 s13 s12
-        V a[R], b[R], c[R];
-        ld(s2, 1, a); // s22
-        ld(s2, 5, b); // s12
-        ld(s2, 0, c); // s11
-        deriv(a);
-#pragma unroll
-        for (int m = 0; m < R; m++) a[m] = cadd(a[m], ZOps<T>::iscale(b[m], xi1));
-        st(s1, 1, a);
-        ld(s2, 3, a); // s23
-        deriv(b);
-#pragma unroll
-        for (int m = 0; m < R; m++) b[m] = cadd(b[m], ZOps<T>::iscale(c[m], xi1));
-        st(s1, 0, b);
-        ld(s2, 4, c); // s13
-        deriv(a);
-#pragma unroll
-        for (int m = 0; m < R; m++) a[m] = cadd(a[m], ZOps<T>::iscale(c[m], xi1));
-        st(s1, 2, a);
-    } else if constexpr (PF && OP == ZOP_STRAIN) {
-        const T sc = (T)sp.inv_n1;
-        V a[R], b[R], c[R];
-        ld(s1, 0, a); // U1
-        ld(s1, 2, b); // U3
-        ld(s1, 1, c); // U2
-        {
-            V d[R];
-#pragma unroll
-            for (int m = 0; m < R; m++) d[m] = cscale(ZOps<T>::iscale(a[m], xi1), sc);
-            st(s2, 0, d); // eps11
-        }
-        deriv(a); // D_z U1
-#pragma unroll
-        for (int m = 0; m < R; m++) a[m] = cscale(cadd(a[m], ZOps<T>::iscale(b[m], xi1)), sc);
-        st(s2, 4, a); // g13
-        ld(s1, 3, a); // D_y U1
-        deriv(b);     // D_z U3
-#pragma unroll
-        for (int m = 0; m < R; m++) b[m] = cscale(b[m], sc);
-        st(s2, 2, b); // eps33
-        ld(s1, 5, b); // D_y U3
-#pragma unroll
-        for (int m = 0; m < R; m++) a[m] = cscale(cadd(a[m], ZOps<T>::iscale(c[m], xi1)), sc);
-        st(s2, 5, a); // g12
-        ld(s1, 4, a); // D_y U2
-        deriv(c);     // D_z U2
-#pragma unroll
-        for (int m = 0; m < R; m++) c[m] = cscale(cadd(c[m], b[m]), sc);
-        st(s2, 3, c); // g23
-#pragma unroll
-        for (int m = 0; m < R; m++) a[m] = cscale(a[m], sc);
-        st(s2, 1, a); // eps22
-    } else if constexpr (PF && OP == ZOP_DIVZ) {
-        const T cd = (T)(-sp.bdt2 * sp.inv_n1);
-        constexpr int SRC[3] = {4, 3, 2};
-        V v[R], w[R], vn[R];
-        ld(s2, SRC[0], v);
-        ld(s1, 0, w);
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            if (j < 2) ld(s2, SRC[j + 1], vn);
-            deriv(v);
-#pragma unroll
-            for (int m = 0; m < R; m++) v[m] = cscale(cadd(v[m], w[m]), cd);
-            st(s1, j, v);
-            if (j < 2) {
-                ld(s1, j + 1, w);
-#pragma unroll
-                for (int m = 0; m < R; m++) v[m] = vn[m];
-            }
-        }
-    } else if constexpr (OP == YOP_DERIV) {
-#pragma unroll 1
-        for (int j = 0; j < 3; j++) {
-            V v[R];
-            ld(s1, j, v);
-            deriv(v);
-            st(s1, 3 + j, v);
-        }
-    } else if constexpr (OP == YOP_DIV) {
-        // sigma Voigt 0..5 = s11 s22 s33 s23 s13 s12; five components are read once each
-        // (s12 feeds both D_y s12 and i xi1 s12)
-        V s12[R];
-        {
-            V v[R], w[R];
-            ld(s2, 5, v);
-#pragma unroll
-            for (int m = 0; m < R; m++) s12[m] = v[m];
-            deriv(v);
-            ld(s2, 0, w);
-#pragma unroll
-            for (int m = 0; m < R; m++) v[m] = cadd(v[m], ZOps<T>::iscale(w[m], xi1));
-            st(s1, 0, v);
-        }
-        {
-            V v[R];
-            ld(s2, 1, v);
-            deriv(v);
-#pragma unroll
-            for (int m = 0; m < R; m++) v[m] = cadd(v[m], ZOps<T>::iscale(s12[m], xi1));
-            st(s1, 1, v);
-        }
-        {
-            V v[R], w[R];
-            ld(s2, 3, v);
-            deriv(v);
-            ld(s2, 4, w);
-#pragma unroll
-            for (int m = 0; m < R; m++) v[m] = cadd(v[m], ZOps<T>::iscale(w[m], xi1));
-            st(s1, 2, v);
-        }
-    } else if constexpr (OP == ZOP_STRAIN) {
-        const T sc = (T)sp.inv_n1;
-        V a[R], b[R];
-        // eps11 = i xi1 U1 ; A = D_z U1
-        ld(s1, 0, a);
-#pragma unroll
-        for (int m = 0; m < R; m++) b[m] = cscale(ZOps<T>::iscale(a[m], xi1), sc);
-        st(s2, 0, b);
-        deriv(a);
-        // g13 = D_z U1 + i xi1 U3 ; eps33 = D_z U3
-        ld(s1, 2, b);
-#pragma unroll
-        for (int m = 0; m < R; m++) a[m] = cscale(cadd(a[m], ZOps<T>::iscale(b[m], xi1)), sc);
-        st(s2, 4, a);
-        deriv(b);
-#pragma unroll
-        for (int m = 0; m < R; m++) b[m] = cscale(b[m], sc);
-        st(s2, 2, b);
-        // g23 = D_z U2 + D_y U3 ; g12 = D_y U1 + i xi1 U2 ; eps22 = D_y U2
-        ld(s1, 1, a);
-#pragma unroll
-        for (int m = 0; m < R; m++) b[m] = a[m];
-        deriv(b);
-        {
-            V d[R];
-            ld(s1, 5, d);
-#pragma unroll
-            for (int m = 0; m < R; m++) d[m] = cscale(cadd(b[m], d[m]), sc);
-            st(s2, 3, d);
-            ld(s1, 3, d);
-#pragma unroll
-            for (int m = 0; m < R; m++) d[m] = cscale(cadd(d[m], ZOps<T>::iscale(a[m], xi1)), sc);
-            st(s2, 5, d);
-            ld(s1, 4, d);
-#pragma unroll
-            for (int m = 0; m < R; m++) d[m] = cscale(d[m], sc);
-            st(s2, 1, d);
-        }
-    } else {
-        // q_j = -beta dt^2 / n1 (Q_j + D_z sigma_j3): sigma_13 = S2[4], sigma_23 = S2[3], sigma_33 = S2[2]
-        const T cd = (T)(-sp.bdt2 * sp.inv_n1);
-        constexpr int SRC[3] = {4, 3, 2};
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            V v[R], w[R];
-            ld(s2, SRC[j], v);
-            deriv(v);
-            ld(s1, j, w);
-#pragma unroll
-            for (int m = 0; m < R; m++) v[m] = cscale(cadd(v[m], w[m]), cd);
-            st(s1, j, v);
-        }
+        // a row and its mirror contribute the same
+        const double tot = block_sum(valid ? (self ? 1.0 : 2.0) * part : 0.0);
+        if (threadIdx.x == 0) partials[(long)fld * gridDim.x + blockIdx.x] = tot;
     }
 }
 
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-static inline int radix_x(int M) { return M >= 8 ? 8 : M; }
-
-// Radix of the x-direction stress pass in FP64 (it holds six components per thread).
-#ifndef NM_STRESS_R64
-#define NM_STRESS_R64 4
-#endif
-#ifndef NM_STRESS_R32
-#define NM_STRESS_R32 4
-#endif
-
-int xfwd_blocks(int n1, long nlines)
-{
-    const int M = n1 / 2, G = M / radix_x(M), LPB = kBlock / G;
-    return (int)((nlines + LPB - 1) / LPB);
-}
-int xinv_blocks(int n1, long nlines) { return xfwd_blocks(n1, nlines); }
-
 #define NM_SIZE_SWITCH(n, ...)                                                                                         \
     switch (n) {                                                                                                       \
     case 8: { constexpr int NN = 8; __VA_ARGS__; } break;                                                              \
@@ -1168,314 +882,168 @@ int xinv_blocks(int n1, long nlines) { return xfwd_blocks(n1, nlines); }
     default: return -1;                                                                                                \
     }
 
-template <typename T> int launch_xfwd(int mode, int n1, const XFwdArgs& a, const void* tw, hipStream_t s)
+static Cols y_cols(const Layout& l)
 {
-    const int blocks = xfwd_blocks(n1, a.nlines);
+    return Cols{l.M * l.n3, l.log2M, l.M - 1, (long)l.n2 * l.M, (long)l.M};
+}
+static Cols z_cols(const Layout& l) { return Cols{l.M * l.n2, 31, 0x7fffffff, 0, (long)l.n2 * l.M}; }
+static AxisFreq axis_freq(const SpecParams& sp, int axis)
+{
+    const double k[3] = {sp.k1, sp.k2, sp.k3}, in[3] = {sp.inv_n1, sp.inv_n2, sp.inv_n3};
+    const int n[3] = {sp.n1, sp.n2, sp.n3}, off[3] = {0, sp.n1, sp.n1 + sp.n2};
+    return AxisFreq{sp.mfreq ? sp.mfreq + off[axis] : nullptr, k[axis], in[axis], n[axis]};
+}
+template <typename T, int L> static int col_tiles(const Cols& g)
+{
+    constexpr int TX = ColShape<T, L>::TX;
+    return (g.ncols + TX - 1) / TX;
+}
+static int ok() { return hipGetLastError() == hipSuccess ? 0 : -2; }
+
+template <typename T> int launch_ystart(int mode, const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s)
+{
+    const Cols g = y_cols(a.lay);
+    const AxisFreq f = axis_freq(sp, 1);
     const cx_t<T>* t = (const cx_t<T>*)tw;
-    NM_SIZE_SWITCH(n1, {
-        constexpr int M = NN / 2, R = (M >= 8 ? 8 : M);
-        if (mode == XF_PLAIN) hipLaunchKernelGGL((k_xfwd<T, NN, R, XF_PLAIN>), dim3(blocks), dim3(kBlock), 0, s, a, t);
-        else if (mode == XF_EXPLICIT)
-            hipLaunchKernelGGL((k_xfwd<T, NN, R, XF_EXPLICIT>), dim3(blocks), dim3(kBlock), 0, s, a, t);
-        else hipLaunchKernelGGL((k_xfwd<T, NN, R, XF_UPDATE>), dim3(blocks), dim3(kBlock), 0, s, a, t);
+    NM_SIZE_SWITCH(a.lay.n2, {
+        const int nt = col_tiles<T, NN>(g);
+        const dim3 grid(3 * nt, 1, a.lay.nb), block(ColShape<T, NN>::BLK);
+        if (mode == YS_APPLY) hipLaunchKernelGGL((k_ystart<T, NN, YS_APPLY>), grid, block, 0, s, a, g, f, nt, t);
+        else if (mode == YS_PCG) hipLaunchKernelGGL((k_ystart<T, NN, YS_PCG>), grid, block, 0, s, a, g, f, nt, t);
+        else if constexpr (sizeof(T) == 8) // the explicit scheme runs in FP64
+            hipLaunchKernelGGL((k_ystart<T, NN, YS_EXPLICIT>), grid, block, 0, s, a, g, f, nt, t);
+        else return -1;
     })
-    return hipGetLastError() == hipSuccess ? 0 : -2;
+    return ok();
 }
 
-template <typename T> int launch_xinv(int mode, int n1, const XInvArgs& a, const void* tw, hipStream_t s)
+template <typename T> int launch_zstrain(const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s)
 {
-    const int blocks = xinv_blocks(n1, a.nlines);
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    NM_SIZE_SWITCH(n1, {
-        constexpr int M = NN / 2, R = (M >= 8 ? 8 : M);
-        if (mode == XI_PLAIN) hipLaunchKernelGGL((k_xinv<T, NN, R, XI_PLAIN>), dim3(blocks), dim3(kBlock), 0, s, a, t);
-        else if (mode == XI_OPERATOR)
-            hipLaunchKernelGGL((k_xinv<T, NN, R, XI_OPERATOR>), dim3(blocks), dim3(kBlock), 0, s, a, t);
-        else if (mode == XI_EXPLICIT)
-            hipLaunchKernelGGL((k_xinv<T, NN, R, XI_EXPLICIT>), dim3(blocks), dim3(kBlock), 0, s, a, t);
-        else hipLaunchKernelGGL((k_xinv<T, NN, R, XI_PRECOND>), dim3(blocks), dim3(kBlock), 0, s, a, t);
+    const Cols g = z_cols(a.lay);
+    const AxisFreq f = axis_freq(sp, 2);
+    NM_SIZE_SWITCH(a.lay.n3, {
+        const int nt = col_tiles<T, NN>(g);
+        hipLaunchKernelGGL((k_zstrain<T, NN>), dim3(3 * nt, 1, a.lay.nb), dim3(ColShape<T, NN>::BLK), 0, s, a, g, f, nt,
+                           (const cx_t<T>*)tw);
     })
-    return hipGetLastError() == hipSuccess ? 0 : -2;
+    return ok();
 }
 
-template <typename T> int launch_xpupdate(int n1, const XInvArgs& a, const void* tw, hipStream_t s)
+template <typename T> int launch_zdiv(const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s)
 {
-    const int blocks = xinv_blocks(n1, a.nlines);
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    NM_SIZE_SWITCH(n1, {
-        constexpr int M = NN / 2, R = (M >= 8 ? 8 : M);
-        hipLaunchKernelGGL((k_xpupdate<T, NN, R>), dim3(blocks), dim3(kBlock), 0, s, a, t);
+    const Cols g = z_cols(a.lay);
+    const AxisFreq f = axis_freq(sp, 2);
+    NM_SIZE_SWITCH(a.lay.n3, {
+        const int nt = col_tiles<T, NN>(g);
+        hipLaunchKernelGGL((k_zdiv<T, NN>), dim3(3 * nt + (a.carry.action != RED_NONE), 1, a.lay.nb),
+                           dim3(ColShape<T, NN>::BLK), 0, s, a, g, f, nt, (const cx_t<T>*)tw);
     })
-    return hipGetLastError() == hipSuccess ? 0 : -2;
+    return ok();
 }
 
-template <typename T>
-int launch_xstress(int n1, void* spec, const SpecLayout& lay, const uint16_t* phase, const void* C21, const void* tw,
-                   hipStream_t s)
+template <typename T> int yend_blocks(const Layout& l)
 {
-    const long lpc = (long)lay.n2 * lay.n3 * lay.nb;
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    NM_SIZE_SWITCH(n1, {
-        constexpr int M = NN / 2;
-        constexpr int RQ = sizeof(T) == 8 ? (NN == 512 ? NM_STRESS512_R64 : NM_STRESS_R64) : NM_STRESS_R32;
-        constexpr int R0 = M >= RQ ? RQ : M;
-        constexpr int R = R0 * 64 >= M ? R0 : M / 64; // a line stays inside one wavefront
-        constexpr int G = M / R, LPB = kBlock / G;
-        const int blocks = (int)((lpc + LPB - 1) / LPB);
-        hipLaunchKernelGGL((k_xstress<T, NN, R>), dim3(blocks), dim3(kBlock), 0, s, (cx_t<T>*)spec, lay, phase,
-                           (const T*)C21, t);
-    })
-    return hipGetLastError() == hipSuccess ? 0 : -2;
-}
-
-// Radix and block size of the column passes.  The y pass holds one component
-// per thread (radix 16: one LDS exchange for L = 256); the fused z kernels hold
-// three components, so FP64 uses a smaller radix to bound register pressure.
-#ifndef NM_ZSPEC_R64
-#define NM_ZSPEC_R64 8
-#endif
-#ifndef NM_ZSPEC_R32
-#define NM_ZSPEC_R32 8
-#endif
-#ifndef NM_ZSPEC_BLK64
-#define NM_ZSPEC_BLK64 256
-#endif
-#ifndef NM_ZSPEC_BLK32
-#define NM_ZSPEC_BLK32 256
-#endif
-
-// Block sizes of the column passes on 512-long columns: a block holds BLK / G columns of G
-// threads each, so a larger block keeps the rows of a tile wide (coalesced) when G is large.
-// Measured at 512^3 (pass times in us, 256-thread blocks -> these): FP32 z strain 1885 -> 1410,
-// z divergence 1352 -> 1098, y divergence 1050 -> 906, preconditioner y passes 759/765 ->
-// 606/607 and z pass 1544 -> 1086 (radix 16); FP64 z strain 3220 -> 2810, z divergence
-// 2569 -> 2127, preconditioner z pass 2994 -> 2518.  The FP64 y passes stay at 256 (512 was
-// 2-5% slower).  LDS per block: up to 64 KB of exchange buffer plus the twiddle table.
-#ifndef NM_COL512_BLK32
-#define NM_COL512_BLK32 512
-#endif
-#ifndef NM_YPASS512_BLK32
-#define NM_YPASS512_BLK32 512
-#endif
-#ifndef NM_ZSPEC512_BLK32
-#define NM_ZSPEC512_BLK32 512
-#endif
-#ifndef NM_ZSPEC512_BLK64
-#define NM_ZSPEC512_BLK64 512
-#endif
-#ifndef NM_COL512_ZBLK64
-#define NM_COL512_ZBLK64 512
-#endif
-#ifndef NM_YPASS512_BLK64
-#define NM_YPASS512_BLK64 256
-#endif
-#ifndef NM_ZSPEC512_R32
-#define NM_ZSPEC512_R32 16
-#endif
-
-template <int L> constexpr int ypass_radix() { return L >= 16 ? 16 : L; }
-template <typename T, int L> constexpr int ypass_block()
-{
-    return L == 512 ? (sizeof(T) == 4 ? NM_YPASS512_BLK32 : NM_YPASS512_BLK64) : 256;
-}
-template <typename T, int L> constexpr int zspec_radix()
-{
-    return L < 8 ? L
-                 : (sizeof(T) == 8 ? (NM_ZSPEC_R64 < L ? NM_ZSPEC_R64 : L)
-                                   : (L == 512 ? NM_ZSPEC512_R32 : (NM_ZSPEC_R32 < L ? NM_ZSPEC_R32 : L)));
-}
-template <typename T, int L> constexpr int zspec_block()
-{
-    return L == 512 ? (sizeof(T) == 8 ? NM_ZSPEC512_BLK64 : NM_ZSPEC512_BLK32)
-                    : (sizeof(T) == 8 ? NM_ZSPEC_BLK64 : NM_ZSPEC_BLK32);
-}
-
-
-template <typename T>
-int launch_ypass(int dir, int ncomp, const SpecLayout& lay, void* spec, const void* tw, hipStream_t s)
-{
-    const int M = lay.M, n3 = lay.n3;
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    NM_SIZE_SWITCH(lay.n2, {
-        constexpr int R = ypass_radix<NN>();
-        constexpr int G = NN / R;
-        constexpr int BLK = ypass_block<T, NN>();
-        constexpr int TXP = BLK / G;
-        const int TX = M >= TXP ? TXP : M;
-        dim3 grid(M / TX, n3, ncomp), block(TX * G);
-        cx_t<T>* d = (cx_t<T>*)spec;
-        if (M >= TXP) {
-            if (dir < 0)
-                hipLaunchKernelGGL((k_ypass<T, NN, R, -1, BLK, TXP>), grid, block, 0, s, d, (long)M, lay.ps, lay.cs, TX, t, lay.stop, lay.bs);
-            else
-                hipLaunchKernelGGL((k_ypass<T, NN, R, +1, BLK, TXP>), grid, block, 0, s, d, (long)M, lay.ps, lay.cs, TX, t, lay.stop, lay.bs);
-        } else {
-            if (dir < 0)
-                hipLaunchKernelGGL((k_ypass<T, NN, R, -1, BLK, 0>), grid, block, 0, s, d, (long)M, lay.ps, lay.cs, TX, t, lay.stop, lay.bs);
-            else
-                hipLaunchKernelGGL((k_ypass<T, NN, R, +1, BLK, 0>), grid, block, 0, s, d, (long)M, lay.ps, lay.cs, TX, t, lay.stop, lay.bs);
-        }
-    })
-    return hipGetLastError() == hipSuccess ? 0 : -2;
-}
-
-template <typename T, int L, int BLK, int TXC>
-static void zprecond_dispatch(dim3 grid, dim3 block, hipStream_t s, cx_t<T>* spec, const SpecLayout& lay, int TX,
-                              const SpecParams& sp, const cx_t<T>* t, double* partials)
-{
-    constexpr int R = zspec_radix<T, L>();
-    hipLaunchKernelGGL((k_zprecond<T, L, R, BLK, TXC>), grid, block, 0, s, spec, lay.cs, lay.ps, TX, sp, t,
-                       partials);
-}
-
-template <typename T> int zprecond_blocks(const SpecParams& sp)
-{
-    const int M = sp.n1 / 2;
-    if (sp.n3 == 1) {
-        constexpr int BLK = zspec_block<T, 1>();
-        const int TX = M < BLK ? M : BLK;
-        return (M / TX) * sp.n2;
-    }
     int nb = 0;
-    [&]() -> int {
-        NM_SIZE_SWITCH(sp.n3, {
-            constexpr int BLK = zspec_block<T, NN>();
-            constexpr int G = NN / zspec_radix<T, NN>();
-            constexpr int TXP = BLK / G;
-            nb = (M >= TXP ? M / TXP : 1) * sp.n2;
+    auto count = [&]() -> int {
+        NM_SIZE_SWITCH(l.n2, nb = 3 * col_tiles<T, NN>(y_cols(l));)
+        return 0;
+    };
+    count();
+    return nb;
+}
+
+template <typename T> int launch_yend(int mode, const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s)
+{
+    const Cols g = y_cols(a.lay);
+    const AxisFreq f = axis_freq(sp, 1);
+    const cx_t<T>* t = (const cx_t<T>*)tw;
+    NM_SIZE_SWITCH(a.lay.n2, {
+        const int nt = col_tiles<T, NN>(g);
+        const dim3 grid(3 * nt, 1, a.lay.nb), block(ColShape<T, NN>::BLK);
+        if (mode == YE_OUT) hipLaunchKernelGGL((k_yend<T, NN, YE_OUT>), grid, block, 0, s, a, g, f, nt, t);
+        else if (mode == YE_UPDATE) hipLaunchKernelGGL((k_yend<T, NN, YE_UPDATE>), grid, block, 0, s, a, g, f, nt, t);
+        else if constexpr (sizeof(T) == 8) hipLaunchKernelGGL((k_yend<T, NN, YE_EXPLICIT>), grid, block, 0, s, a, g, f, nt, t);
+        else return -1;
+    })
+    return ok();
+}
+
+template <typename T> int launch_colfft(const ColFft& f, const void* tw, hipStream_t s)
+{
+    const Cols g = f.axis == 1 ? y_cols(f.lay) : z_cols(f.lay);
+    const cx_t<T>* t = (const cx_t<T>*)tw;
+    NM_SIZE_SWITCH(f.axis == 1 ? f.lay.n2 : f.lay.n3, {
+        const int nt = col_tiles<T, NN>(g);
+        const dim3 grid(3 * nt + (f.carry.action != RED_NONE), 1, f.lay.nb), block(ColShape<T, NN>::BLK);
+        if (f.dir < 0) hipLaunchKernelGGL((k_colfft<T, NN, -1>), grid, block, 0, s, f, g, nt, t);
+        else hipLaunchKernelGGL((k_colfft<T, NN, +1>), grid, block, 0, s, f, g, nt, t);
+    })
+    return ok();
+}
+
+template <typename T> int xstress_blocks(const Layout& l)
+{
+    const int lpb = kBlock / (l.n1 / kXR), np = l.n2 / 2 * l.n3;
+    return (np + lpb - 1) / lpb;
+}
+
+template <typename T> int launch_xstress(const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s)
+{
+    const AxisFreq f = axis_freq(sp, 0);
+    NM_SIZE_SWITCH(a.lay.n1, {
+        hipLaunchKernelGGL((k_xstress<T, NN>), dim3(xstress_blocks<T>(a.lay), 1, a.lay.nb), dim3(kBlock), 0, s, a, f,
+                           a.lay.n2 / 2 * a.lay.n3, (const cx_t<T>*)tw);
+    })
+    return ok();
+}
+
+// Rows (ky, kz) of which one of each mirrored couple is taken; `full` of them belong to 0 < kz < n3/2.
+static int mirror_rows(const Layout& l, int* full)
+{
+    *full = l.n3 > 1 ? (l.n3 / 2 - 1) * l.n2 : 0;
+    return *full + (l.n2 / 2 + 1) * (l.n3 > 1 ? 2 : 1);
+}
+
+template <typename T> int xprecond_blocks(const Layout& l)
+{
+    int nb = 0, full;
+    const int rows = mirror_rows(l, &full);
+    auto count = [&]() -> int {
+        NM_SIZE_SWITCH(l.n1, {
+            constexpr int LPB = XPShape<T, NN>::BLK / XPShape<T, NN>::G;
+            nb = (rows + LPB - 1) / LPB;
         })
         return 0;
-    }();
+    };
+    count();
     return nb;
 }
 
 template <typename T>
-int launch_zprecond(const SpecParams& sp, const SpecLayout& lay, void* spec, const void* tw, hipStream_t s,
-                    double* partials)
+int launch_xprecond(const SpecParams& sp, const Layout& lay, const void* src, long sc, long sb, void* S2, const void* tw,
+                    hipStream_t s, double* partials)
 {
-    const int M = sp.n1 / 2;
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    cx_t<T>* d = (cx_t<T>*)spec;
-    if (sp.n3 == 1) {
-        constexpr int BLK = zspec_block<T, 1>();
-        const int TX = M < BLK ? M : BLK;
-        zprecond_dispatch<T, 1, BLK, 0>(dim3(M / TX, sp.n2, sp.bk), dim3(TX), s, d, lay, TX, sp, t, partials);
-    } else {
-        NM_SIZE_SWITCH(sp.n3, {
-            constexpr int BLK = zspec_block<T, NN>();
-            constexpr int G = NN / zspec_radix<T, NN>();
-            constexpr int TXP = BLK / G;
-            if (M >= TXP)
-                zprecond_dispatch<T, NN, BLK, TXP>(dim3(M / TXP, sp.n2, sp.bk), dim3(TXP * G), s, d, lay, TXP, sp, t,
-                                                    partials);
-            else
-                zprecond_dispatch<T, NN, BLK, 0>(dim3(1, sp.n2, sp.bk), dim3(M * G), s, d, lay, M, sp, t, partials);
-        })
-    }
-    return hipGetLastError() == hipSuccess ? 0 : -2;
-}
-
-#ifndef NM_COLOP_R64
-#define NM_COLOP_R64 16
-#endif
-// Software-pipelined column operators (three operand tiles per thread).
-#ifndef NM_COLOP_PF32
-#define NM_COLOP_PF32 1
-#endif
-#ifndef NM_COLOP_PF64
-#define NM_COLOP_PF64 0
-#endif
-template <typename T, int L> constexpr int colop_radix()
-{
-    return L < 16 ? L : (sizeof(T) == 8 ? (NM_COLOP_R64 < L ? NM_COLOP_R64 : L) : 16);
-}
-
-#ifndef NM_COL256_YBLK32
-#define NM_COL256_YBLK32 256
-#endif
-#ifndef NM_COL256_ZBLK32
-#define NM_COL256_ZBLK32 256
-#endif
-template <typename T, int L, int OP> constexpr int colop_block()
-{
-    return L == 512 ? (sizeof(T) == 4 ? NM_COL512_BLK32
-                                      : ((OP == ZOP_STRAIN || OP == ZOP_DIVZ) ? NM_COL512_ZBLK64 : 256))
-                    : ((L == 256 && sizeof(T) == 4) ? ((OP == ZOP_STRAIN || OP == ZOP_DIVZ) ? NM_COL256_ZBLK32
-                                                                                            : NM_COL256_YBLK32)
-                                                    : 256);
-}
-
-template <typename T, int L, int TXC>
-static void colop_dispatch(int op, dim3 grid, dim3 block, hipStream_t s, cx_t<T>* S, cx_t<T>* S2, long rowstride,
-                           long cs, int TX, const SpecParams& sp, const cx_t<T>* t)
-{
-    constexpr int R = colop_radix<T, L>();
-    constexpr bool PF = sizeof(T) == 8 ? NM_COLOP_PF64 : NM_COLOP_PF32;
-    switch (op) {
-    case YOP_DERIV:
-        hipLaunchKernelGGL((k_colop<T, L, R, YOP_DERIV, colop_block<T, L, YOP_DERIV>(), TXC, PF>), grid, block, 0, s, S,
-                           S2, rowstride, cs, TX, sp, t);
-        break;
-    case YOP_DIV:
-        hipLaunchKernelGGL((k_colop<T, L, R, YOP_DIV, colop_block<T, L, YOP_DIV>(), TXC, PF>), grid, block, 0, s, S, S2,
-                           rowstride, cs, TX, sp, t);
-        break;
-    case ZOP_STRAIN:
-        hipLaunchKernelGGL((k_colop<T, L, R, ZOP_STRAIN, colop_block<T, L, ZOP_STRAIN>(), TXC, PF>), grid, block, 0, s,
-                           S, S2, rowstride, cs, TX, sp, t);
-        break;
-    default:
-        hipLaunchKernelGGL((k_colop<T, L, R, ZOP_DIVZ, colop_block<T, L, ZOP_DIVZ>(), TXC, PF>), grid, block, 0, s, S,
-                           S2, rowstride, cs, TX, sp, t);
-        break;
-    }
-}
-
-template <typename T>
-int launch_colop(int op, const SpecParams& sp, const SpecLayout& lay, void* S, void* S2, const void* tw,
-                 hipStream_t s)
-{
-    const int M = lay.M;
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    cx_t<T>* a = (cx_t<T>*)S;
-    cx_t<T>* b = (cx_t<T>*)S2;
-    const bool yax = (op == YOP_DERIV || op == YOP_DIV);
-    const int L = yax ? lay.n2 : lay.n3;
-    const int planes = yax ? lay.n3 : lay.n2;
-    if (L == 1) {
-        const int TX = M < 256 ? M : 256;
-        colop_dispatch<T, 1, 0>(op, dim3(M / TX, planes, sp.bk), dim3(TX), s, a, b, lay.ps, lay.cs, TX, sp, t);
-    } else {
-        NM_SIZE_SWITCH(L, {
-            constexpr int G = NN / colop_radix<T, NN>();
-            // y and z operators may take different block sizes (and so tile widths)
-            constexpr int TXY = colop_block<T, NN, YOP_DERIV>() / G;
-            constexpr int TXZ = colop_block<T, NN, ZOP_STRAIN>() / G;
-            if (yax ? M >= TXY : M >= TXZ) {
-                if (yax)
-                    colop_dispatch<T, NN, TXY>(op, dim3(M / TXY, planes, sp.bk), dim3(TXY * G), s, a, b, lay.ps, lay.cs,
-                                               TXY, sp, t);
-                else
-                    colop_dispatch<T, NN, TXZ>(op, dim3(M / TXZ, planes, sp.bk), dim3(TXZ * G), s, a, b, lay.ps, lay.cs,
-                                               TXZ, sp, t);
-            } else {
-                colop_dispatch<T, NN, 0>(op, dim3(1, planes, sp.bk), dim3(M * G), s, a, b, lay.ps, lay.cs, M, sp, t);
-            }
-        })
-    }
-    return hipGetLastError() == hipSuccess ? 0 : -2;
+    int full;
+    const int rows = mirror_rows(lay, &full);
+    NM_SIZE_SWITCH(lay.n1, {
+        hipLaunchKernelGGL((k_xprecond<T, NN>), dim3(xprecond_blocks<T>(lay), 1, lay.nb), dim3(XPShape<T, NN>::BLK), 0, s,
+                           precond_params<T>(sp), lay, (const cx_t<T>*)src, sc, sb, (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials);
+    })
+    return ok();
 }
 
 #define NM_INST(T)                                                                                                     \
-    template int launch_xfwd<T>(int, int, const XFwdArgs&, const void*, hipStream_t);                                  \
-    template int launch_xinv<T>(int, int, const XInvArgs&, const void*, hipStream_t);                                  \
-    template int launch_xpupdate<T>(int, const XInvArgs&, const void*, hipStream_t);                                   \
-    template int launch_xstress<T>(int, void*, const SpecLayout&, const uint16_t*, const void*, const void*,          \
-                                   hipStream_t);                                                                       \
-    template int launch_ypass<T>(int, int, const SpecLayout&, void*, const void*, hipStream_t);                        \
-    template int launch_zprecond<T>(const SpecParams&, const SpecLayout&, void*, const void*, hipStream_t, double*); \
-    template int zprecond_blocks<T>(const SpecParams&);                                                             \
-    template int launch_colop<T>(int, const SpecParams&, const SpecLayout&, void*, void*, const void*, hipStream_t);
+    template int xstress_blocks<T>(const Layout&);                                                                     \
+    template int yend_blocks<T>(const Layout&);                                                                        \
+    template int xprecond_blocks<T>(const Layout&);                                                                    \
+    template int launch_ystart<T>(int, const SpecParams&, const PassArgs&, const void*, hipStream_t);                  \
+    template int launch_zstrain<T>(const SpecParams&, const PassArgs&, const void*, hipStream_t);                      \
+    template int launch_xstress<T>(const SpecParams&, const PassArgs&, const void*, hipStream_t);                      \
+    template int launch_zdiv<T>(const SpecParams&, const PassArgs&, const void*, hipStream_t);                         \
+    template int launch_yend<T>(int, const SpecParams&, const PassArgs&, const void*, hipStream_t);                    \
+    template int launch_colfft<T>(const ColFft&, const void*, hipStream_t);                                            \
+    template int launch_xprecond<T>(const SpecParams&, const Layout&, const void*, long, long, void*, const void*,     \
+                                    hipStream_t, double*);
 NM_INST(double)
 NM_INST(float)
 

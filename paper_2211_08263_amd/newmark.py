@@ -369,8 +369,8 @@ def green_solve(ctx: Context, V) -> np.ndarray:
     return X
 
 
-OPERATOR_PASSES = ("x_fwd", "y_deriv", "z_strain", "x_stress", "y_div", "z_div", "x_inv_inertia")
-PRECOND_PASSES = ("x_fwd", "y_fwd3", "z_precond", "y_inv3", "x_inv")
+OPERATOR_PASSES = ("y_start", "z_strain", "x_sigma", "z_div", "y_end")
+PRECOND_PASSES = ("y_fwd", "z_fwd", "x_precond", "z_inv", "y_inv")
 
 
 def profile_passes(ctx: Context, which: int, u, out, reps: int = 10):

@@ -1,0 +1,53 @@
+"""The operator's and the preconditioner's passes at the edges of their launch shapes, against the
+FP64 oracle.
+
+The column passes hold tiles of columns (fewer columns than a tile on the smallest grids), the stress
+pass pairs of x rows (one wavefront per pair up to 256 voxels, two at 512), the preconditioner's x
+pass pairs of mirrored rows (own mirrors at ky, kz = 0 and n/2; butterflies from one to sixty-four
+threads per row); in 3D the z passes carry the reductions of the passes before, in 2D there are no z
+passes.  The grids put the shortest and the longest axis in every place.
+
+Bars: FP64 1e-12 and FP32 1e-5 of the largest entry (a few hundred roundings of eps), as for the
+other operator checks; the conjugate-gradient solve replayed for the same number of iterations
+1e-10 in the 2-norm (rounding differences grow with the condition number, below 1e3 here)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2211_08263_amd import newmark as nmb
+from paper_2211_08263_amd import workloads as W
+
+from gpu_common import dev, field3, random_problem, rel_l2, rel_max
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(3, (8, 8, 8)), (3, (16, 8, 16)), (3, (512, 8, 8)), (3, (8, 512, 8)), (3, (8, 8, 512)), (3, (256, 8, 16)),
+         (3, (128, 16, 8)), (2, (8, 8)), (2, (8, 512)), (2, (512, 8))]
+
+
+@pytest.mark.parametrize("dim,n", CASES, ids=["x".join(map(str, n)) for _, n in CASES])
+def test_passes_at_the_edges_of_their_shapes(dim, n):
+    import torch
+    pb = random_problem(dim, n, seed=11 + sum(n))
+    op = oracle.OracleProblem.from_problem(pb)
+    u = W.random_field(op.field_shape, seed=5)
+    b = W.random_field(op.field_shape, seed=6)
+    want = {"operator": field3(op.apply(u), dim), "precond": field3(op.precond(u), dim)}
+    with nmb.newmark_init_problem(pb, nmb.Options(tol=1e-10)) as ctx:
+        for dtype, bar in ((torch.float64, 1e-12), (torch.float32, 1e-5)):
+            ud = dev(field3(u, dim), dtype)
+            for name, fn in (("operator", nmb.apply_operator), ("precond", nmb.precond_apply)):
+                out = torch.full_like(ud, 7.0)
+                fn(ctx, ud, out)
+                torch.cuda.synchronize()
+                err = rel_max(out.double().cpu().numpy(), want[name])
+                print(f"{name} {n} {dtype}: {err:.2e}", flush=True)
+                assert err <= bar
+        x = torch.zeros(3 * ctx.N, dtype=torch.float64, device="cuda")
+        it, rel = nmb.pcg_solve(ctx, dev(field3(b, dim)).reshape(-1), x, tol=1e-10)
+        assert 1 < it < 300 and rel <= 1e-10
+        got = x.cpu().numpy().reshape(3, -1)
+    ref, _, _ = op.pcg(b, fixed_iters=it)
+    err = rel_l2(got, field3(ref, dim))
+    print(f"pcg {n}: {it} iterations, {err:.2e}", flush=True)
+    assert err <= 1e-10
