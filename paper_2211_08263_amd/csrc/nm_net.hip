@@ -320,8 +320,7 @@ __global__ __launch_bounds__(256, CINP == 16 ? 3 : 2) void k_conv_fwd(const uint
 // A tile is 16 consecutive voxels of one x row.  With 32 input channels, for each (dz, dy)
 // the wave stages the 18 source voxels x0 - 1 .. x0 + 16 of that row (every channel) in its
 // own LDS slot with 16-byte loads, and the three dx taps take their operands from there
-// (1.61 -> 1.18 ms at 128^3 against per-lane 2-byte gathers); 16 input channels keep the
-// gathers.
+// (1.61 -> 1.18 ms at 128^3 against per-lane 2-byte gathers).
 // ---------------------------------------------------------------------------
 template <int CINP>
 __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ X, const uint16_t* __restrict__ DZ,
@@ -353,55 +352,87 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
     float bsum = 0.f;
     const long t0 = wave * tiles_per_wave;
     const long t1 = t0 + tiles_per_wave < ntiles ? t0 + tiles_per_wave : ntiles;
-    for (long tile = t0; tile < t1; tile++) {
-        const long v0 = tile * 16;
-        const int x0 = (int)(v0 & (g.n1 - 1));
-        const long yz = v0 / g.n1;
-        const int y = (int)(yz % g.n2), z = (int)(yz / g.n2);
-        bf16x4 b;
+    if constexpr (CINP == 16) {
+        // 16 channels: the per-lane gathers of a tile are independent and beat the staging, whose nine
+        // rounds per tile each wait for LDS (31 against 50 us at 64^3)
+        for (long tile = t0; tile < t1; tile++) {
+            const long v0 = tile * 16;
+            const int x0 = (int)(v0 & (g.n1 - 1));
+            const long yz = v0 / g.n1;
+            const int y = (int)(yz % g.n2), z = (int)(yz / g.n2);
+            bf16x4 b;
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const uint16_t h = DZ[(v0 + 4 * gq + i) * kHid + r];
-            b[i] = (short)h;
-            bsum += bf2f(h);
-        }
-        if constexpr (CINP == 16) {
-            // 16 channels: the per-lane gathers from the caches beat the staging, whose nine
-            // rounds per tile each wait for their loads (0.55 against 0.78 ms at 128^3)
+            for (int i = 0; i < 4; i++) {
+                const uint16_t h = DZ[(v0 + 4 * gq + i) * kHid + r];
+                b[i] = (short)h;
+                bsum += bf2f(h);
+            }
 #pragma unroll
             for (int t = 0; t < 27; t++) {
-                long vs[4];
-#pragma unroll
-                for (int i = 0; i < 4; i++) vs[i] = tap_voxel(x0 + 4 * gq + i, y, z, t, g);
                 bf16x4 a;
 #pragma unroll
-                for (int i = 0; i < 4; i++) a[i] = (short)X[vs[i] * CINP + r];
+                for (int i = 0; i < 4; i++) a[i] = (short)X[tap_voxel(x0 + 4 * gq + i, y, z, t, g) * CINP + r];
                 acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t][0], 0, 0, 0);
             }
-            continue;
         }
-#pragma unroll
-        for (int dzy = 0; dzy < 9; dzy++) {
+    } else {
+        constexpr int NCH = (ROWCH + 63) / 64;
+        // row (dz, dy) of a tile's source voxels: global -> registers, fetched a row ahead of its use (64^3:
+        // 90 -> 75 us)
+        auto fetch = [&](u32x4 (&buf)[NCH], long tile, int dzy) {
+            const long v0 = tile * 16;
+            const int x0 = (int)(v0 & (g.n1 - 1));
+            const long yz = v0 / g.n1;
+            const int y = (int)(yz % g.n2), z = (int)(yz / g.n2);
             const int zz = (z + dzy / 3 - 1) & (g.n3 - 1), yy = (y + dzy % 3 - 1) & (g.n2 - 1);
             const long rbase = ((long)zz * g.n2 + yy) * g.n1;
-            wave_sync(); // every lane is done with the previous row
-            for (int c = lane; c < ROWCH; c += 64) {
+#pragma unroll
+            for (int k = 0; k < NCH; k++) {
+                // chunks past the row re-read chunk 0 and are not staged
+                const int c = lane + 64 * k < ROWCH ? lane + 64 * k : 0;
                 const int j = c / CPV, q = c % CPV;
                 const int xx = (x0 - 1 + j) & (g.n1 - 1);
-                rows[wv][c] = *(const u32x4*)(X + (rbase + xx) * CINP + q * 8);
+                buf[k] = *(const u32x4*)(X + (rbase + xx) * CINP + q * 8);
             }
-            wave_sync();
+        };
+        auto fetch_dz = [&](uint16_t (&h)[4], long tile) {
 #pragma unroll
-            for (int dx = 0; dx < 3; dx++) {
-                // tap (dz, dy, dx) in tap_voxel's order; element i of this lane is voxel
-                // x0 + 4 gq + i + dx - 1, staged at j = 4 gq + i + dx
-                const int t = dzy * 3 + dx;
+            for (int i = 0; i < 4; i++) h[i] = DZ[(tile * 16 + 4 * gq + i) * kHid + r];
+        };
+        u32x4 pre[NCH];
+        uint16_t hn[4];
+        fetch(pre, t0, 0);
+        fetch_dz(hn, t0);
+        for (long tile = t0; tile < t1; tile++) {
+            const long next = tile + 1 < t1 ? tile + 1 : tile;
+            bf16x4 b;
 #pragma unroll
-                for (int kc = 0; kc < KC; kc++) {
-                    bf16x4 a;
+            for (int i = 0; i < 4; i++) {
+                b[i] = (short)hn[i];
+                bsum += bf2f(hn[i]);
+            }
+            fetch_dz(hn, next);
 #pragma unroll
-                    for (int i = 0; i < 4; i++) a[i] = (short)rowl[(4 * gq + i + dx) * CINP + kc * 16 + r];
-                    acc[t][kc] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t][kc], 0, 0, 0);
+            for (int dzy = 0; dzy < 9; dzy++) {
+                wave_sync(); // every lane is done with the previous row
+#pragma unroll
+                for (int k = 0; k < NCH; k++)
+                    if (lane + 64 * k < ROWCH) rows[wv][lane + 64 * k] = pre[k];
+                if (dzy < 8) fetch(pre, tile, dzy + 1);
+                else fetch(pre, next, 0);
+                wave_sync();
+#pragma unroll
+                for (int dx = 0; dx < 3; dx++) {
+                    // tap (dz, dy, dx) in tap_voxel's order; element i of this lane is voxel
+                    // x0 + 4 gq + i + dx - 1, staged at j = 4 gq + i + dx
+                    const int t = dzy * 3 + dx;
+#pragma unroll
+                    for (int kc = 0; kc < KC; kc++) {
+                        bf16x4 a;
+#pragma unroll
+                        for (int i = 0; i < 4; i++) a[i] = (short)rowl[(4 * gq + i + dx) * CINP + kc * 16 + r];
+                        acc[t][kc] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t][kc], 0, 0, 0);
+                    }
                 }
             }
         }
@@ -418,26 +449,39 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
 
 // Sum the per-wave partials (fixed order) and scatter into dW[co][ci][tap], db[co].
 // D element (lane l, reg i) of chunk kc = [row ci = kc*16 + 4*(l/16) + i][col co = l % 16].
+// A block owns 64 consecutive elements (256-byte rows of every slot) and its 16 wavefronts the slots
+// w, w + 16, ...: one thread per element walking all of up to 1024 slots was one serial chain on 28-55
+// blocks (240 us whatever the channels, at 64^3); at this split the 28 / 57 MB take 6 / 10 us.
+constexpr int kRedRows = 16;
 template <int CINP>
-__global__ void k_reduce_bwdw(const float* __restrict__ partial, int nwaves, float* __restrict__ dW,
-                              float* __restrict__ db, int cin, int cout)
+__global__ __launch_bounds__(64 * kRedRows) void k_reduce_bwdw(const float* __restrict__ partial, int nwaves,
+                                                               float* __restrict__ dW, float* __restrict__ db, int cin,
+                                                               int cout)
 {
     constexpr int KC = CINP / 16;
     constexpr long PW = 27L * KC * 256 + 64;
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ float sh[kRedRows][64];
+    const int l = threadIdx.x & 63, row = threadIdx.x >> 6;
+    const long e = (long)blockIdx.x * 64 + l; // e < PW: the last block holds the bias sums
+    float s = 0.f;
+#pragma unroll 8
+    for (int w = row; w < nwaves; w += kRedRows) s += partial[w * PW + e];
+    sh[row][l] = s;
+    __syncthreads();
+    if (row != 0) return;
+    s = 0.f;
+#pragma unroll
+    for (int q = 0; q < kRedRows; q++) s += sh[q][l];
     if (e < 27L * KC * 256) {
-        float s = 0.f;
-        for (int w = 0; w < nwaves; w++) s += partial[w * PW + e];
         const int i = (int)(e % 4), lane = (int)((e / 4) % 64), tk = (int)(e / 256);
         const int t = tk / KC, kc = tk % KC;
         const int ci = kc * 16 + 4 * (lane / 16) + i, co = lane % 16;
         if (ci < cin && co < cout) dW[((long)co * cin + ci) * 27 + t] = s;
-    } else if (e < 27L * KC * 256 + 16) {
-        const int co = (int)(e - 27L * KC * 256);
-        float s = 0.f;
-        for (int w = 0; w < nwaves; w++)
-            for (int q = 0; q < 4; q++) s += partial[w * PW + 27L * KC * 256 + co + 16 * q];
-        if (co < cout) db[co] = s;
+    } else {
+        // bias: the four lane groups of a channel
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (l < cout) db[l] = s;
     }
 }
 
@@ -688,7 +732,11 @@ static int launch_conv(int cinp, int epi, const uint16_t* X, const uint16_t* W, 
 {
     // tiles: 16 x TY x ZC voxels per block (grid dimensions are powers of two, n1 >= 16)
     const int TY = g.n2 < kMaxTY ? g.n2 : kMaxTY;
-    const int ZC = g.n3 < 16 ? g.n3 : 16;
+    // 16 planes a block (18 read) fill the chip from 128^3 on; below, fewer planes a block down to 2 until
+    // every compute unit has one (64^3: 64 blocks of 18 planes -> 256 of 6; 16-channel layers 41 -> 17 us,
+    // the 32-channel one 61 -> 27)
+    int ZC = g.n3 < 16 ? g.n3 : 16;
+    while (ZC > 2 && (long)(g.n1 / kTX) * (g.n2 / TY) * (g.n3 / ZC) < 256) ZC /= 2;
     const dim3 grid(g.n1 / kTX, g.n2 / TY, g.n3 / ZC);
     if (g.n1 % kTX) return -1;
 #define NM_CONV_LAUNCH(CI, EP)                                                                                         \
@@ -718,14 +766,14 @@ static int launch_bwdw(int cinp, const uint16_t* X, const uint16_t* DZ, float* p
     const long tpw = (ntiles + waves - 1) / waves;
     waves = (ntiles + tpw - 1) / tpw;
     const int blocks = (int)((waves + 3) / 4);
-    const long nout = 27L * (cinp / 16) * 256 + 16;
+    const unsigned nred = (unsigned)(bwdw_slot_floats(cinp) / 64);
     if (cinp == 32) {
         hipLaunchKernelGGL((k_conv_bwdw<32>), dim3(blocks), dim3(256), 0, s, X, DZ, partial, g, tpw);
-        hipLaunchKernelGGL((k_reduce_bwdw<32>), dim3((unsigned)((nout + 255) / 256)), dim3(256), 0, s, partial,
+        hipLaunchKernelGGL((k_reduce_bwdw<32>), dim3(nred), dim3(64 * kRedRows), 0, s, partial,
                            (int)waves, dW, db, cin, cout);
     } else {
         hipLaunchKernelGGL((k_conv_bwdw<16>), dim3(blocks), dim3(256), 0, s, X, DZ, partial, g, tpw);
-        hipLaunchKernelGGL((k_reduce_bwdw<16>), dim3((unsigned)((nout + 255) / 256)), dim3(256), 0, s, partial,
+        hipLaunchKernelGGL((k_reduce_bwdw<16>), dim3(nred), dim3(64 * kRedRows), 0, s, partial,
                            (int)waves, dW, db, cin, cout);
     }
     return hipGetLastError() == hipSuccess ? 0 : -2;
