@@ -28,6 +28,9 @@ using namespace nm;
 #define NM_PAD_COMP 1040
 #endif
 
+// Work buffers of the passes: components of S and of S2 (see PassArgs), allocated together.
+constexpr int kWorkS = 5, kWork = 8;
+
 struct nm_ctx {
     // problem
     int dim = 3, n1 = 0, n2 = 0, n3 = 0, nph = 0;
@@ -87,7 +90,7 @@ struct nm_ctx {
     int* singdev = nullptr;        // set by the factorization on a zero pivot
     int green_sweeps = 0, green_inner = 0; // mixed-precision Green route: running totals
     // several unit-force solves at once (Green route preprocessing): fields [b][3][N] and
-    // spectra [b][6 cs] of up to mnb solves, their partial sums and scalar blocks
+    // work buffers [b][8 cs] of up to mnb solves, their partial sums and scalar blocks
     int mnb = 0;
     double *mX = nullptr, *mR = nullptr, *mP = nullptr, *mQ = nullptr, *mU = nullptr, *mB = nullptr;
     double2 *mS = nullptr, *mS2 = nullptr;
@@ -704,8 +707,8 @@ int green_batch_size(nm_ctx* c)
     return nb < 2 ? 1 : nb;
 }
 
-// Buffers of nb fields side by side in one precision: real fields [b][3][N], spectra
-// [b][6 cs], per-field device scalars.
+// Buffers of nb fields side by side in one precision: real fields [b][3][N], work
+// buffers [b][8 cs], per-field device scalars.
 template <typename T> struct MultiBufs {
     T *x, *r, *p, *q;
     cx_t<T>*S, *S2;
@@ -718,7 +721,7 @@ Layout multi_layout(nm_ctx* c, int nb)
     l.stop = nullptr;
     l.nb = nb;
     l.bf = 3 * c->lay.ns;
-    l.bs = 6 * c->lay.cs;
+    l.bs = kWork * c->lay.cs;
     return l;
 }
 
@@ -896,12 +899,12 @@ int build_green(nm_ctx* c, const double* G_in)
                                       xprecond_blocks<double>(c->lay), xprecond_blocks<float>(c->lay)});
             for (double** f : {&c->mX, &c->mR, &c->mP, &c->mQ, &c->mB}) CHK(dalloc(c, f, nb * n));
             CHK(dalloc(c, &c->mU, 3 * (size_t)nb));
-            CHK(dalloc(c, &c->mS, nb * 6 * cs));
-            CHK(dalloc(c, &c->mS2, nb * 6 * cs));
+            CHK(dalloc(c, &c->mS, nb * kWork * cs));
+            c->mS2 = c->mS + kWorkS * cs;
             if (mixed) {
                 for (float** f : {&c->mD32, &c->mR32, &c->mP32, &c->mQ32}) CHK(dalloc(c, f, nb * n));
-                CHK(dalloc(c, &c->mS32, nb * 6 * cs));
-                CHK(dalloc(c, &c->mS2_32, nb * 6 * cs));
+                CHK(dalloc(c, &c->mS32, nb * kWork * cs));
+                c->mS2_32 = c->mS32 + kWorkS * cs;
             }
             CHK(dalloc(c, &c->mpa, (size_t)nb * npa));
             CHK(dalloc(c, &c->mpb, (size_t)nb * npb));
@@ -931,9 +934,9 @@ int build_green(nm_ctx* c, const double* G_in)
         for (double** f : {&c->mX, &c->mR, &c->mP, &c->mQ, &c->mB, &c->mU, &c->mpa, &c->mpb, &c->mscal}) dfree(c, f);
         for (float** f : {&c->mD32, &c->mR32, &c->mP32, &c->mQ32}) dfree(c, f);
         dfree(c, &c->mS);
-        dfree(c, &c->mS2);
         dfree(c, &c->mS32);
-        dfree(c, &c->mS2_32);
+        c->mS2 = nullptr;
+        c->mS2_32 = nullptr;
         (void)hipHostFree(c->mhscal);
         c->mhscal = nullptr;
         c->mnb = 0;
@@ -1317,15 +1320,15 @@ static int init_impl(nm_ctx* c, const nm_problem* pb, const nm_options* op)
         CHK(dalloc(c, f64[k], n));
         LCHK(c, launch_fill<double>(*f64[k], 0.0, n, s));
     }
-    CHK(dalloc(c, &c->spec64, 6 * c->lay.cs));
-    CHK(dalloc(c, &c->spec64b, 6 * c->lay.cs));
+    CHK(dalloc(c, &c->spec64, kWork * c->lay.cs));
+    c->spec64b = c->spec64 + kWorkS * c->lay.cs;
     if (c->route == NM_ROUTE_GREEN && !c->explicit_scheme) {
         CHK(dalloc(c, &c->uf, n));
         LCHK(c, launch_fill<double>(c->uf, 0.0, n, s));
     }
     if (!c->explicit_scheme) {
-        CHK(dalloc(c, &c->spec32, 6 * c->lay.cs));
-        CHK(dalloc(c, &c->spec32b, 6 * c->lay.cs));
+        CHK(dalloc(c, &c->spec32, kWork * c->lay.cs));
+        c->spec32b = c->spec32 + kWorkS * c->lay.cs;
     }
     if (c->explicit_scheme || c->route == NM_ROUTE_GREEN) {
         CHK(dalloc(c, &c->Fdev, c->dim * std::max<long>(c->ng, 1)));

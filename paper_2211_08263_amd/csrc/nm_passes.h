@@ -79,8 +79,9 @@ enum YEndMode { YE_OUT = 0, YE_UPDATE = 1, YE_EXPLICIT = 2 };
 
 struct PassArgs {
     Layout lay;
-    void* S = nullptr;         // work buffer (6 components): derivatives, then stresses
-    void* S2 = nullptr;        // work buffer: preconditioner spectrum (0..2), inertia and divergence Q (3..5)
+    void* S = nullptr;         // work buffer (5 components): derivatives, then stresses
+    void* S2 = nullptr;        // work buffer (3 components): the preconditioner's spectrum between its first
+                               // pass and YS_PCG, Q (inertia and divergence) between the stress pass and the last
     void* u = nullptr;         // YS_APPLY: field (in); YS_EXPLICIT: displacement (in/out)
     void* p = nullptr;         // YS_PCG: search direction (in/out); z and x passes: the field derived
     void* x = nullptr;         // YS_PCG: iterate (in/out)

@@ -147,12 +147,29 @@ __device__ __forceinline__ void carry_reduce(const Carry& c, int field)
     }
 }
 
-// Copy the twiddle table of length L into LDS (block-cooperative; the caller
-// synchronizes the block before use).
-template <int L, typename V> __device__ __forceinline__ void stage_twiddles(V* dst, const V* __restrict__ tw)
-{
-    for (int i = threadIdx.x; i < L; i += blockDim.x) dst[i] = tw[tw_offset(L) + i];
-}
+// The twiddle table of length L on its way to LDS: fetched to registers first thing in a kernel, so
+// that the fetch overlaps the check of the stop flag and the operands' loads, and stored behind
+// them (the caller synchronizes the block before use).
+template <int L, int BLK, typename V> struct TwStage {
+    static constexpr int N = (L + BLK - 1) / BLK;
+    V r[N];
+    __device__ __forceinline__ void fetch(const V* __restrict__ tw)
+    {
+#pragma unroll
+        for (int k = 0; k < N; k++) {
+            const int i = (int)threadIdx.x + k * BLK;
+            r[k] = tw[tw_offset(L) + (i < L ? i : 0)];
+        }
+    }
+    __device__ __forceinline__ void store(V* dst) const
+    {
+#pragma unroll
+        for (int k = 0; k < N; k++) {
+            const int i = (int)threadIdx.x + k * BLK;
+            if (i < L) dst[i] = r[k];
+        }
+    }
+};
 
 // Frequency (times 1/n, the round trip's normalization) of the bins of one axis.
 struct AxisFreq {
@@ -269,14 +286,22 @@ template <typename T> __device__ __forceinline__ int col_tile(int blk, int ntile
 {
     return sizeof(T) == 4 ? blk / 3 : blk % ntiles;
 }
-#define NM_COL_LDS(L)                                                                                                  \
+// Prologue of a column kernel: the twiddles' fetch, the stop flag ...
+#define NM_COL_BEGIN(L)                                                                                                \
     __shared__ V lds[ColShape<T, L>::G > 1 ? ColShape<T, L>::BLK * ColShape<T, L>::R : 1];                             \
     __shared__ V tws[L];                                                                                               \
-    if constexpr (ColShape<T, L>::G > 1) stage_twiddles<L>(tws, tw);
-// the same with the axis frequencies, published to the block
-#define NM_COL_LDS_FREQ(L)                                                                                             \
-    NM_COL_LDS(L)                                                                                                      \
+    TwStage<L, ColShape<T, L>::BLK, V> tst;                                                                            \
+    if constexpr (ColShape<T, L>::G > 1) tst.fetch(tw);                                                                \
+    if (stopped(a.lay.stop)) return;
+// ... and, behind the operands' loads, the tables published to the block.
+#define NM_COL_TABLES(L)                                                                                               \
+    if constexpr (ColShape<T, L>::G > 1) tst.store(tws);
+#define NM_COL_READY(L)                                                                                                \
+    NM_COL_TABLES(L)                                                                                                   \
+    __syncthreads();
+#define NM_COL_READY_FREQ(L)                                                                                           \
     __shared__ T frs[L];                                                                                               \
+    NM_COL_TABLES(L)                                                                                                   \
     stage_freq<L>(frs, f);                                                                                             \
     __syncthreads();
 
@@ -284,10 +309,9 @@ template <typename T, int L, int MODE>
 __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_ystart(PassArgs a, Cols g, AxisFreq f, int ntiles,
                                                                   const cx_t<T>* __restrict__ tw)
 {
-    if (stopped(a.lay.stop)) return;
     using V = cx_t<T>;
     constexpr int R = ColShape<T, L>::R, NT = NM_NT(YS, T);
-    NM_COL_LDS_FREQ(L)
+    NM_COL_BEGIN(L)
     const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
     const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
     const long fo = (long)fld * a.lay.bf + j * a.lay.ns;
@@ -296,6 +320,8 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
     V v[R];
     if constexpr (MODE == YS_APPLY) {
         c.template ld<NT>((const V*)a.u + fo, v);
+        NM_COL_READY_FREQ(L)
+        c.deriv(v, lds, tws, frs);
     } else if constexpr (MODE == YS_EXPLICIT) {
         const T dt = (T)a.dt, h2 = (T)(0.5 * a.dt * a.dt);
         V vo[R], ao[R];
@@ -306,6 +332,8 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
         for (int m = 0; m < R; m++)
             v[m] = V{v[m].x + dt * vo[m].x + h2 * ao[m].x, v[m].y + dt * vo[m].y + h2 * ao[m].y};
         c.template st<NT>((V*)a.u + fo, v);
+        NM_COL_READY_FREQ(L)
+        c.deriv(v, lds, tws, frs);
     } else {
         const double* sc = a.scal + (long)fld * S_COUNT;
         const bool first = sc[S_FIRST] != 0.0;
@@ -324,6 +352,7 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
 #pragma unroll
             for (int m = 0; m < R; m++) po[m] = V{0, 0};
         }
+        NM_COL_READY_FREQ(L)
         c.template fft<+1>(v, lds, tws);
         if (a.mask) c.masked(a.mask, v);
         if (!first) {
@@ -335,8 +364,8 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
             for (int m = 0; m < R; m++) v[m] = V{0, 0};
         }
         c.template st<NT>((V*)a.p + fo, v);
+        c.deriv(v, lds, tws, frs);
     }
-    c.deriv(v, lds, tws, frs);
     c.template st<NT>(dst, v);
 }
 
@@ -344,10 +373,9 @@ template <typename T, int L>
 __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_zstrain(PassArgs a, Cols g, AxisFreq f, int ntiles,
                                                                    const cx_t<T>* __restrict__ tw)
 {
-    if (stopped(a.lay.stop)) return;
     using V = cx_t<T>;
     constexpr int R = ColShape<T, L>::R, NT = NM_NT(ZS, T);
-    NM_COL_LDS_FREQ(L)
+    NM_COL_BEGIN(L)
     const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
     const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
     V* const S = (V*)a.S + (long)fld * a.lay.bs;
@@ -355,6 +383,7 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
     V v[R], w[R];
     c.template ld<NT>((const V*)a.p + (long)fld * a.lay.bf + j * a.lay.ns, v);
     if (j == 1) c.template ld<NT>(dst, w); // D_y p_3
+    NM_COL_READY_FREQ(L)
     c.deriv(v, lds, tws, frs);
     if (j == 1) {
         // g23 = D_z p_2 + D_y p_3
@@ -368,9 +397,9 @@ template <typename T, int L>
 __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_zdiv(PassArgs a, Cols g, AxisFreq f, int ntiles,
                                                                 const cx_t<T>* __restrict__ tw)
 {
-    if (stopped(a.lay.stop)) return;
     using V = cx_t<T>;
     constexpr int R = ColShape<T, L>::R, NT = NM_NT(ZD, T);
+    NM_COL_BEGIN(L)
     const int fld = blockIdx.z;
     int blk = blockIdx.x;
     if (a.carry.action != RED_NONE) {
@@ -380,15 +409,15 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
         }
         blk--;
     }
-    NM_COL_LDS_FREQ(L)
     const int j = col_comp<T>(blk, ntiles);
     const ColTile<T, L> c(g, col_tile<T>(blk, ntiles));
     // sigma_31, sigma_32, sigma_33
     const V* src = (const V*)a.S + (long)fld * a.lay.bs + (j == 0 ? 3 : j == 1 ? 2 : 4) * a.lay.cs;
-    V* const Q = (V*)a.S2 + (long)fld * a.lay.bs + (3 + j) * a.lay.cs;
+    V* const Q = (V*)a.S2 + (long)fld * a.lay.bs + j * a.lay.cs;
     V v[R], w[R];
     c.template ld<NT>(src, v);
     c.template ld<NT>(Q, w);
+    NM_COL_READY_FREQ(L)
     c.deriv(v, lds, tws, frs);
     const T cd = (T)-a.bdt2;
 #pragma unroll
@@ -400,20 +429,20 @@ template <typename T, int L, int MODE>
 __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_yend(PassArgs a, Cols g, AxisFreq f, int ntiles,
                                                                 const cx_t<T>* __restrict__ tw)
 {
-    if (stopped(a.lay.stop)) return;
     using V = cx_t<T>;
     constexpr int R = ColShape<T, L>::R, NT = NM_NT(YE, T);
-    NM_COL_LDS_FREQ(L)
+    NM_COL_BEGIN(L)
     const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
     const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
     const long fo = (long)fld * a.lay.bf + j * a.lay.ns;
     // sigma_21, sigma_22, sigma_23
     const V* src = (const V*)a.S + (long)fld * a.lay.bs + j * a.lay.cs;
-    const V* Q = (const V*)a.S2 + (long)fld * a.lay.bs + (3 + j) * a.lay.cs;
+    const V* Q = (const V*)a.S2 + (long)fld * a.lay.bs + j * a.lay.cs;
     const bool zero_comp = a.lay.dim == 2 && j == 2;
     V v[R], w[R];
     c.template ld<NT>(src, v);
     c.template ld<NT>(Q, w);
+    NM_COL_READY_FREQ(L)
     c.deriv(v, lds, tws, frs);
     const T cd = (T)-a.bdt2;
 #pragma unroll
@@ -479,9 +508,9 @@ template <typename T, int L, int DIR>
 __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_colfft(ColFft a, Cols g, int ntiles,
                                                                   const cx_t<T>* __restrict__ tw)
 {
-    if (stopped(a.lay.stop)) return;
     using V = cx_t<T>;
     constexpr int R = ColShape<T, L>::R, NT = NM_NT(CF, T);
+    NM_COL_BEGIN(L)
     const int fld = blockIdx.z;
     int blk = blockIdx.x;
     if (a.carry.action != RED_NONE) {
@@ -491,12 +520,11 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
         }
         blk--;
     }
-    NM_COL_LDS(L)
-    __syncthreads();
     const int j = col_comp<T>(blk, ntiles);
     const ColTile<T, L> c(g, col_tile<T>(blk, ntiles));
     V v[R];
     c.template ld<NT>((const V*)a.src + (long)fld * a.sb + j * a.sc, v);
+    NM_COL_READY(L)
     c.template fft<DIR>(v, lds, tws);
     if constexpr (DIR > 0) {
         if (a.mask) c.masked(a.mask, v);
@@ -544,7 +572,6 @@ constexpr int kXR = 4; // elements per thread of a pair of x lines in the stress
 template <typename T, int N1>
 __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? kXStressWaves64 : kXStressWaves32) void k_xstress(PassArgs a, AxisFreq f, int npairs, const cx_t<T>* __restrict__ tw)
 {
-    if (stopped(a.lay.stop)) return;
     using V = cx_t<T>;
     constexpr int R = kXR, G = N1 / R, LPB = kBlock / G, NT = NM_NT(XS, T);
     constexpr int EARLY = sizeof(T) == 8 ? 0 : 3; // strains fetched ahead of the first transform
@@ -553,9 +580,9 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? kXStressWaves64 : kXStress
     __shared__ V lds[3 * AREA];
     __shared__ V tws[N1];
     __shared__ T frs[N1];
-    stage_twiddles<N1>(tws, tw);
-    stage_freq<N1>(frs, f);
-    __syncthreads();
+    TwStage<N1, kBlock, V> tst;
+    tst.fetch(tw);
+    if (stopped(a.lay.stop)) return;
     const int ll = threadIdx.x / G, t = threadIdx.x % G, fld = blockIdx.z;
     const int pr = blockIdx.x * LPB + ll;
     const bool valid = pr < npairs;
@@ -564,7 +591,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? kXStressWaves64 : kXStress
     const LineAddr<AREA> addr{ll * LP};
     const T* const p = (const T*)((const V*)a.p + (long)fld * a.lay.bf);
     T* const S = (T*)((V*)a.S + (long)fld * a.lay.bs);
-    T* const Q = (T*)((V*)a.S2 + (long)fld * a.lay.bs + 3 * a.lay.cs);
+    T* const Q = (T*)((V*)a.S2 + (long)fld * a.lay.bs);
     const long ps = 2 * a.lay.ns, cs = 2 * a.lay.cs;
     const bool has_z = a.lay.n3 > 1;
     // the lane's byte offset, hidden from the optimizer at each use: otherwise it keeps one 64-bit
@@ -599,6 +626,9 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? kXStressWaves64 : kXStress
 #pragma unroll
     for (int m = 0; m < R; m++)
         ph[m] = (uint32_t)a.phase[base + m * G] | ((uint32_t)a.phase[base + m * G + N1] << 16);
+    tst.store(tws);
+    stage_freq<N1>(frs, f);
+    __syncthreads();
     auto deriv3 = [&](V (&v)[3][R], auto between) {
         group_fft<N1, R, -1, WAVE, FFT_PLAIN, 3>(v, t, lds, addr, tws);
         between();
@@ -745,14 +775,17 @@ __global__ __launch_bounds__((XPShape<T, N1>::BLK), sizeof(T) == 8 ? kXPrecondWa
                                                                     int nfull, const cx_t<T>* __restrict__ tw,
                                                                     double* __restrict__ partials)
 {
-    if (stopped(lay.stop)) return;
     using V = cx_t<T>;
     using Sh = XPShape<T, N1>;
     constexpr int R = Sh::R, G = Sh::G, LPB = Sh::BLK / G, M = N1 / 2, NT = NM_NT(XP, T);
     constexpr int LP = line_elems(N1), AREA = LPB * LP;
     __shared__ V lds[AREA];
     __shared__ V tws[N1];
-    stage_twiddles<N1>(tws, tw);
+    if (stopped(lay.stop)) return;
+    // (tables ahead of the operands here: held over their store, the operands spill in FP64)
+    TwStage<N1, Sh::BLK, V> tst;
+    tst.fetch(tw);
+    tst.store(tws);
     __syncthreads();
     const int ll = threadIdx.x / G, t = threadIdx.x % G, fld = blockIdx.z;
     const int ln = blockIdx.x * LPB + ll;
