@@ -28,7 +28,7 @@ using namespace nm;
 #define NM_PAD_COMP 1040
 #endif
 
-// Work buffers of the passes: components of S and of S2 (see PassArgs), allocated together.
+// Work buffers of the passes: components of S, and of S and S2 together (see PassArgs).
 constexpr int kWorkS = 5, kWork = 8;
 
 struct nm_ctx {
@@ -1320,15 +1320,15 @@ static int init_impl(nm_ctx* c, const nm_problem* pb, const nm_options* op)
         CHK(dalloc(c, f64[k], n));
         LCHK(c, launch_fill<double>(*f64[k], 0.0, n, s));
     }
-    CHK(dalloc(c, &c->spec64, kWork * c->lay.cs));
-    c->spec64b = c->spec64 + kWorkS * c->lay.cs;
+    CHK(dalloc(c, &c->spec64, kWorkS * c->lay.cs));
+    CHK(dalloc(c, &c->spec64b, (kWork - kWorkS) * c->lay.cs));
     if (c->route == NM_ROUTE_GREEN && !c->explicit_scheme) {
         CHK(dalloc(c, &c->uf, n));
         LCHK(c, launch_fill<double>(c->uf, 0.0, n, s));
     }
     if (!c->explicit_scheme) {
-        CHK(dalloc(c, &c->spec32, kWork * c->lay.cs));
-        c->spec32b = c->spec32 + kWorkS * c->lay.cs;
+        CHK(dalloc(c, &c->spec32, kWorkS * c->lay.cs));
+        CHK(dalloc(c, &c->spec32b, (kWork - kWorkS) * c->lay.cs));
     }
     if (c->explicit_scheme || c->route == NM_ROUTE_GREEN) {
         CHK(dalloc(c, &c->Fdev, c->dim * std::max<long>(c->ng, 1)));

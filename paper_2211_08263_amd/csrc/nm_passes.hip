@@ -207,7 +207,9 @@ struct Cols {
 };
 
 template <typename T, int L> struct ColShape {
-    static constexpr int R = L <= 16 ? L : (L <= 64 ? 8 : 16);
+    // (128-long columns in FP64: radix 16 takes 67 KB of LDS, two blocks per compute unit and 1.5 rounds of
+    // blocks at 128^3; radix 8 half of that: PCG iteration 279 -> 273 us)
+    static constexpr int R = L <= 16 ? L : (L <= (sizeof(T) == 8 ? 128 : 64) ? 8 : 16);
     static constexpr int G = L / R;
     static constexpr int BLK = (L == 512 && sizeof(T) == 4) ? 512 : 256;
     static constexpr int W = sizeof(T) == 8 ? kColWaves64 : kColWaves32; // wavefronts per SIMD
@@ -331,8 +333,8 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
 #pragma unroll
         for (int m = 0; m < R; m++)
             v[m] = V{v[m].x + dt * vo[m].x + h2 * ao[m].x, v[m].y + dt * vo[m].y + h2 * ao[m].y};
-        c.template st<NT>((V*)a.u + fo, v);
         NM_COL_READY_FREQ(L)
+        c.template st<NT>((V*)a.u + fo, v);
         c.deriv(v, lds, tws, frs);
     } else {
         const double* sc = a.scal + (long)fld * S_COUNT;
@@ -565,22 +567,31 @@ template <int NT, typename T> __device__ __forceinline__ void st_s(T* p, T v)
 
 constexpr int kXR = 4; // elements per thread of a pair of x lines in the stress pass
 
+// Threads per block of the x passes.  On small grids a wavefront (two where a line spans two) per
+// block: the passes are then one chain of instructions per wavefront, in which four wavefronts on one
+// compute unit wait for each other's memory and LDS instructions while other units stand idle.  From
+// two blocks of 256 per compute unit on, 256 threads share the staging of the tables.  FP64 PCG
+// iteration with 256 threads and with these: 64^3 73.9 / 67.4 us, 32^3 56.5 / 48.1, 512x8x8 64.8 / 54.6,
+// 64^2 42.3 / 36.5.
+constexpr int kXSmallBlocks = 512;
+template <int N1, int R> constexpr int x_small_block() { return N1 / R > 64 ? N1 / R : 64; }
+
 // The stress pass: 16 fields and the grain ids, 256^3: 0.217 ms in FP32 (5.1 TB/s), 0.458 in FP64
 // (4.8); the x pass it replaces moved 12 fields in 0.20 and 0.36 ms.  HBM bounds it in FP32, and in FP64
 // the registers too (two wavefronts per SIMD).  A group of N1 / 4 lanes holds the rows (y, y + 1) of one z plane as a complex
 // line of N1 points, in all three components at once (one synchronisation per stage for the three).
-template <typename T, int N1>
-__global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? kXStressWaves64 : kXStressWaves32) void k_xstress(PassArgs a, AxisFreq f, int npairs, const cx_t<T>* __restrict__ tw)
+template <typename T, int N1, int BLK>
+__global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXStressWaves64 : kXStressWaves32) void k_xstress(PassArgs a, AxisFreq f, int npairs, const cx_t<T>* __restrict__ tw)
 {
     using V = cx_t<T>;
-    constexpr int R = kXR, G = N1 / R, LPB = kBlock / G, NT = NM_NT(XS, T);
+    constexpr int R = kXR, G = N1 / R, LPB = BLK / G, NT = NM_NT(XS, T);
     constexpr int EARLY = sizeof(T) == 8 ? 0 : 3; // strains fetched ahead of the first transform
     constexpr bool WAVE = G <= 64;
     constexpr int LP = line_elems(N1), AREA = LPB * LP;
     __shared__ V lds[3 * AREA];
     __shared__ V tws[N1];
     __shared__ T frs[N1];
-    TwStage<N1, kBlock, V> tst;
+    TwStage<N1, BLK, V> tst;
     tst.fetch(tw);
     if (stopped(a.lay.stop)) return;
     const int ll = threadIdx.x / G, t = threadIdx.x % G, fld = blockIdx.z;
@@ -766,24 +777,23 @@ template <typename T> static PrecondParams<T> precond_params(const SpecParams& s
 
 template <typename T, int N1> struct XPShape {
     static constexpr int R = 8, G = N1 / R;
-    static constexpr int BLK = 256;
 };
 
-template <typename T, int N1>
-__global__ __launch_bounds__((XPShape<T, N1>::BLK), sizeof(T) == 8 ? kXPrecondWaves64 : kXPrecondWaves32) void k_xprecond(PrecondParams<T> sp, Layout lay, const cx_t<T>* __restrict__ src,
+template <typename T, int N1, int BLK>
+__global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXPrecondWaves64 : kXPrecondWaves32) void k_xprecond(PrecondParams<T> sp, Layout lay, const cx_t<T>* __restrict__ src,
                                                                     long sc, long sb, cx_t<T>* __restrict__ dst, int nlines,
                                                                     int nfull, const cx_t<T>* __restrict__ tw,
                                                                     double* __restrict__ partials)
 {
     using V = cx_t<T>;
     using Sh = XPShape<T, N1>;
-    constexpr int R = Sh::R, G = Sh::G, LPB = Sh::BLK / G, M = N1 / 2, NT = NM_NT(XP, T);
+    constexpr int R = Sh::R, G = Sh::G, LPB = BLK / G, M = N1 / 2, NT = NM_NT(XP, T);
     constexpr int LP = line_elems(N1), AREA = LPB * LP;
     __shared__ V lds[AREA];
     __shared__ V tws[N1];
     if (stopped(lay.stop)) return;
     // (tables ahead of the operands here: held over their store, the operands spill in FP64)
-    TwStage<N1, Sh::BLK, V> tst;
+    TwStage<N1, BLK, V> tst;
     tst.fetch(tw);
     tst.store(tws);
     __syncthreads();
@@ -1014,18 +1024,36 @@ template <typename T> int launch_colfft(const ColFft& f, const void* tw, hipStre
     return ok();
 }
 
+// Blocks of an x pass over `lines` groups of n1 / R lanes, and their threads (see kXSmallBlocks).
+static int x_blocks(int n1, int R, int lines, int* threads)
+{
+    const int G = n1 / R, small = G > 64 ? G : 64;
+    int blk = kBlock, nb = (lines + blk / G - 1) / (blk / G);
+    if (nb < kXSmallBlocks) {
+        blk = small;
+        nb = (lines + blk / G - 1) / (blk / G);
+    }
+    *threads = blk;
+    return nb;
+}
+
 template <typename T> int xstress_blocks(const Layout& l)
 {
-    const int lpb = kBlock / (l.n1 / kXR), np = l.n2 / 2 * l.n3;
-    return (np + lpb - 1) / lpb;
+    int threads;
+    return x_blocks(l.n1, kXR, l.n2 / 2 * l.n3, &threads);
 }
 
 template <typename T> int launch_xstress(const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s)
 {
     const AxisFreq f = axis_freq(sp, 0);
+    const int np = a.lay.n2 / 2 * a.lay.n3;
+    int threads;
+    const dim3 grid(x_blocks(a.lay.n1, kXR, np, &threads), 1, a.lay.nb);
     NM_SIZE_SWITCH(a.lay.n1, {
-        hipLaunchKernelGGL((k_xstress<T, NN>), dim3(xstress_blocks<T>(a.lay), 1, a.lay.nb), dim3(kBlock), 0, s, a, f,
-                           a.lay.n2 / 2 * a.lay.n3, (const cx_t<T>*)tw);
+        constexpr int SM = x_small_block<NN, kXR>();
+        if (threads == kBlock)
+            hipLaunchKernelGGL((k_xstress<T, NN, kBlock>), grid, dim3(kBlock), 0, s, a, f, np, (const cx_t<T>*)tw);
+        else hipLaunchKernelGGL((k_xstress<T, NN, SM>), grid, dim3(SM), 0, s, a, f, np, (const cx_t<T>*)tw);
     })
     return ok();
 }
@@ -1039,28 +1067,26 @@ static int mirror_rows(const Layout& l, int* full)
 
 template <typename T> int xprecond_blocks(const Layout& l)
 {
-    int nb = 0, full;
-    const int rows = mirror_rows(l, &full);
-    auto count = [&]() -> int {
-        NM_SIZE_SWITCH(l.n1, {
-            constexpr int LPB = XPShape<T, NN>::BLK / XPShape<T, NN>::G;
-            nb = (rows + LPB - 1) / LPB;
-        })
-        return 0;
-    };
-    count();
-    return nb;
+    int full, threads;
+    return x_blocks(l.n1, XPShape<T, 8>::R, mirror_rows(l, &full), &threads);
 }
 
 template <typename T>
 int launch_xprecond(const SpecParams& sp, const Layout& lay, const void* src, long sc, long sb, void* S2, const void* tw,
                     hipStream_t s, double* partials)
 {
-    int full;
+    int full, threads;
     const int rows = mirror_rows(lay, &full);
+    const dim3 grid(x_blocks(lay.n1, XPShape<T, 8>::R, rows, &threads), 1, lay.nb);
+    const PrecondParams<T> pp = precond_params<T>(sp);
     NM_SIZE_SWITCH(lay.n1, {
-        hipLaunchKernelGGL((k_xprecond<T, NN>), dim3(xprecond_blocks<T>(lay), 1, lay.nb), dim3(XPShape<T, NN>::BLK), 0, s,
-                           precond_params<T>(sp), lay, (const cx_t<T>*)src, sc, sb, (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials);
+        constexpr int SM = x_small_block<NN, XPShape<T, NN>::R>();
+        if (threads == kBlock)
+            hipLaunchKernelGGL((k_xprecond<T, NN, kBlock>), grid, dim3(kBlock), 0, s, pp, lay, (const cx_t<T>*)src, sc, sb,
+                               (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials);
+        else
+            hipLaunchKernelGGL((k_xprecond<T, NN, SM>), grid, dim3(SM), 0, s, pp, lay, (const cx_t<T>*)src, sc, sb,
+                               (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials);
     })
     return ok();
 }
