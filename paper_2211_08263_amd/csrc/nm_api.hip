@@ -1607,22 +1607,31 @@ static int explicit_impl(nm_ctx* c, const double* Udot, int per_point, int n_ste
     auto t0 = std::chrono::steady_clock::now();
     const double dt = c->dt;
     for (int k = 0; k < n_steps; k++) {
-        // u_n = u + dt v + dt^2/2 a, and its derivatives; (dt/2) div sigma(u_n)
-        // -> v <- v + dt/2 a + (dt/2) div sigma / rho, a <- div sigma / rho
+        // v + dt/2 a, u <- u + dt (that), and its derivatives; (dt/2) div sigma(u) then ends the step and,
+        // unless it is the batch's last, begins the next one
+        const bool last = k == n_steps - 1;
+        const double* Uk = c->ubatch + (size_t)row * k;
         PassArgs pa = pass_args<double>(c, c->u);
         pa.v = c->v;
         pa.a = c->a;
         pa.dt = dt;
         pa.bdt2 = -0.5 * dt;
-        LCHK(c, launch_ystart<double>(YS_EXPLICIT, c->sp, pa, c->tw64, s));
+        if (k == 0) LCHK(c, launch_ystart<double>(YS_EXPLICIT, c->sp, pa, c->tw64, s));
         pa.rho = nullptr; // no inertia term
         CHK(operator_middle<double>(c, pa));
         pa.rho = c->rho64;
+        if (!last) {
+            // Gamma: the prescribed velocity U lies half way between the two half steps' velocities
+            if (c->ng > 0) LCHK(c, launch_explicit_gamma_next(c->v, c->gidx, c->ng, Uk, per_point, d, c->N, s));
+            pa.mask = c->ng > 0 ? c->mask : nullptr;
+            LCHK(c, launch_yend<double>(YE_EXPLICIT_NEXT, c->sp, pa, c->tw64, s));
+            continue;
+        }
         LCHK(c, launch_yend<double>(YE_EXPLICIT, c->sp, pa, c->tw64, s));
         // Gamma: the force that gives the prescribed velocity
         if (c->ng > 0)
-            LCHK(c, launch_explicit_gamma(c->v, c->a, c->phase, c->rho64, c->gidx, c->ng, c->ubatch + (size_t)row * k,
-                                          per_point, d, c->N, dt, c->Fdev, s));
+            LCHK(c, launch_explicit_gamma(c->v, c->a, c->phase, c->rho64, c->gidx, c->ng, Uk, per_point, d, c->N, dt,
+                                          c->Fdev, s));
     }
     HIPCHK(c, hipStreamSynchronize(s));
     c->step += n_steps;

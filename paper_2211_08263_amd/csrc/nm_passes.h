@@ -65,7 +65,8 @@ struct Carry {
 
 // First pass of the operator, y columns: D_y of the three components into work components 0..2.
 //   YS_APPLY    the field u as it is
-//   YS_EXPLICIT u <- u + dt v + dt^2/2 a first (central differences, eq. Central_diff_rule)
+//   YS_EXPLICIT v <- v + dt/2 a (the velocity half a step on), u <- u + dt v first (central differences,
+//               eq. Central_diff_rule)
 //   YS_PCG      z = mask(y-inverse of Z), p = z + beta p, x += alpha p_old (p = z, x untouched while
 //               S_FIRST is set), then D_y p: the preconditioner's last pass, the direction update
 //               and the operator's first pass in one
@@ -74,15 +75,18 @@ enum YStartMode { YS_APPLY = 0, YS_EXPLICIT = 1, YS_PCG = 2 };
 //   YE_OUT      q (masked) to out
 //   YE_UPDATE   R_j -= alpha y-forward(mask q_j), R the y spectrum of the residual, with the partial
 //               sums of r.r (Parseval)
-//   YE_EXPLICIT o = q: v <- v + dt/2 a + o / rho, a <- 2 o / (dt rho)
-enum YEndMode { YE_OUT = 0, YE_UPDATE = 1, YE_EXPLICIT = 2 };
+//   YE_EXPLICIT o = q, the last step of a batch: v <- v + o / rho, a <- 2 o / (dt rho)
+//   YE_EXPLICIT_NEXT a step with a next one behind it: this step's end and the next one's YS_EXPLICIT
+//               in one, v <- v + 2 o / rho (Gamma voxels, whose v is already the next half step's: v as it
+//               is), u <- u + dt v, D_y u into work components 0..2; a is not needed in between
+enum YEndMode { YE_OUT = 0, YE_UPDATE = 1, YE_EXPLICIT = 2, YE_EXPLICIT_NEXT = 3 };
 
 struct PassArgs {
     Layout lay;
     void* S = nullptr;         // work buffer (5 components): derivatives, then stresses
     void* S2 = nullptr;        // work buffer (3 components): the preconditioner's spectrum between its first
                                // pass and YS_PCG, Q (inertia and divergence) between the stress pass and the last
-    void* u = nullptr;         // YS_APPLY: field (in); YS_EXPLICIT: displacement (in/out)
+    void* u = nullptr;         // YS_APPLY: field (in); explicit scheme: displacement (in/out)
     void* p = nullptr;         // YS_PCG: search direction (in/out); z and x passes: the field derived
     void* x = nullptr;         // YS_PCG: iterate (in/out)
     void* v = nullptr;         // explicit scheme: velocity

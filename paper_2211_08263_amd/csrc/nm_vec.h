@@ -86,6 +86,9 @@ int launch_accel0_damped(double* a, const double* q, const double* v, const uint
 // Udot: dim values (uniform) or dim*ng values (per point).
 int launch_explicit_gamma(double* v, double* a, const uint16_t* phase, const double* rho, const int64_t* gidx, long ng,
                           const double* Udot, int per_point, int dim, long N, double dt, double* F, hipStream_t s);
+// Gamma velocities between two steps of a batch: v <- 2 U - v.
+int launch_explicit_gamma_next(double* v, const int64_t* gidx, long ng, const double* Udot, int per_point, int dim,
+                               long N, hipStream_t s);
 // Partial sums of sum rho(phase) x^2 over a 3 x N field (vec_blocks(3 N) of them).
 int launch_rho_norm2(const double* x, const uint16_t* phase, const double* rho, long N, double* partials,
                      hipStream_t s);

@@ -570,6 +570,29 @@ int launch_explicit_gamma(double* v, double* a, const uint16_t* phase, const dou
     return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
+// Between two explicit steps: v holds the half step's velocity v_h = v + dt/2 a; the Gamma force that
+// makes the step's end U leaves the next half step U + (U - v_h).
+__global__ __launch_bounds__(kBlock) void k_explicit_gamma_next(double* __restrict__ v, const int64_t* __restrict__ gidx,
+                                                                long ng, const double* __restrict__ Udot,
+                                                                int per_point, int dim, long N)
+{
+    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= ng * dim) return;
+    const long p = e / dim;
+    const int j = (int)(e % dim);
+    const long i = j * N + gidx[p];
+    v[i] = 2.0 * (per_point ? Udot[dim * p + j] : Udot[j]) - v[i];
+}
+int launch_explicit_gamma_next(double* v, const int64_t* gidx, long ng, const double* Udot, int per_point, int dim,
+                               long N, hipStream_t s)
+{
+    const long n = ng * dim;
+    if (n == 0) return 0;
+    hipLaunchKernelGGL(k_explicit_gamma_next, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, v, gidx, ng,
+                       Udot, per_point, dim, N);
+    return hipGetLastError() == hipSuccess ? 0 : -2;
+}
+
 __global__ __launch_bounds__(kBlock) void k_rho_norm2(const double* __restrict__ x, const uint16_t* __restrict__ phase,
                                                      const double* __restrict__ rho, long N, long n,
                                                      double* __restrict__ partials)
