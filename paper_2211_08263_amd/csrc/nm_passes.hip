@@ -74,7 +74,13 @@
 #ifndef NM_NT_XP32
 #define NM_NT_XP32 0
 #endif
-#define NM_NT(FAM, T) (sizeof(T) == 8 ? NM_NT_##FAM##64 : NM_NT_##FAM##32)
+// Those are for grids whose fields pass through the last-level cache.  Where a solve's fields about fit it
+// (kPlainBytes), nothing streams: FP64 PCG iteration at 128^3 270.9 us with the settings above, 260.7 all
+// plain.  Blocks of small grids (see kColSmallBlocks, kXSmallBlocks) stream everything, as stores that
+// wait in the L2 are written back at the kernel's end, where nothing covers them: 64^3 66.2 us with the
+// settings above, 68.4 all plain, 59.8 all streaming (32^3: 43.1, 42.4, 43.8).
+enum Mem { MEM_PLAIN = 0, MEM_STREAM = 1 };
+#define NM_NT(FAM, T) (SMALL ? 3 : MEM == MEM_PLAIN ? 0 : sizeof(T) == 8 ? NM_NT_##FAM##64 : NM_NT_##FAM##32)
 
 namespace nm {
 
@@ -95,28 +101,36 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Block sum, valid in thread 0 (blocks of whole wavefronts).
-__device__ __forceinline__ double block_sum(double v)
+// Block sum, valid in thread 0 (blocks of BLK threads, whole wavefronts).
+template <int BLK> __device__ __forceinline__ double block_sum(double v)
 {
+    if constexpr (BLK == 64) return wave_sum(v);
     __shared__ double sh[16];
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
     double s = 0.0;
     if (threadIdx.x == 0)
-        for (int i = 0; i < (int)blockDim.x / 64; i++) s += sh[i];
+        for (int i = 0; i < BLK / 64; i++) s += sh[i];
     return s;
 }
 
 // The reduction a pass carries (see Carry): run by the first block of every field, beside the
 // pass's own blocks, so that it costs no launch of its own.
-__device__ __forceinline__ void carry_reduce(const Carry& c, int field)
+template <int BLK> __device__ __forceinline__ void carry_reduce(const Carry& c, int field)
 {
     const double* part = c.part + (long)field * c.n;
     double* scal = c.scal + (long)field * S_COUNT;
     double v = 0.0;
-    for (int i = threadIdx.x; i < c.n; i += blockDim.x) v += part[i];
-    const double s = block_sum(v);
+    constexpr int U = 8; // partials in flight per thread
+    for (int i = threadIdx.x; i < c.n; i += U * BLK) {
+        double w[U];
+#pragma unroll
+        for (int k = 0; k < U; k++) w[k] = i + k * BLK < c.n ? part[i + k * BLK] : 0.0;
+#pragma unroll
+        for (int k = 0; k < U; k++) v += w[k];
+    }
+    const double s = block_sum<BLK>(v);
     if (threadIdx.x != 0) return;
     const bool frozen = c.multi && scal[S_STOP] != 0.0;
     switch (c.action) {
@@ -181,9 +195,9 @@ struct AxisFreq {
 
 // The axis frequencies in LDS, beside the twiddles: computed per point in registers they would put a
 // branch (table or formula) and a conversion in front of every multiplication.
-template <int L, typename T> __device__ __forceinline__ void stage_freq(T* dst, const AxisFreq& f)
+template <int L, int BLK, typename T> __device__ __forceinline__ void stage_freq(T* dst, const AxisFreq& f)
 {
-    for (int i = threadIdx.x; i < L; i += blockDim.x) dst[i] = (T)f.at(i);
+    for (int i = threadIdx.x; i < L; i += BLK) dst[i] = (T)f.at(i);
 }
 
 // multiply by i s
@@ -206,19 +220,33 @@ struct Cols {
     long hi, step;
 };
 
-template <typename T, int L> struct ColShape {
+// Points per thread.
+template <typename T, int L> constexpr int col_radix()
+{
     // (128-long columns in FP64: radix 16 takes 67 KB of LDS, two blocks per compute unit and 1.5 rounds of
     // blocks at 128^3; radix 8 half of that: PCG iteration 279 -> 273 us)
-    static constexpr int R = L <= 16 ? L : (L <= (sizeof(T) == 8 ? 128 : 64) ? 8 : 16);
-    static constexpr int G = L / R;
-    static constexpr int BLK = (L == 512 && sizeof(T) == 4) ? 512 : 256;
+    return L <= 16 ? L : (L <= (sizeof(T) == 8 ? 128 : 64) ? 8 : 16);
+}
+// Threads per block, and on grids too small to give every compute unit a block of those: a wavefront, or
+// what keeps the rows of a tile eight elements wide, with every operand fetched ahead of the first
+// transform.  FP64, 32^3: operator 49.5 -> 39.5 us, PCG iteration 47.8 -> 43.1; 512x8x8 54.4 -> 51.3.
+constexpr int kColSmallBlocks = 512;
+template <typename T, int L> constexpr int col_block() { return L == 512 && sizeof(T) == 4 ? 512 : 256; }
+template <typename T, int L> constexpr int col_small_block()
+{
+    const int b = 8 * (L / col_radix<T, L>());
+    return b > 64 ? b : 64;
+}
+
+template <typename T, int L, int BLK> struct ColShape {
+    static constexpr int R = col_radix<T, L>(), G = L / R;
     static constexpr int W = sizeof(T) == 8 ? kColWaves64 : kColWaves32; // wavefronts per SIMD
     static constexpr int TX = BLK / G;
 };
 
-template <typename T, int L> struct ColTile {
+template <typename T, int L, int BLK> struct ColTile {
     using V = cx_t<T>;
-    using Sh = ColShape<T, L>;
+    using Sh = ColShape<T, L, BLK>;
     static constexpr int R = Sh::R, G = Sh::G, TX = Sh::TX;
     int t;
     bool valid;
@@ -267,14 +295,26 @@ template <typename T, int L> struct ColTile {
         for (int m = 0; m < R; m++) v[m] = iscale(v[m], fr[t + m * G]);
         fft<+1>(v, lds, tw);
     }
-    __device__ __forceinline__ void masked(const uint8_t* mask, V (&v)[R]) const
+    // the Gamma mask (null: none) of the thread's points
+    __device__ __forceinline__ void ld_mask(const uint8_t* mask, uint16_t (&k)[R]) const
+    {
+#pragma unroll
+        for (int m = 0; m < R; m++) k[m] = mask ? ((const uint16_t*)mask)[elem(m)] : (uint16_t)0;
+    }
+    __device__ __forceinline__ void masked(const uint16_t (&k)[R], V (&v)[R]) const
     {
 #pragma unroll
         for (int m = 0; m < R; m++) {
-            const uint16_t k = ((const uint16_t*)mask)[elem(m)];
-            if (k & 0x00ffu) v[m].x = 0;
-            if (k & 0xff00u) v[m].y = 0;
+            if (k[m] & 0x00ffu) v[m].x = 0;
+            if (k[m] & 0xff00u) v[m].y = 0;
         }
+    }
+    __device__ __forceinline__ void masked(const uint8_t* mask, V (&v)[R]) const
+    {
+        if (!mask) return;
+        uint16_t k[R];
+        ld_mask(mask, k);
+        masked(k, v);
     }
 };
 // Component and tile of a block: in FP32 the three components of a tile are neighbours, in FP64 one
@@ -290,32 +330,33 @@ template <typename T> __device__ __forceinline__ int col_tile(int blk, int ntile
 }
 // Prologue of a column kernel: the twiddles' fetch, the stop flag ...
 #define NM_COL_BEGIN(L)                                                                                                \
-    __shared__ V lds[ColShape<T, L>::G > 1 ? ColShape<T, L>::BLK * ColShape<T, L>::R : 1];                             \
+    [[maybe_unused]] constexpr bool SMALL = BLK < col_block<T, L>();                                                   \
+    __shared__ V lds[ColShape<T, L, BLK>::G > 1 ? BLK * ColShape<T, L, BLK>::R : 1];                             \
     __shared__ V tws[L];                                                                                               \
-    TwStage<L, ColShape<T, L>::BLK, V> tst;                                                                            \
-    if constexpr (ColShape<T, L>::G > 1) tst.fetch(tw);                                                                \
+    TwStage<L, BLK, V> tst;                                                                            \
+    if constexpr (ColShape<T, L, BLK>::G > 1) tst.fetch(tw);                                                                \
     if (stopped(a.lay.stop)) return;
 // ... and, behind the operands' loads, the tables published to the block.
 #define NM_COL_TABLES(L)                                                                                               \
-    if constexpr (ColShape<T, L>::G > 1) tst.store(tws);
+    if constexpr (ColShape<T, L, BLK>::G > 1) tst.store(tws);
 #define NM_COL_READY(L)                                                                                                \
     NM_COL_TABLES(L)                                                                                                   \
     __syncthreads();
 #define NM_COL_READY_FREQ(L)                                                                                           \
     __shared__ T frs[L];                                                                                               \
     NM_COL_TABLES(L)                                                                                                   \
-    stage_freq<L>(frs, f);                                                                                             \
+    stage_freq<L, BLK>(frs, f);                                                                                             \
     __syncthreads();
 
-template <typename T, int L, int MODE>
-__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_ystart(PassArgs a, Cols g, AxisFreq f, int ntiles,
+template <typename T, int L, int BLK, int MEM, int MODE>
+__global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_ystart(PassArgs a, Cols g, AxisFreq f, int ntiles,
                                                                   const cx_t<T>* __restrict__ tw)
 {
     using V = cx_t<T>;
-    constexpr int R = ColShape<T, L>::R, NT = NM_NT(YS, T);
     NM_COL_BEGIN(L)
+    constexpr int R = ColShape<T, L, BLK>::R, NT = NM_NT(YS, T);
     const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
-    const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
+    const ColTile<T, L, BLK> c(g, col_tile<T>(blockIdx.x, ntiles));
     const long fo = (long)fld * a.lay.bf + j * a.lay.ns;
     V* const dst = (V*)a.S + (long)fld * a.lay.bs + j * a.lay.cs;
     const bool zero_comp = a.lay.dim == 2 && j == 2;
@@ -357,9 +398,12 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
 #pragma unroll
             for (int m = 0; m < R; m++) po[m] = V{0, 0};
         }
+        uint16_t mk[R];
+        if constexpr (SMALL) c.ld_mask(a.mask, mk);
         NM_COL_READY_FREQ(L)
         c.template fft<+1>(v, lds, tws);
-        if (a.mask) c.masked(a.mask, v);
+        if constexpr (!SMALL) c.masked(a.mask, v);
+        else c.masked(mk, v);
         if (!first) {
 #pragma unroll
             for (int m = 0; m < R; m++) v[m] = V{v[m].x + beta * po[m].x, v[m].y + beta * po[m].y};
@@ -374,15 +418,15 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
     c.template st<NT>(dst, v);
 }
 
-template <typename T, int L>
-__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_zstrain(PassArgs a, Cols g, AxisFreq f, int ntiles,
+template <typename T, int L, int BLK, int MEM>
+__global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_zstrain(PassArgs a, Cols g, AxisFreq f, int ntiles,
                                                                    const cx_t<T>* __restrict__ tw)
 {
     using V = cx_t<T>;
-    constexpr int R = ColShape<T, L>::R, NT = NM_NT(ZS, T);
     NM_COL_BEGIN(L)
+    constexpr int R = ColShape<T, L, BLK>::R, NT = NM_NT(ZS, T);
     const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
-    const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
+    const ColTile<T, L, BLK> c(g, col_tile<T>(blockIdx.x, ntiles));
     V* const S = (V*)a.S + (long)fld * a.lay.bs;
     V* const dst = S + (j == 0 ? 3 : j == 1 ? 2 : 4) * a.lay.cs;
     V v[R], w[R];
@@ -398,24 +442,24 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
     c.template st<NT>(dst, v);
 }
 
-template <typename T, int L>
-__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_zdiv(PassArgs a, Cols g, AxisFreq f, int ntiles,
+template <typename T, int L, int BLK, int MEM>
+__global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_zdiv(PassArgs a, Cols g, AxisFreq f, int ntiles,
                                                                 const cx_t<T>* __restrict__ tw)
 {
     using V = cx_t<T>;
-    constexpr int R = ColShape<T, L>::R, NT = NM_NT(ZD, T);
     NM_COL_BEGIN(L)
+    constexpr int R = ColShape<T, L, BLK>::R, NT = NM_NT(ZD, T);
     const int fld = blockIdx.z;
     int blk = blockIdx.x;
     if (a.carry.action != RED_NONE) {
         if (blk == 0) {
-            carry_reduce(a.carry, fld);
+            carry_reduce<BLK>(a.carry, fld);
             return;
         }
         blk--;
     }
     const int j = col_comp<T>(blk, ntiles);
-    const ColTile<T, L> c(g, col_tile<T>(blk, ntiles));
+    const ColTile<T, L, BLK> c(g, col_tile<T>(blk, ntiles));
     // sigma_31, sigma_32, sigma_33
     const V* src = (const V*)a.S + (long)fld * a.lay.bs + (j == 0 ? 3 : j == 1 ? 2 : 4) * a.lay.cs;
     V* const Q = (V*)a.S2 + (long)fld * a.lay.bs + j * a.lay.cs;
@@ -430,15 +474,15 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
     c.template st<NT>(Q, v);
 }
 
-template <typename T, int L, int MODE>
-__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_yend(PassArgs a, Cols g, AxisFreq f, int ntiles,
+template <typename T, int L, int BLK, int MEM, int MODE>
+__global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_yend(PassArgs a, Cols g, AxisFreq f, int ntiles,
                                                                 const cx_t<T>* __restrict__ tw)
 {
     using V = cx_t<T>;
-    constexpr int R = ColShape<T, L>::R, NT = NM_NT(YE, T);
     NM_COL_BEGIN(L)
+    constexpr int R = ColShape<T, L, BLK>::R, NT = NM_NT(YE, T);
     const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
-    const ColTile<T, L> c(g, col_tile<T>(blockIdx.x, ntiles));
+    const ColTile<T, L, BLK> c(g, col_tile<T>(blockIdx.x, ntiles));
     const long fo = (long)fld * a.lay.bf + j * a.lay.ns;
     // sigma_21, sigma_22, sigma_23
     V* const src = (V*)a.S + (long)fld * a.lay.bs + j * a.lay.cs;
@@ -447,6 +491,10 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
     V v[R], w[R];
     c.template ld<NT>(src, v);
     c.template ld<NT>(Q, w);
+    V ro[R];
+    uint16_t mk[R];
+    if constexpr (SMALL && MODE == YE_UPDATE) c.template ld<NT>((const V*)a.r + fo, ro);
+    if constexpr (SMALL && (MODE == YE_UPDATE || MODE == YE_OUT)) c.ld_mask(a.mask, mk);
     NM_COL_READY_FREQ(L)
     c.deriv(v, lds, tws, frs);
     const T cd = (T)-a.bdt2;
@@ -466,7 +514,7 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
         constexpr int H = NEXT ? 2 : R < 4 ? R : 4;
 #pragma unroll
         for (int q = 0; q < R; q += H) {
-            ColTile<T, L> e = c; // the offset hidden: kept per array and chunk, the addresses would spill
+            ColTile<T, L, BLK> e = c; // the offset hidden: kept per array and chunk, the addresses would spill
             asm("" : "+v"(e.lane));
             V vo[H], ao[H]; // ao: acceleration, or the next displacement
             uint32_t ph[H];
@@ -515,52 +563,56 @@ __global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_
             c.template st<NT>(src, v);
         }
     } else {
-        if (a.mask) c.masked(a.mask, v);
+        if constexpr (!SMALL) c.masked(a.mask, v);
+        else c.masked(mk, v);
         if constexpr (MODE == YE_OUT) {
             c.template st<NT>((V*)a.out + fo, v);
         } else {
             // the residual's y spectrum R -= alpha y-forward(q); r.r by Parseval
             V* const rp = (V*)a.r + fo;
             const T alpha = (T)a.scal[(long)fld * S_COUNT + S_ALPHA];
-            c.template ld<NT>(rp, w);
+            if constexpr (!SMALL) c.template ld<NT>(rp, ro);
             c.template fft<-1>(v, lds, tws);
             double part = 0.0;
 #pragma unroll
             for (int m = 0; m < R; m++) {
-                w[m] = V{w[m].x - alpha * v[m].x, w[m].y - alpha * v[m].y};
-                part += (double)w[m].x * (double)w[m].x + (double)w[m].y * (double)w[m].y;
+                ro[m] = V{ro[m].x - alpha * v[m].x, ro[m].y - alpha * v[m].y};
+                part += (double)ro[m].x * (double)ro[m].x + (double)ro[m].y * (double)ro[m].y;
             }
-            c.template st<NT>(rp, w);
-            const double s = block_sum(c.valid ? part : 0.0);
-            if (threadIdx.x == 0) a.partials[(long)fld * gridDim.x + blockIdx.x] = s * f.inv_n;
+            c.template st<NT>(rp, ro);
+            const double s = block_sum<BLK>(c.valid ? part : 0.0);
+            if (threadIdx.x == 0) a.partials[(long)fld * (3 * ntiles) + blockIdx.x] = s * f.inv_n;
         }
     }
 }
 
-template <typename T, int L, int DIR>
-__global__ __launch_bounds__((ColShape<T, L>::BLK), (ColShape<T, L>::W)) void k_colfft(ColFft a, Cols g, int ntiles,
+template <typename T, int L, int BLK, int MEM, int DIR>
+__global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_colfft(ColFft a, Cols g, int ntiles,
                                                                   const cx_t<T>* __restrict__ tw)
 {
     using V = cx_t<T>;
-    constexpr int R = ColShape<T, L>::R, NT = NM_NT(CF, T);
     NM_COL_BEGIN(L)
+    constexpr int R = ColShape<T, L, BLK>::R, NT = NM_NT(CF, T);
     const int fld = blockIdx.z;
     int blk = blockIdx.x;
     if (a.carry.action != RED_NONE) {
         if (blk == 0) {
-            carry_reduce(a.carry, fld);
+            carry_reduce<BLK>(a.carry, fld);
             return;
         }
         blk--;
     }
     const int j = col_comp<T>(blk, ntiles);
-    const ColTile<T, L> c(g, col_tile<T>(blk, ntiles));
+    const ColTile<T, L, BLK> c(g, col_tile<T>(blk, ntiles));
     V v[R];
+    uint16_t mk[R];
     c.template ld<NT>((const V*)a.src + (long)fld * a.sb + j * a.sc, v);
+    if constexpr (SMALL && DIR > 0) c.ld_mask(a.mask, mk);
     NM_COL_READY(L)
     c.template fft<DIR>(v, lds, tws);
     if constexpr (DIR > 0) {
-        if (a.mask) c.masked(a.mask, v);
+        if constexpr (!SMALL) c.masked(a.mask, v);
+        else c.masked(mk, v);
         if (a.zero3 && j == 2) {
 #pragma unroll
             for (int m = 0; m < R; m++) v[m] = V{0, 0};
@@ -606,17 +658,25 @@ constexpr int kXR = 4; // elements per thread of a pair of x lines in the stress
 // 64^2 42.3 / 36.5.
 constexpr int kXSmallBlocks = 512;
 template <int N1, int R> constexpr int x_small_block() { return N1 / R > 64 ? N1 / R : 64; }
+// (small blocks are alone on their SIMD: all its registers, and every operand fetched at once)
+template <typename T, int BLK> constexpr int x_waves(int w64, int w32)
+{
+    return BLK != kBlock ? 1 : sizeof(T) == 8 ? w64 : w32;
+}
 
 // The stress pass: 16 fields and the grain ids, 256^3: 0.217 ms in FP32 (5.1 TB/s), 0.458 in FP64
 // (4.8); the x pass it replaces moved 12 fields in 0.20 and 0.36 ms.  HBM bounds it in FP32, and in FP64
 // the registers too (two wavefronts per SIMD).  A group of N1 / 4 lanes holds the rows (y, y + 1) of one z plane as a complex
 // line of N1 points, in all three components at once (one synchronisation per stage for the three).
-template <typename T, int N1, int BLK>
-__global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXStressWaves64 : kXStressWaves32) void k_xstress(PassArgs a, AxisFreq f, int npairs, const cx_t<T>* __restrict__ tw)
+template <typename T, int N1, int BLK, int MEM>
+__global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWaves32)))
+    void k_xstress(PassArgs a, AxisFreq f, int npairs, const cx_t<T>* __restrict__ tw)
 {
     using V = cx_t<T>;
+    constexpr bool SMALL = BLK != kBlock;
     constexpr int R = kXR, G = N1 / R, LPB = BLK / G, NT = NM_NT(XS, T);
-    constexpr int EARLY = sizeof(T) == 8 ? 0 : 3; // strains fetched ahead of the first transform
+    // strains fetched ahead of the first transform
+    constexpr int EARLY = SMALL ? 5 : sizeof(T) == 8 ? 0 : 3;
     constexpr bool WAVE = G <= 64;
     constexpr int LP = line_elems(N1), AREA = LPB * LP;
     __shared__ V lds[3 * AREA];
@@ -663,13 +723,27 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXStressWaves64 : kXStressWav
 #pragma unroll
     for (int j = 0; j < 3; j++) ld(p + j * ps, d[j]);
 #pragma unroll
-    for (int c = 0; c < EARLY; c++) ld(S + c * cs, w[c]);
+    for (int c = 0; c < EARLY; c++) {
+        if (c < 3 || has_z) {
+            ld(S + c * cs, w[c]);
+        } else {
+#pragma unroll
+            for (int m = 0; m < R; m++) w[c][m] = V{0, 0};
+        }
+    }
+    V po[3][R];
+    if constexpr (SMALL) {
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+#pragma unroll
+            for (int m = 0; m < R; m++) po[j][m] = d[j][m];
+    }
     uint32_t ph[R];
 #pragma unroll
     for (int m = 0; m < R; m++)
         ph[m] = (uint32_t)a.phase[base + m * G] | ((uint32_t)a.phase[base + m * G + N1] << 16);
     tst.store(tws);
-    stage_freq<N1>(frs, f);
+    stage_freq<N1, BLK>(frs, f);
     __syncthreads();
     auto deriv3 = [&](V (&v)[3][R], auto between) {
         group_fft<N1, R, -1, WAVE, FFT_PLAIN, 3>(v, t, lds, addr, tws);
@@ -729,10 +803,11 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXStressWaves64 : kXStressWav
     }
     // p again for the inertia term: its second read comes from the caches, and held over the
     // transforms it would cost a wave of occupancy
-    V po[3][R];
     deriv3(d, [&]() {
+        if constexpr (!SMALL) {
 #pragma unroll
-        for (int j = 0; j < 3; j++) ld(p + j * ps, po[j]);
+            for (int j = 0; j < 3; j++) ld(p + j * ps, po[j]);
+        }
     });
     T rh[R][2];
 #pragma unroll
@@ -756,8 +831,8 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXStressWaves64 : kXStressWav
         if (valid) st(Q + j * cs, d[j]);
     }
     if (a.partials) {
-        const double s = block_sum(valid ? part : 0.0);
-        if (threadIdx.x == 0) a.partials[(long)fld * gridDim.x + blockIdx.x] = s;
+        const double s = block_sum<BLK>(valid ? part : 0.0);
+        if (threadIdx.x == 0) a.partials[(long)fld * ((npairs + LPB - 1) / LPB) + blockIdx.x] = s;
     }
 }
 
@@ -810,24 +885,29 @@ template <typename T, int N1> struct XPShape {
     static constexpr int R = 8, G = N1 / R;
 };
 
-template <typename T, int N1, int BLK>
-__global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXPrecondWaves64 : kXPrecondWaves32) void k_xprecond(PrecondParams<T> sp, Layout lay, const cx_t<T>* __restrict__ src,
+template <typename T, int N1, int BLK, int MEM>
+__global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXPrecondWaves64, kXPrecondWaves32)))
+    void k_xprecond(PrecondParams<T> sp, Layout lay, const cx_t<T>* __restrict__ src,
                                                                     long sc, long sb, cx_t<T>* __restrict__ dst, int nlines,
                                                                     int nfull, const cx_t<T>* __restrict__ tw,
                                                                     double* __restrict__ partials)
 {
     using V = cx_t<T>;
     using Sh = XPShape<T, N1>;
+    constexpr bool SMALL = BLK != kBlock;
     constexpr int R = Sh::R, G = Sh::G, LPB = BLK / G, M = N1 / 2, NT = NM_NT(XP, T);
     constexpr int LP = line_elems(N1), AREA = LPB * LP;
     __shared__ V lds[AREA];
     __shared__ V tws[N1];
-    if (stopped(lay.stop)) return;
-    // (tables ahead of the operands here: held over their store, the operands spill in FP64)
     TwStage<N1, BLK, V> tst;
-    tst.fetch(tw);
-    tst.store(tws);
-    __syncthreads();
+    if constexpr (SMALL) tst.fetch(tw);
+    if (stopped(lay.stop)) return;
+    if constexpr (!SMALL) {
+        // (tables ahead of the operands here: held over their store, the operands spill in FP64)
+        tst.fetch(tw);
+        tst.store(tws);
+        __syncthreads();
+    }
     const int ll = threadIdx.x / G, t = threadIdx.x % G, fld = blockIdx.z;
     const int ln = blockIdx.x * LPB + ll;
     const bool valid = ln < nlines;
@@ -857,6 +937,10 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXPrecondWaves64 : kXPrecondW
                 ca[j][m] = ld_nt<NT>(in + j * sc + (o1 + m * G));
                 cb[j][m] = ld_nt<NT>(in + j * sc + (o2 + m * G));
             }
+        if constexpr (SMALL) {
+            tst.store(tws);
+            __syncthreads();
+        }
 #pragma unroll
         for (int j = 0; j < 3; j++)
 #pragma unroll
@@ -936,8 +1020,8 @@ __global__ __launch_bounds__(BLK, sizeof(T) == 8 ? kXPrecondWaves64 : kXPrecondW
     }
     if (partials) {
         // a row and its mirror contribute the same
-        const double tot = block_sum(valid ? (self ? 1.0 : 2.0) * part : 0.0);
-        if (threadIdx.x == 0) partials[(long)fld * gridDim.x + blockIdx.x] = tot;
+        const double tot = block_sum<BLK>(valid ? (self ? 1.0 : 2.0) * part : 0.0);
+        if (threadIdx.x == 0) partials[(long)fld * ((nlines + LPB - 1) / LPB) + blockIdx.x] = tot;
     }
 }
 
@@ -967,27 +1051,53 @@ static AxisFreq axis_freq(const SpecParams& sp, int axis)
     const int n[3] = {sp.n1, sp.n2, sp.n3}, off[3] = {0, sp.n1, sp.n1 + sp.n2};
     return AxisFreq{sp.mfreq ? sp.mfreq + off[axis] : nullptr, k[axis], in[axis], n[axis]};
 }
-template <typename T, int L> static int col_tiles(const Cols& g)
+// Whether the fields of a conjugate-gradient iteration (work buffers 8, direction, iterate, residual) about fit
+// the 256 MB last-level cache.
+constexpr long kPlainBytes = 320L << 20; // (FP64 iteration plain / streaming: 285 MB 260.7 / 270.9 us, 1.14 GB 1045 / 945)
+template <typename T> static bool plain_memory(const Layout& l)
 {
-    constexpr int TX = ColShape<T, L>::TX;
-    return (g.ncols + TX - 1) / TX;
+    return 17 * l.ns * l.nb * (long)sizeof(cx_t<T>) <= kPlainBytes;
+}
+
+// fn(threads per block and memory setting as constants, tiles) for the columns g of L points.
+template <typename T, int L, typename F> static void col_shape(const Layout& l, const Cols& g, F&& fn)
+{
+    using Plain = std::integral_constant<int, MEM_PLAIN>;
+    using Stream = std::integral_constant<int, MEM_STREAM>;
+    constexpr int G = L / col_radix<T, L>(), BIG = col_block<T, L>(), SM = col_small_block<T, L>();
+    auto tiles = [&](int blk) { return (g.ncols + blk / G - 1) / (blk / G); };
+    if constexpr (SM < BIG) {
+        if (3 * tiles(BIG) < kColSmallBlocks) {
+            fn(std::integral_constant<int, SM>{}, Stream{}, tiles(SM));
+            return;
+        }
+    }
+    if (plain_memory<T>(l)) fn(std::integral_constant<int, BIG>{}, Plain{}, tiles(BIG));
+    else fn(std::integral_constant<int, BIG>{}, Stream{}, tiles(BIG));
 }
 static int ok() { return hipGetLastError() == hipSuccess ? 0 : -2; }
+
+// Launch K<T, NN, BLK, MEM, ...> on the columns of `n` points; extra: blocks ahead of the tiles'.
+#define NM_COL_LAUNCH(n, l, g, extra, s, K, ...)                                                                       \
+    NM_SIZE_SWITCH(n, (col_shape<T, NN>(l, g, [&](auto blk, auto mem, int nt) {                                        \
+                       constexpr int BLK = decltype(blk)::value, MEM = decltype(mem)::value;                           \
+                       hipLaunchKernelGGL(K, dim3(3 * nt + (extra), 1, (l).nb), dim3(BLK), 0, s, __VA_ARGS__, nt,      \
+                                          (const cx_t<T>*)tw);                                                         \
+                   })))
 
 template <typename T> int launch_ystart(int mode, const SpecParams& sp, const PassArgs& a, const void* tw, hipStream_t s)
 {
     const Cols g = y_cols(a.lay);
     const AxisFreq f = axis_freq(sp, 1);
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    NM_SIZE_SWITCH(a.lay.n2, {
-        const int nt = col_tiles<T, NN>(g);
-        const dim3 grid(3 * nt, 1, a.lay.nb), block(ColShape<T, NN>::BLK);
-        if (mode == YS_APPLY) hipLaunchKernelGGL((k_ystart<T, NN, YS_APPLY>), grid, block, 0, s, a, g, f, nt, t);
-        else if (mode == YS_PCG) hipLaunchKernelGGL((k_ystart<T, NN, YS_PCG>), grid, block, 0, s, a, g, f, nt, t);
-        else if constexpr (sizeof(T) == 8) // the explicit scheme runs in FP64
-            hipLaunchKernelGGL((k_ystart<T, NN, YS_EXPLICIT>), grid, block, 0, s, a, g, f, nt, t);
-        else return -1;
-    })
+    if (mode == YS_APPLY) {
+        NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_ystart<T, NN, BLK, MEM, YS_APPLY>), a, g, f)
+    } else if (mode == YS_PCG) {
+        NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_ystart<T, NN, BLK, MEM, YS_PCG>), a, g, f)
+    } else if constexpr (sizeof(T) == 8) { // the explicit scheme runs in FP64
+        NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_ystart<T, NN, BLK, MEM, YS_EXPLICIT>), a, g, f)
+    } else {
+        return -1;
+    }
     return ok();
 }
 
@@ -995,11 +1105,7 @@ template <typename T> int launch_zstrain(const SpecParams& sp, const PassArgs& a
 {
     const Cols g = z_cols(a.lay);
     const AxisFreq f = axis_freq(sp, 2);
-    NM_SIZE_SWITCH(a.lay.n3, {
-        const int nt = col_tiles<T, NN>(g);
-        hipLaunchKernelGGL((k_zstrain<T, NN>), dim3(3 * nt, 1, a.lay.nb), dim3(ColShape<T, NN>::BLK), 0, s, a, g, f, nt,
-                           (const cx_t<T>*)tw);
-    })
+    NM_COL_LAUNCH(a.lay.n3, a.lay, g, 0, s, (k_zstrain<T, NN, BLK, MEM>), a, g, f)
     return ok();
 }
 
@@ -1007,11 +1113,7 @@ template <typename T> int launch_zdiv(const SpecParams& sp, const PassArgs& a, c
 {
     const Cols g = z_cols(a.lay);
     const AxisFreq f = axis_freq(sp, 2);
-    NM_SIZE_SWITCH(a.lay.n3, {
-        const int nt = col_tiles<T, NN>(g);
-        hipLaunchKernelGGL((k_zdiv<T, NN>), dim3(3 * nt + (a.carry.action != RED_NONE), 1, a.lay.nb),
-                           dim3(ColShape<T, NN>::BLK), 0, s, a, g, f, nt, (const cx_t<T>*)tw);
-    })
+    NM_COL_LAUNCH(a.lay.n3, a.lay, g, a.carry.action != RED_NONE, s, (k_zdiv<T, NN, BLK, MEM>), a, g, f)
     return ok();
 }
 
@@ -1019,7 +1121,7 @@ template <typename T> int yend_blocks(const Layout& l)
 {
     int nb = 0;
     auto count = [&]() -> int {
-        NM_SIZE_SWITCH(l.n2, nb = 3 * col_tiles<T, NN>(y_cols(l));)
+        NM_SIZE_SWITCH(l.n2, (col_shape<T, NN>(l, y_cols(l), [&](auto, auto, int nt) { nb = 3 * nt; })))
         return 0;
     };
     count();
@@ -1030,30 +1132,31 @@ template <typename T> int launch_yend(int mode, const SpecParams& sp, const Pass
 {
     const Cols g = y_cols(a.lay);
     const AxisFreq f = axis_freq(sp, 1);
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    NM_SIZE_SWITCH(a.lay.n2, {
-        const int nt = col_tiles<T, NN>(g);
-        const dim3 grid(3 * nt, 1, a.lay.nb), block(ColShape<T, NN>::BLK);
-        if (mode == YE_OUT) hipLaunchKernelGGL((k_yend<T, NN, YE_OUT>), grid, block, 0, s, a, g, f, nt, t);
-        else if (mode == YE_UPDATE) hipLaunchKernelGGL((k_yend<T, NN, YE_UPDATE>), grid, block, 0, s, a, g, f, nt, t);
-        else if constexpr (sizeof(T) == 8) {
-            if (mode == YE_EXPLICIT) hipLaunchKernelGGL((k_yend<T, NN, YE_EXPLICIT>), grid, block, 0, s, a, g, f, nt, t);
-            else hipLaunchKernelGGL((k_yend<T, NN, YE_EXPLICIT_NEXT>), grid, block, 0, s, a, g, f, nt, t);
-        } else return -1;
-    })
+    if (mode == YE_OUT) {
+        NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_yend<T, NN, BLK, MEM, YE_OUT>), a, g, f)
+    } else if (mode == YE_UPDATE) {
+        NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_yend<T, NN, BLK, MEM, YE_UPDATE>), a, g, f)
+    } else if constexpr (sizeof(T) == 8) {
+        if (mode == YE_EXPLICIT) {
+            NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_yend<T, NN, BLK, MEM, YE_EXPLICIT>), a, g, f)
+        } else {
+            NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_yend<T, NN, BLK, MEM, YE_EXPLICIT_NEXT>), a, g, f)
+        }
+    } else {
+        return -1;
+    }
     return ok();
 }
 
 template <typename T> int launch_colfft(const ColFft& f, const void* tw, hipStream_t s)
 {
     const Cols g = f.axis == 1 ? y_cols(f.lay) : z_cols(f.lay);
-    const cx_t<T>* t = (const cx_t<T>*)tw;
-    NM_SIZE_SWITCH(f.axis == 1 ? f.lay.n2 : f.lay.n3, {
-        const int nt = col_tiles<T, NN>(g);
-        const dim3 grid(3 * nt + (f.carry.action != RED_NONE), 1, f.lay.nb), block(ColShape<T, NN>::BLK);
-        if (f.dir < 0) hipLaunchKernelGGL((k_colfft<T, NN, -1>), grid, block, 0, s, f, g, nt, t);
-        else hipLaunchKernelGGL((k_colfft<T, NN, +1>), grid, block, 0, s, f, g, nt, t);
-    })
+    const int n = f.axis == 1 ? f.lay.n2 : f.lay.n3, extra = f.carry.action != RED_NONE;
+    if (f.dir < 0) {
+        NM_COL_LAUNCH(n, f.lay, g, extra, s, (k_colfft<T, NN, BLK, MEM, -1>), f, g)
+    } else {
+        NM_COL_LAUNCH(n, f.lay, g, extra, s, (k_colfft<T, NN, BLK, MEM, +1>), f, g)
+    }
     return ok();
 }
 
@@ -1070,6 +1173,19 @@ static int x_blocks(int n1, int R, int lines, int* threads)
     return nb;
 }
 
+// Launch an x pass K<T, NN, BLK, MEM> of R elements per thread on `grid` blocks of `threads` threads.
+#define NM_X_LAUNCH(K, R, l, ...)                                                                                      \
+    if (threads != kBlock) {                                                                                           \
+        constexpr int BLK = x_small_block<NN, R>(), MEM = MEM_STREAM;                                                  \
+        hipLaunchKernelGGL(K, grid, dim3(BLK), 0, s, __VA_ARGS__);                                                     \
+    } else if (plain_memory<T>(l)) {                                                                                   \
+        constexpr int BLK = kBlock, MEM = MEM_PLAIN;                                                                   \
+        hipLaunchKernelGGL(K, grid, dim3(BLK), 0, s, __VA_ARGS__);                                                     \
+    } else {                                                                                                           \
+        constexpr int BLK = kBlock, MEM = MEM_STREAM;                                                                  \
+        hipLaunchKernelGGL(K, grid, dim3(BLK), 0, s, __VA_ARGS__);                                                     \
+    }
+
 template <typename T> int xstress_blocks(const Layout& l)
 {
     int threads;
@@ -1083,10 +1199,7 @@ template <typename T> int launch_xstress(const SpecParams& sp, const PassArgs& a
     int threads;
     const dim3 grid(x_blocks(a.lay.n1, kXR, np, &threads), 1, a.lay.nb);
     NM_SIZE_SWITCH(a.lay.n1, {
-        constexpr int SM = x_small_block<NN, kXR>();
-        if (threads == kBlock)
-            hipLaunchKernelGGL((k_xstress<T, NN, kBlock>), grid, dim3(kBlock), 0, s, a, f, np, (const cx_t<T>*)tw);
-        else hipLaunchKernelGGL((k_xstress<T, NN, SM>), grid, dim3(SM), 0, s, a, f, np, (const cx_t<T>*)tw);
+        NM_X_LAUNCH((k_xstress<T, NN, BLK, MEM>), kXR, a.lay, a, f, np, (const cx_t<T>*)tw);
     })
     return ok();
 }
@@ -1113,13 +1226,8 @@ int launch_xprecond(const SpecParams& sp, const Layout& lay, const void* src, lo
     const dim3 grid(x_blocks(lay.n1, XPShape<T, 8>::R, rows, &threads), 1, lay.nb);
     const PrecondParams<T> pp = precond_params<T>(sp);
     NM_SIZE_SWITCH(lay.n1, {
-        constexpr int SM = x_small_block<NN, XPShape<T, NN>::R>();
-        if (threads == kBlock)
-            hipLaunchKernelGGL((k_xprecond<T, NN, kBlock>), grid, dim3(kBlock), 0, s, pp, lay, (const cx_t<T>*)src, sc, sb,
-                               (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials);
-        else
-            hipLaunchKernelGGL((k_xprecond<T, NN, SM>), grid, dim3(SM), 0, s, pp, lay, (const cx_t<T>*)src, sc, sb,
-                               (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials);
+        NM_X_LAUNCH((k_xprecond<T, NN, BLK, MEM>), (XPShape<T, NN>::R), lay, pp, lay, (const cx_t<T>*)src, sc, sb,
+                    (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials);
     })
     return ok();
 }
