@@ -215,21 +215,19 @@ template <typename T> PassArgs pass_args(nm_ctx* c, const T* p)
 
 // The passes of q = A p between the first (which left D_y p in S) and the last: D_z, the stress
 // pass and the z part of the divergence.  partials (or null): per-block sums of p . A p; with them
-// the z part of the divergence also reduces them into the step length alpha (2D: a kernel of its
-// own), so that it is there for the last pass.
-template <typename T> int operator_middle(nm_ctx* c, PassArgs a, double* scal = nullptr, int multi = 0)
+// the z part of the divergence also reduces them into the step length alpha, so that it is there for
+// the last pass (2D: the last pass sums them itself, a.carry on return).
+template <typename T> int operator_middle(nm_ctx* c, PassArgs& a, double* scal = nullptr, int multi = 0)
 {
     hipStream_t s = c->stream;
     const void* tw = Prec<T>::tw(c);
     const int nbx = xstress_blocks<T>(a.lay);
     if (c->n3 > 1) LCHK(c, launch_zstrain<T>(c->sp, a, tw, s));
     LCHK(c, launch_xstress<T>(c->sp, a, tw, s));
+    a.carry = a.partials ? Carry{a.partials, nbx, scal, RED_ALPHA, multi} : Carry{};
     if (c->n3 > 1) {
-        if (a.partials) a.carry = Carry{a.partials, nbx, scal, RED_ALPHA, multi};
         LCHK(c, launch_zdiv<T>(c->sp, a, tw, s));
-    } else if (a.partials) {
-        if (multi) LCHK(c, launch_reduce_multi(a.partials, nbx, a.lay.nb, scal, RED_ALPHA, s));
-        else LCHK(c, launch_reduce(a.partials, nbx, scal, RED_ALPHA, 0, s, true));
+        a.carry = Carry{};
     }
     return NM_OK;
 }
@@ -237,7 +235,8 @@ template <typename T> int operator_middle(nm_ctx* c, PassArgs a, double* scal = 
 // The passes of z = M r between the y-forward and the y-inverse: src holds the y spectrum of r
 // (component stride sc, field stride sb), the y spectrum of z is left in components 0..2 of S2.
 // The z passes carry the reduction of the pass before (red: r.r of the residual update, or none)
-// and that of r . z (rz_action, from partials); in 2D they are kernels of their own.
+// and that of r . z (rz_action, from partials).  2D: the x pass carries red, and the next YS_PCG
+// sums r . z itself (rz_carry).
 template <typename T>
 int precond_middle(nm_ctx* c, const Layout& lay, const void* src, long sc, long sb, void* S2, const Carry& red,
                    double* partials, int rz_action, double* scal, int multi)
@@ -246,17 +245,9 @@ int precond_middle(nm_ctx* c, const Layout& lay, const void* src, long sc, long 
     const void* tw = Prec<T>::tw(c);
     const int nbz = xprecond_blocks<T>(lay);
     const Carry rz{partials, nbz, scal, partials ? rz_action : (int)RED_NONE, multi};
-    const bool guarded = lay.stop != nullptr;
-    auto reduce = [&](const Carry& r) -> int {
-        if (r.action == RED_NONE) return NM_OK;
-        if (multi) LCHK(c, launch_reduce_multi(r.part, r.n, lay.nb, r.scal, r.action, s));
-        else LCHK(c, launch_reduce(r.part, r.n, r.scal, r.action, 0, s, guarded));
-        return NM_OK;
-    };
     if (c->n3 == 1) {
-        CHK(reduce(red));
-        LCHK(c, launch_xprecond<T>(c->sp, lay, src, sc, sb, S2, tw, s, partials));
-        return reduce(rz);
+        LCHK(c, launch_xprecond<T>(c->sp, lay, src, sc, sb, S2, tw, s, partials, red));
+        return NM_OK;
     }
     ColFft f{};
     f.lay = lay;
@@ -270,7 +261,7 @@ int precond_middle(nm_ctx* c, const Layout& lay, const void* src, long sc, long 
     f.db = lay.bs;
     f.carry = red;
     LCHK(c, launch_colfft<T>(f, tw, s));
-    LCHK(c, launch_xprecond<T>(c->sp, lay, S2, lay.cs, lay.bs, S2, tw, s, partials));
+    LCHK(c, launch_xprecond<T>(c->sp, lay, S2, lay.cs, lay.bs, S2, tw, s, partials, Carry{}));
     f.dir = +1;
     f.src = S2;
     f.sc = lay.cs;
@@ -278,6 +269,14 @@ int precond_middle(nm_ctx* c, const Layout& lay, const void* src, long sc, long 
     f.carry = rz;
     LCHK(c, launch_colfft<T>(f, tw, s));
     return NM_OK;
+}
+
+// The reduction of r . z that YS_PCG makes before it forms the direction: in 2D, after precond_middle
+// left partials; in 3D a z pass has made it.
+template <typename T> Carry rz_carry(nm_ctx* c, const Layout& lay, double* partials, double* scal, int multi)
+{
+    if (c->n3 > 1) return Carry{};
+    return Carry{partials, xprecond_blocks<T>(lay), scal, RED_BETA, multi};
 }
 
 // The preconditioner's first pass: y-forward transform of the real field r (3 x N) in dst
@@ -441,6 +440,7 @@ int pcg(nm_ctx* c, const T* rhs, T* x, T* r, T* p, T* q, bool masked, bool x_zer
             // alpha = rz / p.q known before its last pass, which updates r -= alpha q ; r.r (iteration
             // count, stop test) ; Z = M r with r.z on the spectrum ; beta = r.z_new / r.z_old
             // (x += alpha p follows in the next p update)
+            a.carry = rz_carry<T>(c, a.lay, c->part_b, c->scal, 0);
             LCHK(c, launch_ystart<T>(YS_PCG, c->sp, a, tw, s));
             a.partials = c->part_b;
             CHK(operator_middle<T>(c, a, c->scal));
@@ -756,6 +756,7 @@ int pcg_multi_core(nm_ctx* c, int nb, const MultiBufs<T>& m, const double* thr2,
         for (int k = 0; k < 4; k++) {
             // p = z + beta p (x += alpha p_old); q = A p; alpha; r -= alpha q, r.r (stop test); z = M r,
             // r.z; beta
+            a.carry = rz_carry<T>(c, L, c->mpb, c->mscal, 1);
             LCHK(c, launch_ystart<T>(YS_PCG, c->sp, a, tw, s));
             a.partials = c->mpb;
             CHK(operator_middle<T>(c, a, c->mscal, 1));
@@ -1039,7 +1040,7 @@ template <typename T> int profile_impl(nm_ctx* c, int which, const T* in, T* out
             y1.zero3 = c->dim == 2;
             rc |= launch_colfft<T>(y0, tw, s) | mark();
             rc |= (z3 ? launch_colfft<T>(z0, tw, s) : 0) | mark();
-            rc |= launch_xprecond<T>(c->sp, lay, S2, lay.cs, 0, S2, tw, s, nullptr) | mark();
+            rc |= launch_xprecond<T>(c->sp, lay, S2, lay.cs, 0, S2, tw, s, nullptr, Carry{}) | mark();
             rc |= (z3 ? launch_colfft<T>(z1, tw, s) : 0) | mark();
             rc |= launch_colfft<T>(y1, tw, s) | mark();
         }

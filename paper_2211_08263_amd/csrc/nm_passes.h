@@ -44,6 +44,7 @@ struct Layout {
 // (S_MODE 0) or the count reaches S_LIMIT; every guarded kernel after that returns at once.
 enum ScalarSlot {
     S_ALPHA = 0, S_BETA = 1, S_FIRST = 2, S_RZ = 3, S_PQ = 4, S_RR = 5,
+    S_RZ2 = 7, // r.z of the iteration under way (2D, see PassArgs::carry)
     S_STOP = 8, S_ITER = 9, S_THR2 = 10, S_LIMIT = 11, S_MODE = 12, S_COUNT = 16
 };
 
@@ -52,7 +53,7 @@ enum ReduceAction {
     RED_NONE = -1, RED_STORE_RR = 0, RED_ALPHA = 1, RED_RZ_INIT = 2, RED_BETA = 3, RED_STORE_SLOT = 4, RED_RR_CHECK = 5
 };
 
-// A reduction carried by a column pass: its first block (one per field) sums n partials of the
+// A reduction carried by a pass: its first block (one per field) sums n partials of the
 // pass before, field b's at part + b n, into scal + b S_COUNT.  multi: a loop whose S_STOP is set
 // is frozen (alpha = beta = 0) instead of skipped.
 struct Carry {
@@ -99,8 +100,10 @@ struct PassArgs {
     const void* rho = nullptr;       // per-grain density, or null (no inertia term)
     double bdt2 = 0.0;               // the divergence is scaled by -bdt2
     double dt = 0.0;                 // explicit scheme
-    const double* scal = nullptr;    // device scalars
+    double* scal = nullptr;          // device scalars
     double* partials = nullptr;      // per-block partial sums or null
+    // z passes: the reduction they carry.  YS_PCG with RED_BETA and YE_UPDATE with RED_ALPHA (2D, where no z
+    // pass lies between): every block sums the partials for itself.
     Carry carry;
 };
 
@@ -135,9 +138,9 @@ template <typename T> int launch_yend(int mode, const SpecParams& sp, const Pass
 template <typename T> int launch_colfft(const ColFft& f, const void* tw, hipStream_t s);
 // x lines of the preconditioner on the (y, z) spectrum src (component stride sc, field stride sb),
 // result to S2 components 0..2: x-forward, (beta dt^2 K + rhobar I)^-1 / (n1 n2 n3), x-inverse;
-// partials (or null): per-block sums of r . z (Parseval).
+// partials (or null): per-block sums of r . z (Parseval); carry: a reduction on the way (2D).
 template <typename T>
 int launch_xprecond(const SpecParams& sp, const Layout& lay, const void* src, long sc, long sb, void* S2, const void* tw,
-                    hipStream_t s, double* partials);
+                    hipStream_t s, double* partials, const Carry& carry);
 
 } // namespace nm

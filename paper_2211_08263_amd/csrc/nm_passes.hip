@@ -21,7 +21,10 @@
 //   z-forward | x: x-forward, (beta dt^2 K + rhobar I)^-1, x-inverse | z-inverse,
 // and its y-inverse is the next iteration's first pass (YS_PCG).  One iteration: eight passes, 80
 // fields (eleven passes and 104 fields before).
-// In 2D (n3 == 1) the z passes drop out: D_z = 0.
+// In 2D (n3 == 1) the z passes drop out: D_z = 0.  The reductions that ride on them in 3D are then done
+// by the passes that need them, every block for itself (a few hundred partials at most), and that of
+// r.r rides on the preconditioner's x pass: four launches an iteration.  (With a launch for each of the
+// three sums, as before: FP64, 64^2, 35.3 us an iteration, 29.4 with these.)
 #include "nm_common.h"
 #include "nm_fft.h"
 #include "nm_passes.h"
@@ -112,6 +115,29 @@ template <int BLK> __device__ __forceinline__ double block_sum(double v)
     double s = 0.0;
     if (threadIdx.x == 0)
         for (int i = 0; i < BLK / 64; i++) s += sh[i];
+    return s;
+}
+
+// Sum over the block of n partials, to every thread.
+template <int BLK> __device__ __forceinline__ double block_total(const double* part, int n)
+{
+    constexpr int U = 4;
+    double v = 0.0;
+    for (int i = threadIdx.x; i < n; i += U * BLK) {
+        double w[U];
+#pragma unroll
+        for (int k = 0; k < U; k++) w[k] = i + k * BLK < n ? part[i + k * BLK] : 0.0;
+#pragma unroll
+        for (int k = 0; k < U; k++) v += w[k];
+    }
+    v = wave_sum(v);
+    if constexpr (BLK == 64) return v;
+    __shared__ double sh[BLK / 64];
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < BLK / 64; i++) s += sh[i];
     return s;
 }
 
@@ -383,7 +409,8 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_ystart(PassAr
     } else {
         const double* sc = a.scal + (long)fld * S_COUNT;
         const bool first = sc[S_FIRST] != 0.0;
-        const T beta = (T)sc[S_BETA], alpha = (T)sc[S_ALPHA];
+        T beta = (T)sc[S_BETA];
+        const T alpha = (T)sc[S_ALPHA];
         c.template ld<NT>((const V*)a.S2 + (long)fld * a.lay.bs + j * a.lay.cs, v);
         V po[R];
         if (!first) {
@@ -400,6 +427,12 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_ystart(PassAr
         }
         uint16_t mk[R];
         if constexpr (SMALL) c.ld_mask(a.mask, mk);
+        if (a.carry.action == RED_BETA) {
+            // S_RZ still holds the last iteration's r.z; YE_UPDATE moves the new one there
+            const double rz = block_total<BLK>(a.carry.part + (long)fld * a.carry.n, a.carry.n);
+            beta = (T)(a.carry.multi && sc[S_STOP] != 0.0 ? 0.0 : rz / sc[S_RZ]);
+            if (blockIdx.x == 0 && threadIdx.x == 0) a.scal[(long)fld * S_COUNT + S_RZ2] = rz;
+        }
         NM_COL_READY_FREQ(L)
         c.template fft<+1>(v, lds, tws);
         if constexpr (!SMALL) c.masked(a.mask, v);
@@ -495,6 +528,10 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_yend(PassArgs
     uint16_t mk[R];
     if constexpr (SMALL && MODE == YE_UPDATE) c.template ld<NT>((const V*)a.r + fo, ro);
     if constexpr (SMALL && (MODE == YE_UPDATE || MODE == YE_OUT)) c.ld_mask(a.mask, mk);
+    double pq = 0.0;
+    if constexpr (MODE == YE_UPDATE) {
+        if (a.carry.action == RED_ALPHA) pq = block_total<BLK>(a.carry.part + (long)fld * a.carry.n, a.carry.n);
+    }
     NM_COL_READY_FREQ(L)
     c.deriv(v, lds, tws, frs);
     const T cd = (T)-a.bdt2;
@@ -570,7 +607,20 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_yend(PassArgs
         } else {
             // the residual's y spectrum R -= alpha y-forward(q); r.r by Parseval
             V* const rp = (V*)a.r + fo;
-            const T alpha = (T)a.scal[(long)fld * S_COUNT + S_ALPHA];
+            double* const sc = a.scal + (long)fld * S_COUNT;
+            T alpha;
+            if (a.carry.action == RED_ALPHA) {
+                const double rz = sc[S_RZ2], al = a.carry.multi && sc[S_STOP] != 0.0 ? 0.0 : rz / pq;
+                alpha = (T)al;
+                if (blockIdx.x == 0 && threadIdx.x == 0) {
+                    sc[S_PQ] = pq;
+                    sc[S_ALPHA] = al;
+                    sc[S_RZ] = rz;
+                    sc[S_FIRST] = 0.0;
+                }
+            } else {
+                alpha = (T)sc[S_ALPHA];
+            }
             if constexpr (!SMALL) c.template ld<NT>(rp, ro);
             c.template fft<-1>(v, lds, tws);
             double part = 0.0;
@@ -890,7 +940,7 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXPrecondWaves64, kXPrecondWa
     void k_xprecond(PrecondParams<T> sp, Layout lay, const cx_t<T>* __restrict__ src,
                                                                     long sc, long sb, cx_t<T>* __restrict__ dst, int nlines,
                                                                     int nfull, const cx_t<T>* __restrict__ tw,
-                                                                    double* __restrict__ partials)
+                                                                    double* __restrict__ partials, Carry carry)
 {
     using V = cx_t<T>;
     using Sh = XPShape<T, N1>;
@@ -902,14 +952,23 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXPrecondWaves64, kXPrecondWa
     TwStage<N1, BLK, V> tst;
     if constexpr (SMALL) tst.fetch(tw);
     if (stopped(lay.stop)) return;
+    const int fld = blockIdx.z;
+    int blk = blockIdx.x;
+    if (carry.action != RED_NONE) {
+        if (blk == 0) {
+            carry_reduce<BLK>(carry, fld);
+            return;
+        }
+        blk--;
+    }
     if constexpr (!SMALL) {
         // (tables ahead of the operands here: held over their store, the operands spill in FP64)
         tst.fetch(tw);
         tst.store(tws);
         __syncthreads();
     }
-    const int ll = threadIdx.x / G, t = threadIdx.x % G, fld = blockIdx.z;
-    const int ln = blockIdx.x * LPB + ll;
+    const int ll = threadIdx.x / G, t = threadIdx.x % G;
+    const int ln = blk * LPB + ll;
     const bool valid = ln < nlines;
     // kz in (0, n3/2): every ky; kz = 0 and n3/2: ky <= n2/2
     int ky, kz;
@@ -1021,7 +1080,7 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXPrecondWaves64, kXPrecondWa
     if (partials) {
         // a row and its mirror contribute the same
         const double tot = block_sum<BLK>(valid ? (self ? 1.0 : 2.0) * part : 0.0);
-        if (threadIdx.x == 0) partials[(long)fld * ((nlines + LPB - 1) / LPB) + blockIdx.x] = tot;
+        if (threadIdx.x == 0) partials[(long)fld * ((nlines + LPB - 1) / LPB) + blk] = tot;
     }
 }
 
@@ -1219,15 +1278,15 @@ template <typename T> int xprecond_blocks(const Layout& l)
 
 template <typename T>
 int launch_xprecond(const SpecParams& sp, const Layout& lay, const void* src, long sc, long sb, void* S2, const void* tw,
-                    hipStream_t s, double* partials)
+                    hipStream_t s, double* partials, const Carry& carry)
 {
     int full, threads;
     const int rows = mirror_rows(lay, &full);
-    const dim3 grid(x_blocks(lay.n1, XPShape<T, 8>::R, rows, &threads), 1, lay.nb);
+    const dim3 grid(x_blocks(lay.n1, XPShape<T, 8>::R, rows, &threads) + (carry.action != RED_NONE), 1, lay.nb);
     const PrecondParams<T> pp = precond_params<T>(sp);
     NM_SIZE_SWITCH(lay.n1, {
         NM_X_LAUNCH((k_xprecond<T, NN, BLK, MEM>), (XPShape<T, NN>::R), lay, pp, lay, (const cx_t<T>*)src, sc, sb,
-                    (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials);
+                    (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials, carry);
     })
     return ok();
 }
@@ -1243,7 +1302,7 @@ int launch_xprecond(const SpecParams& sp, const Layout& lay, const void* src, lo
     template int launch_yend<T>(int, const SpecParams&, const PassArgs&, const void*, hipStream_t);                    \
     template int launch_colfft<T>(const ColFft&, const void*, hipStream_t);                                            \
     template int launch_xprecond<T>(const SpecParams&, const Layout&, const void*, long, long, void*, const void*,     \
-                                    hipStream_t, double*);
+                                    hipStream_t, double*, const Carry&);
 NM_INST(double)
 NM_INST(float)
 

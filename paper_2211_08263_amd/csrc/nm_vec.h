@@ -9,17 +9,10 @@ namespace nm {
 // x += alpha p, alpha read from the device (the deferred last update of a Krylov loop).
 template <typename T> int launch_axpy_scal(T* x, const T* p, const double* alpha, long n, hipStream_t s);
 // Arm a batched Krylov loop: clear S_STOP and S_ITER, set S_THR2, S_LIMIT, S_MODE (1: run
-// exactly `limit` iterations).
+// exactly `limit` iterations) and S_FIRST.
 int launch_loop_init(double* scal, double thr2, int limit, int fixed, hipStream_t s);
-// guarded: the kernel does nothing once scal[S_STOP] is set.  RED_RR_CHECK stores r.r,
-// counts the iteration and sets S_STOP when the loop is done (see ScalarSlot).
-int launch_reduce(const double* partials, int n, double* scal, int action, int slot, hipStream_t s,
-                  bool guarded = false);
-// The same for nb independent Krylov loops run together (one block per loop): loop b sums
-// partials [b n, (b + 1) n) into scal + b S_COUNT.  A loop whose S_STOP is set is frozen
-// instead of skipped: RED_ALPHA and RED_BETA then store zero, so that its iterate receives the
-// deferred last update once and then stays, and RED_RR_CHECK no longer counts.
-int launch_reduce_multi(const double* partials, int n, int nb, double* scal, int action, hipStream_t s);
+// Sum of n partials into scal[S_RR] (RED_STORE_RR) or scal[slot] (RED_STORE_SLOT).
+int launch_reduce(const double* partials, int n, double* scal, int action, int slot, hipStream_t s);
 
 // Number of partials written by the grid-stride kernels below.
 int vec_blocks(long n);

@@ -34,83 +34,12 @@ __device__ __forceinline__ double block_sum_v(double v)
 }
 
 // One block of 1024 threads: thread i sums partials i, i+1024, ... in order.
-__global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ part, int n, double* scal, int action,
-                                                 int slot, int guarded)
+__global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ part, int n, double* scal, int slot)
 {
-    if (guarded && scal[S_STOP] != 0.0) return;
     double v = 0.0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) v += part[i];
     const double s = block_sum_v(v);
-    if (threadIdx.x == 0) {
-        switch (action) {
-        case RED_STORE_RR: scal[S_RR] = s; break;
-        case RED_RR_CHECK: {
-            scal[S_RR] = s;
-            const double it = scal[S_ITER] + 1.0;
-            scal[S_ITER] = it;
-            const bool done = scal[S_MODE] != 0.0 ? it >= scal[S_LIMIT]
-                                                  : (s <= scal[S_THR2] || it >= scal[S_LIMIT] || !(s < 1e300));
-            if (done) scal[S_STOP] = 1.0;
-            break;
-        }
-        case RED_ALPHA:
-            scal[S_PQ] = s;
-            scal[S_ALPHA] = scal[S_RZ] / s;
-            break;
-        case RED_RZ_INIT:
-            scal[S_RZ] = s;
-            scal[S_FIRST] = 1.0;
-            break;
-        case RED_BETA:
-            scal[S_BETA] = s / scal[S_RZ];
-            scal[S_RZ] = s;
-            scal[S_FIRST] = 0.0;
-            break;
-        default: scal[slot] = s; break;
-        }
-    }
-}
-
-__global__ __launch_bounds__(1024) void k_reduce_multi(const double* __restrict__ part, int n, double* scal_all,
-                                                       int action)
-{
-    const double* pb = part + (long)blockIdx.x * n;
-    double* scal = scal_all + (long)blockIdx.x * S_COUNT;
-    double v = 0.0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) v += pb[i];
-    const double s = block_sum_v(v);
-    if (threadIdx.x == 0) {
-        const bool frozen = scal[S_STOP] != 0.0;
-        switch (action) {
-        case RED_RR_CHECK: {
-            if (frozen) break;
-            scal[S_RR] = s;
-            const double it = scal[S_ITER] + 1.0;
-            scal[S_ITER] = it;
-            if (s <= scal[S_THR2] || it >= scal[S_LIMIT] || !(s < 1e300)) scal[S_STOP] = 1.0;
-            break;
-        }
-        case RED_ALPHA:
-            scal[S_PQ] = s;
-            scal[S_ALPHA] = frozen ? 0.0 : scal[S_RZ] / s;
-            break;
-        case RED_RZ_INIT:
-            scal[S_RZ] = s;
-            scal[S_FIRST] = 1.0;
-            break;
-        case RED_BETA:
-            scal[S_BETA] = frozen ? 0.0 : s / scal[S_RZ];
-            scal[S_RZ] = s;
-            scal[S_FIRST] = 0.0;
-            break;
-        default: scal[S_RR] = s; break;
-        }
-    }
-}
-int launch_reduce_multi(const double* partials, int n, int nb, double* scal, int action, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_reduce_multi, dim3(nb), dim3(1024), 0, s, partials, n, scal, action);
-    return hipGetLastError() == hipSuccess ? 0 : -2;
+    if (threadIdx.x == 0) scal[slot] = s;
 }
 
 // x += alpha p with alpha read from the device
@@ -133,6 +62,7 @@ template int launch_axpy_scal<float>(float*, const float*, const double*, long, 
 __global__ void k_loop_init(double* scal, double thr2, double limit, double mode)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
+        scal[S_FIRST] = 1.0;
         scal[S_STOP] = 0.0;
         scal[S_ITER] = 0.0;
         scal[S_THR2] = thr2;
@@ -146,9 +76,9 @@ int launch_loop_init(double* scal, double thr2, int limit, int fixed, hipStream_
     return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
-int launch_reduce(const double* partials, int n, double* scal, int action, int slot, hipStream_t s, bool guarded)
+int launch_reduce(const double* partials, int n, double* scal, int action, int slot, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, s, partials, n, scal, action, slot, guarded ? 1 : 0);
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, s, partials, n, scal, action == RED_STORE_RR ? (int)S_RR : slot);
     return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
