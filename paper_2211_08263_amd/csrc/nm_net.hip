@@ -317,28 +317,44 @@ __global__ __launch_bounds__(256, CINP == 16 ? 3 : 2) void k_conv_fwd(const uint
 // K = voxels), bias gradient db[co] = sum_v dZ[v][co].  Each wave writes its
 // partial sums; k_reduce_partials adds them in a fixed order.
 //   partial layout per wave: [27][KC][64 lanes][4] then [64 lanes] (bias)
-// A tile is 16 consecutive voxels of one x row.  With 32 input channels, for each (dz, dy)
-// the wave stages the 18 source voxels x0 - 1 .. x0 + 16 of that row (every channel) in its
-// own LDS slot with 16-byte loads, and the three dx taps take their operands from there
-// (1.61 -> 1.18 ms at 128^3 against per-lane 2-byte gathers).
+// A tile is 16 consecutive voxels of one x row.  For each tile the wave stages the 9 x 18 source voxels
+// around it and dZ in its own LDS slot with 16-byte loads (issued a tile ahead), 16 channels of a voxel
+// in a row, and takes its operands from there with transposing reads: A[m = channel][k = voxel] wants
+// four voxels of one channel per lane, memory holds the channels of one voxel.  What is left is one
+// read and one MFMA per tap and 16 channels.  64^3: 75 -> T32 us with 32 input channels (staged row by
+// row, operands gathered from LDS by 2 bytes), 31 -> T16 with 16 (gathered by 2 bytes from memory).
 // ---------------------------------------------------------------------------
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+
+// Four rows of 16 elements each per 16 lanes: lane (gq, r) gets elements r of rows 4 gq .. 4 gq + 3, its
+// own address being that of row 4 gq + r / 4, elements 4 (r % 4) .. + 3.
+__device__ __forceinline__ bf16x4 read_rows_tr(const uint16_t* p)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4*)p);
+}
+
 template <int CINP>
 __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ X, const uint16_t* __restrict__ DZ,
                                                    float* __restrict__ partial, Grid g, long tiles_per_wave)
 {
     constexpr int KC = CINP / 16;
     constexpr long PW = 27L * KC * 256 + 64;
-    constexpr int CPV = CINP / 8;          // 16-byte chunks per voxel
-    constexpr int ROWCH = 18 * CPV;        // chunks of one staged row
-    __shared__ u32x4 rows[4][ROWCH];       // one staged row per wave of the block
+    constexpr int CPV = CINP / 8;            // 16-byte chunks per voxel
+    constexpr int ROWCH = 18 * CPV;          // chunks of one row of source voxels
+    constexpr int XCH = 9 * ROWCH;           // chunks of a tile's source voxels; 32 more hold its dZ
+    constexpr int NCH = (XCH + 32 + 63) / 64;
+    constexpr int SLOT = 162 * CINP + 256;   // [KC][9 rows][18 voxels][16 channels], then dZ [16 voxels][16]
+    static_assert(kHid == 16, "dZ rows are 16 channels wide");
+    __shared__ __align__(16) uint16_t slots[4][SLOT];
     const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const long wave = (long)blockIdx.x * (blockDim.x / 64) + wv;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long wave = (long)blockIdx.x * 4 + wv;
     const int r = lane & 15, gq = lane >> 4;
     const long ntiles = g.N / 16;
     // waves past the last tile range own no partial slot
     if (wave * tiles_per_wave >= ntiles) return;
-    const uint16_t* rowl = (const uint16_t*)rows[wv];
+    uint16_t* const slot = slots[wv];
+    const uint16_t* const tr = slot + (4 * gq + r / 4) * 16 + (r % 4) * 4;
     auto wave_sync = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -352,90 +368,57 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
     float bsum = 0.f;
     const long t0 = wave * tiles_per_wave;
     const long t1 = t0 + tiles_per_wave < ntiles ? t0 + tiles_per_wave : ntiles;
-    if constexpr (CINP == 16) {
-        // 16 channels: the per-lane gathers of a tile are independent and beat the staging, whose nine
-        // rounds per tile each wait for LDS (31 against 50 us at 64^3)
-        for (long tile = t0; tile < t1; tile++) {
-            const long v0 = tile * 16;
-            const int x0 = (int)(v0 & (g.n1 - 1));
-            const long yz = v0 / g.n1;
-            const int y = (int)(yz % g.n2), z = (int)(yz / g.n2);
-            bf16x4 b;
+    // Voxel indices as bit fields (x lowest; the sizes are powers of two): a source voxel is the tile's first
+    // plus a displacement, wrapped field by field.  x and z are added in one word with y's field empty
+    // between them, where x's carry ends, y in another.
+    const uint32_t mx = g.n1 - 1, my = (uint32_t)(g.n2 - 1) * g.n1, mz = (uint32_t)(g.n3 - 1) * g.n1 * g.n2;
+    uint32_t dxz[NCH], dy[NCH];
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint16_t h = DZ[(v0 + 4 * gq + i) * kHid + r];
-                b[i] = (short)h;
-                bsum += bf2f(h);
-            }
+    for (int k = 0; k < NCH; k++) {
+        // chunks past the source voxels re-read chunk 0 here
+        const int c = lane + 64 * k, vox = c < XCH ? c / CPV : 0, row = vox / 18, j = vox % 18;
+        dxz[k] = ((uint32_t)(g.n1 + j - 1) & mx) | ((uint32_t)(g.n3 + row / 3 - 1) * g.n1 * g.n2 & mz);
+        dy[k] = (uint32_t)(g.n2 + row % 3 - 1) * g.n1 & my;
+    }
+    const uint16_t* const Xq = X + lane % CPV * 8;
+    u32x4 pre[NCH];
+    auto fetch = [&](long tile) {
+        const uint32_t v0 = (uint32_t)(tile * 16);
 #pragma unroll
-            for (int t = 0; t < 27; t++) {
-                bf16x4 a;
-#pragma unroll
-                for (int i = 0; i < 4; i++) a[i] = (short)X[tap_voxel(x0 + 4 * gq + i, y, z, t, g) * CINP + r];
-                acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t][0], 0, 0, 0);
-            }
+        for (int k = 0; k < NCH; k++) {
+            const uint32_t v = (((v0 & (mx | mz)) + dxz[k]) & (mx | mz)) | (((v0 & my) + dy[k]) & my);
+            const uint16_t* src = Xq + (size_t)v * CINP;
+            // dZ: 32 chunks, those past them re-read its first
+            const int c = lane + 64 * k;
+            if (k == NCH - 1 && c >= XCH) src = DZ + (size_t)v0 * kHid + (c < XCH + 32 ? c - XCH : 0) * 8;
+            pre[k] = *(const u32x4*)src;
         }
-    } else {
-        constexpr int NCH = (ROWCH + 63) / 64;
-        // row (dz, dy) of a tile's source voxels: global -> registers, fetched a row ahead of its use (64^3:
-        // 90 -> 75 us)
-        auto fetch = [&](u32x4 (&buf)[NCH], long tile, int dzy) {
-            const long v0 = tile * 16;
-            const int x0 = (int)(v0 & (g.n1 - 1));
-            const long yz = v0 / g.n1;
-            const int y = (int)(yz % g.n2), z = (int)(yz / g.n2);
-            const int zz = (z + dzy / 3 - 1) & (g.n3 - 1), yy = (y + dzy % 3 - 1) & (g.n2 - 1);
-            const long rbase = ((long)zz * g.n2 + yy) * g.n1;
+    };
+    static_assert(64 * (NCH - 1) <= XCH && 64 % CPV == 0, "dZ is in the last round of chunks");
+    fetch(t0);
+    for (long tile = t0; tile < t1; tile++) {
+        wave_sync(); // every lane is done with the previous tile
 #pragma unroll
-            for (int k = 0; k < NCH; k++) {
-                // chunks past the row re-read chunk 0 and are not staged
-                const int c = lane + 64 * k < ROWCH ? lane + 64 * k : 0;
-                const int j = c / CPV, q = c % CPV;
-                const int xx = (x0 - 1 + j) & (g.n1 - 1);
-                buf[k] = *(const u32x4*)(X + (rbase + xx) * CINP + q * 8);
-            }
-        };
-        auto fetch_dz = [&](uint16_t (&h)[4], long tile) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) h[i] = DZ[(tile * 16 + 4 * gq + i) * kHid + r];
-        };
-        u32x4 pre[NCH];
-        uint16_t hn[4];
-        fetch(pre, t0, 0);
-        fetch_dz(hn, t0);
-        for (long tile = t0; tile < t1; tile++) {
-            const long next = tile + 1 < t1 ? tile + 1 : tile;
-            bf16x4 b;
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                b[i] = (short)hn[i];
-                bsum += bf2f(hn[i]);
-            }
-            fetch_dz(hn, next);
-#pragma unroll
-            for (int dzy = 0; dzy < 9; dzy++) {
-                wave_sync(); // every lane is done with the previous row
-#pragma unroll
-                for (int k = 0; k < NCH; k++)
-                    if (lane + 64 * k < ROWCH) rows[wv][lane + 64 * k] = pre[k];
-                if (dzy < 8) fetch(pre, tile, dzy + 1);
-                else fetch(pre, next, 0);
-                wave_sync();
-#pragma unroll
-                for (int dx = 0; dx < 3; dx++) {
-                    // tap (dz, dy, dx) in tap_voxel's order; element i of this lane is voxel
-                    // x0 + 4 gq + i + dx - 1, staged at j = 4 gq + i + dx
-                    const int t = dzy * 3 + dx;
-#pragma unroll
-                    for (int kc = 0; kc < KC; kc++) {
-                        bf16x4 a;
-#pragma unroll
-                        for (int i = 0; i < 4; i++) a[i] = (short)rowl[(4 * gq + i + dx) * CINP + kc * 16 + r];
-                        acc[t][kc] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t][kc], 0, 0, 0);
-                    }
-                }
-            }
+        for (int k = 0; k < NCH; k++) {
+            const int c = lane + 64 * k;
+            const int q = c % CPV, vox = c / CPV; // voxel row * 18 + j of the source tile
+            const int off = c < XCH ? (q >> 1) * (162 * 16) + vox * 16 + (q & 1) * 8 : 162 * CINP + (c - XCH) * 8;
+            if (c < XCH + 32) *(u32x4*)(slot + off) = pre[k];
         }
+        fetch(tile + 1 < t1 ? tile + 1 : tile);
+        wave_sync();
+        const bf16x4 b = read_rows_tr(tr + 162 * CINP);
+#pragma unroll
+        for (int i = 0; i < 4; i++) bsum += bf2f((uint16_t)b[i]);
+        // tap (dz, dy, dx) in tap_voxel's order; element i of this lane is voxel x0 + 4 gq + i + dx - 1,
+        // staged at j = 4 gq + i + dx
+#pragma unroll
+        for (int t = 0; t < 27; t++)
+#pragma unroll
+            for (int kc = 0; kc < KC; kc++) {
+                const bf16x4 a = read_rows_tr(tr + (kc * 162 + t / 3 * 18 + t % 3) * 16);
+                acc[t][kc] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t][kc], 0, 0, 0);
+            }
     }
     float* out = partial + wave * PW;
 #pragma unroll
