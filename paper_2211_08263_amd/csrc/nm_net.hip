@@ -314,15 +314,15 @@ __global__ __launch_bounds__(256, CINP == 16 ? 3 : 2) void k_conv_fwd(const uint
 
 // ---------------------------------------------------------------------------
 // Weight gradient: dW[co][ci][tap] = sum_v dZ[v][co] X[v + d(tap)][ci]  (MFMA with
-// K = voxels), bias gradient db[co] = sum_v dZ[v][co].  Each wave writes its
-// partial sums; k_reduce_partials adds them in a fixed order.
-//   partial layout per wave: [27][KC][64 lanes][4] then [64 lanes] (bias)
+// K = voxels), bias gradient db[co] = sum_v dZ[v][co].  Each block writes its
+// four waves' sums; k_reduce_bwdw adds them in a fixed order.
+//   partial layout per block: [27][KC][64 lanes][4] then [64 lanes] (bias)
 // A tile is 16 consecutive voxels of one x row.  For each tile the wave stages the 9 x 18 source voxels
 // around it and dZ in its own LDS slot with 16-byte loads (issued a tile ahead), 16 channels of a voxel
 // in a row, and takes its operands from there with transposing reads: A[m = channel][k = voxel] wants
 // four voxels of one channel per lane, memory holds the channels of one voxel.  What is left is one
-// read and one MFMA per tap and 16 channels.  64^3: 75 -> T32 us with 32 input channels (staged row by
-// row, operands gathered from LDS by 2 bytes), 31 -> T16 with 16 (gathered by 2 bytes from memory).
+// read and one MFMA per tap and 16 channels.  64^3: 75 -> 29 us with 32 input channels (staged row by
+// row, operands gathered from LDS by 2 bytes), 31 -> 15 with 16 (gathered by 2 bytes from memory).
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
@@ -351,8 +351,6 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
     const long wave = (long)blockIdx.x * 4 + wv;
     const int r = lane & 15, gq = lane >> 4;
     const long ntiles = g.N / 16;
-    // waves past the last tile range own no partial slot
-    if (wave * tiles_per_wave >= ntiles) return;
     uint16_t* const slot = slots[wv];
     const uint16_t* const tr = slot + (4 * gq + r / 4) * 16 + (r % 4) * 4;
     auto wave_sync = [] {
@@ -395,7 +393,7 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
         }
     };
     static_assert(64 * (NCH - 1) <= XCH && 64 % CPV == 0, "dZ is in the last round of chunks");
-    fetch(t0);
+    if (t0 < t1) fetch(t0);
     for (long tile = t0; tile < t1; tile++) {
         wave_sync(); // every lane is done with the previous tile
 #pragma unroll
@@ -420,24 +418,43 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
                 acc[t][kc] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t][kc], 0, 0, 0);
             }
     }
-    float* out = partial + wave * PW;
+    // The block's four waves to one slot, CH accumulators at a time through the staging area: a slot a wave
+    // meant 28 / 57 MB of partials (16 / 32 channels) to write and read back.
+    constexpr int NI = 27 * KC, CH = 4 * KC;
+    static_assert(4 * CH * 64 * 16 <= (int)sizeof(slots), "the accumulators of a round fit the staging area");
+    f32x4* const red = (f32x4*)slots;
+    f32x4* const out = (f32x4*)(partial + blockIdx.x * PW);
 #pragma unroll
-    for (int t = 0; t < 27; t++)
+    for (int c0 = 0; c0 < NI; c0 += CH) {
+        __syncthreads();
 #pragma unroll
-        for (int kc = 0; kc < KC; kc++)
+        for (int i = 0; i < CH; i++)
+            if (c0 + i < NI) red[(wv * CH + i) * 64 + lane] = acc[(c0 + i) / KC][(c0 + i) % KC];
+        __syncthreads();
+        for (int i = wv; i < CH && c0 + i < NI; i += 4) {
+            f32x4 s = red[i * 64 + lane];
 #pragma unroll
-            for (int i = 0; i < 4; i++) out[((long)(t * KC + kc) * 64 + lane) * 4 + i] = acc[t][kc][i];
-    out[27L * KC * 256 + lane] = bsum;
+            for (int w = 1; w < 4; w++) s += red[(w * CH + i) * 64 + lane];
+            out[(c0 + i) * 64 + lane] = s;
+        }
+    }
+    __syncthreads();
+    float* const bred = (float*)slots;
+    bred[threadIdx.x] = bsum;
+    __syncthreads();
+    if (threadIdx.x < 64)
+        partial[blockIdx.x * PW + 27L * KC * 256 + lane] =
+            bred[lane] + bred[64 + lane] + bred[128 + lane] + bred[192 + lane];
 }
 
-// Sum the per-wave partials (fixed order) and scatter into dW[co][ci][tap], db[co].
+// Sum the per-block partials (fixed order) and scatter into dW[co][ci][tap], db[co].
 // D element (lane l, reg i) of chunk kc = [row ci = kc*16 + 4*(l/16) + i][col co = l % 16].
 // A block owns 64 consecutive elements (256-byte rows of every slot) and its 16 wavefronts the slots
-// w, w + 16, ...: one thread per element walking all of up to 1024 slots was one serial chain on 28-55
-// blocks (240 us whatever the channels, at 64^3); at this split the 28 / 57 MB take 6 / 10 us.
+// w, w + 16, ...: one thread per element walking all slots was one serial chain on 28-55 blocks (240 us
+// whatever the channels, for 1024 slots); at this split and 256 slots 4 / 5 us (64^3, 16 / 32 channels).
 constexpr int kRedRows = 16;
 template <int CINP>
-__global__ __launch_bounds__(64 * kRedRows) void k_reduce_bwdw(const float* __restrict__ partial, int nwaves,
+__global__ __launch_bounds__(64 * kRedRows) void k_reduce_bwdw(const float* __restrict__ partial, int nslots,
                                                                float* __restrict__ dW, float* __restrict__ db, int cin,
                                                                int cout)
 {
@@ -448,7 +465,7 @@ __global__ __launch_bounds__(64 * kRedRows) void k_reduce_bwdw(const float* __re
     const long e = (long)blockIdx.x * 64 + l; // e < PW: the last block holds the bias sums
     float s = 0.f;
 #pragma unroll 8
-    for (int w = row; w < nwaves; w += kRedRows) s += partial[w * PW + e];
+    for (int w = row; w < nslots; w += kRedRows) s += partial[w * PW + e];
     sh[row][l] = s;
     __syncthreads();
     if (row != 0) return;
@@ -736,9 +753,10 @@ static int launch_conv(int cinp, int epi, const uint16_t* X, const uint16_t* W, 
     return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
-// Waves of the weight-gradient pass (each owns a partial-sum slot of bwdw_slot_floats(cinp)).
+// Waves of the weight-gradient pass; every block of four owns a partial-sum slot of bwdw_slot_floats(cinp).
 constexpr long kBwdwWaves = 1024;
 static long bwdw_waves(long ntiles, long cap = kBwdwWaves) { return ntiles < cap ? ntiles : cap; }
+static long bwdw_slots(long ntiles) { return (bwdw_waves(ntiles) + 3) / 4; }
 static constexpr long bwdw_slot_floats(int cinp) { return 27L * (cinp / 16) * 256 + 64; }
 
 static int launch_bwdw(int cinp, const uint16_t* X, const uint16_t* DZ, float* partial, float* dW, float* db, int cin,
@@ -753,11 +771,11 @@ static int launch_bwdw(int cinp, const uint16_t* X, const uint16_t* DZ, float* p
     if (cinp == 32) {
         hipLaunchKernelGGL((k_conv_bwdw<32>), dim3(blocks), dim3(256), 0, s, X, DZ, partial, g, tpw);
         hipLaunchKernelGGL((k_reduce_bwdw<32>), dim3(nred), dim3(64 * kRedRows), 0, s, partial,
-                           (int)waves, dW, db, cin, cout);
+                           blocks, dW, db, cin, cout);
     } else {
         hipLaunchKernelGGL((k_conv_bwdw<16>), dim3(blocks), dim3(256), 0, s, X, DZ, partial, g, tpw);
         hipLaunchKernelGGL((k_reduce_bwdw<16>), dim3(nred), dim3(64 * kRedRows), 0, s, partial,
-                           (int)waves, dW, db, cin, cout);
+                           blocks, dW, db, cin, cout);
     }
     return hipGetLastError() == hipSuccess ? 0 : -2;
 }
@@ -822,8 +840,7 @@ static int net_workspace(nm_net* n, long N)
     CHECK_NM(net_alloc((void**)&n->dz0, N * kHid * 2, &n->ws_allocs));
     CHECK_NM(net_alloc((void**)&n->dz1, N * kHid * 2, &n->ws_allocs));
     CHECK_NM(net_alloc((void**)&n->pred, N * kPredStride * 4, &n->ws_allocs));
-    const long waves = bwdw_waves(N / 16);
-    CHECK_NM(net_alloc((void**)&n->partial, waves * (27L * 2 * 256 + 64) * 4, &n->ws_allocs));
+    CHECK_NM(net_alloc((void**)&n->partial, bwdw_slots(N / 16) * bwdw_slot_floats(32) * 4, &n->ws_allocs));
     CHECK_NM(net_alloc((void**)&n->red, 4096 * sizeof(double), &n->ws_allocs));
     n->capN = N;
     return NM_OK;
@@ -1106,8 +1123,7 @@ int nm_conv3d_bf16(void* stream, int mode, const int* grid, int cinp, int cin, i
         net_alloc((void**)&b.wf, 27 * 16 * cinp * 2, &tmp) || net_alloc((void**)&b.wb, 27 * 256 * 2, &tmp))
         rc = NM_ENOMEM;
     if (rc == NM_OK && mode == 2) {
-        const long waves = bwdw_waves(g.N / 16);
-        if (net_alloc((void**)&b.part, waves * bwdw_slot_floats(cinp) * 4, &tmp) ||
+        if (net_alloc((void**)&b.part, bwdw_slots(g.N / 16) * bwdw_slot_floats(cinp) * 4, &tmp) ||
             net_alloc((void**)&b.dw, nw * 4, &tmp) || net_alloc((void**)&b.db, 64, &tmp))
             rc = NM_ENOMEM;
     }
@@ -1122,7 +1138,7 @@ int nm_conv3d_bf16(void* stream, int mode, const int* grid, int cinp, int cin, i
 // nm_conv3d_bf16_noalloc: the same layer kernels with every device buffer of the call
 // (FP32 and packed BF16 weights, bias, weight-gradient partials and sums) carved out of one
 // file-scope device array, so that callers that may not allocate device memory can run
-// them.  The weight-gradient pass uses at most kNoAllocWaves partial-sum slots, which keeps
+// them.  The weight-gradient pass uses at most kNoAllocWaves waves, which keeps
 // the array's size independent of the grid.  Every call on a device shares that device's
 // array (kept until the process ends); calls that overlap on one device race.
 // ---------------------------------------------------------------------------
