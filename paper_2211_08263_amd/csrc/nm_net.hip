@@ -325,6 +325,7 @@ __global__ __launch_bounds__(256, CINP == 16 ? 3 : 2) void k_conv_fwd(const uint
 // row, operands gathered from LDS by 2 bytes), 31 -> 15 with 16 (gathered by 2 bytes from memory).
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any; // callers' tensors may start anywhere
 
 // Four rows of 16 elements each per 16 lanes: lane (gq, r) gets elements r of rows 4 gq .. 4 gq + 3, its
 // own address being that of row 4 gq + r / 4, elements 4 (r % 4) .. + 3.
@@ -389,7 +390,7 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
             // dZ: 32 chunks, those past them re-read its first
             const int c = lane + 64 * k;
             if (k == NCH - 1 && c >= XCH) src = DZ + (size_t)v0 * kHid + (c < XCH + 32 ? c - XCH : 0) * 8;
-            pre[k] = *(const u32x4*)src;
+            pre[k] = *(const u32x4_any*)src;
         }
     };
     static_assert(64 * (NCH - 1) <= XCH && 64 % CPV == 0, "dZ is in the last round of chunks");
