@@ -367,6 +367,25 @@ struct PcgResult {
     bool converged = false;
 };
 
+// r = P (b - A x) and *rr = r.r (waits for it); r32: r also rounded to FP32, or null.
+template <typename T>
+int residual_of(nm_ctx* c, const T* b, const T* x, T* r, const uint8_t* mask, float* r32, double* rr)
+{
+    PassArgs a = pass_args<T>(c, x);
+    a.out = r;
+    a.b = b;
+    a.r32 = r32;
+    a.mask = mask;
+    LCHK(c, launch_ystart<T>(YS_APPLY, c->sp, a, Prec<T>::tw(c), c->stream));
+    CHK(operator_middle<T>(c, a));
+    a.partials = c->part_a;
+    LCHK(c, launch_yend<T>(YE_RESIDUAL, c->sp, a, Prec<T>::tw(c), c->stream));
+    LCHK(c, launch_reduce(c->part_a, yend_blocks<T>(c->lay), c->scal, RED_STORE_RR, 0, c->stream));
+    CHK(read_scalars(c));
+    *rr = c->hscal[S_RR];
+    return NM_OK;
+}
+
 // Preconditioned conjugate gradients (Hestenes-Stiefel) on real-space vectors.
 // x: initial guess / solution.  With masked, P A P and P M P on the free dofs.
 // rr_known >= 0: r already holds P (rhs - A x) with r.r = rr_known (no initial apply;
@@ -386,12 +405,15 @@ int pcg(nm_ctx* c, const T* rhs, T* x, T* r, T* p, T* q, bool masked, bool x_zer
     double rr = rr_known;
     if (rr_known < 0 && !rhs) return fail(c, NM_EINVAL, "PCG needs the right-hand side or the initial residual");
     if (rr_known < 0) {
-        if (x_zero) LCHK(c, launch_fill<T>(q, (T)0, n, s));
-        else CHK(apply_A<T>(c, x, q, mk));
-        LCHK(c, launch_residual<T>(rhs, q, r, mk, c->N, 3, c->part_a, s));
-        LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
-        CHK(read_scalars(c));
-        rr = c->hscal[S_RR];
+        if (x_zero) {
+            LCHK(c, launch_fill<T>(q, (T)0, n, s));
+            LCHK(c, launch_residual<T>(rhs, q, r, mk, c->N, 3, c->part_a, s));
+            LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
+            CHK(read_scalars(c));
+            rr = c->hscal[S_RR];
+        } else {
+            CHK(residual_of<T>(c, rhs, x, r, mk, nullptr, &rr));
+        }
     }
     res->iters = 0;
     res->rr = rr;
@@ -498,11 +520,9 @@ int projected_bref(nm_ctx* c, const double* x, double* bref)
         LCHK(c, launch_gather_gamma(c->gbuf, x, c->gidx, c->ng, 3, c->N, s));
         LCHK(c, launch_set_gamma(c->z, c->gidx, c->ng, c->gbuf, 1, 3, c->N, s));
     }
-    CHK(apply_A<double>(c, c->z, c->q, c->mask));
-    LCHK(c, launch_residual<double>(c->b, c->q, c->r, c->mask, c->N, 3, c->part_a, s, c->r32));
-    LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
-    CHK(read_scalars(c));
-    *bref = std::sqrt(c->hscal[S_RR]);
+    double rr;
+    CHK(residual_of<double>(c, c->b, c->z, c->r, c->mask, c->r32, &rr));
+    *bref = std::sqrt(rr);
     return NM_OK;
 }
 
@@ -576,11 +596,7 @@ int solve_mixed(nm_ctx* c, double* x, double bref, nm_step_stats* st, double rr_
                 return NM_OK;
             }
         } else {
-            CHK(apply_A<double>(c, x, c->q, c->mask));
-            LCHK(c, launch_residual<double>(c->b, c->q, c->r, c->mask, c->N, 3, c->part_a, s, c->r32));
-            LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
-            CHK(read_scalars(c));
-            rr = c->hscal[S_RR];
+            CHK(residual_of<double>(c, c->b, x, c->r, c->mask, c->r32, &rr));
         }
         if (sweeps == 0 && st) st->relres0 = std::sqrt(rr) / bref;
         if (!std::isfinite(rr)) return fail(c, NM_ENAN, "non-finite residual in refinement sweep %d", sweeps);
@@ -625,12 +641,16 @@ int solve_mixed_plain(nm_ctx* c, const double* rhs, double* x, double bref, doub
     int sweeps = 0, inner = 0;
     for (;;) {
         // r = rhs - A x (the first residual of a zero start is rhs itself)
-        if (sweeps == 0 && x_zero) LCHK(c, launch_fill<double>(c->q, 0.0, n, s));
-        else CHK(apply_A<double>(c, x, c->q, nullptr));
-        LCHK(c, launch_residual<double>(rhs, c->q, c->r, nullptr, c->N, 3, c->part_a, s, c->r32));
-        LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
-        CHK(read_scalars(c));
-        double rr = c->hscal[S_RR];
+        double rr;
+        if (sweeps == 0 && x_zero) {
+            LCHK(c, launch_fill<double>(c->q, 0.0, n, s));
+            LCHK(c, launch_residual<double>(rhs, c->q, c->r, nullptr, c->N, 3, c->part_a, s, c->r32));
+            LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
+            CHK(read_scalars(c));
+            rr = c->hscal[S_RR];
+        } else {
+            CHK(residual_of<double>(c, rhs, x, c->r, nullptr, c->r32, &rr));
+        }
         if (!std::isfinite(rr)) return fail(c, NM_ENAN, "non-finite residual in refinement sweep %d", sweeps);
         if (sweeps == 0 && guard_zero && !x_zero && rr > bref * bref) {
             // restart from zero: r = rhs
@@ -678,11 +698,7 @@ int green_solve(nm_ctx* c, const double* rhs, double* x, double bref, double tol
     double rr0 = -1.0;
     if (guard_zero && !x_zero) {
         const long n = 3 * c->N;
-        CHK(apply_A<double>(c, x, c->q, nullptr));
-        LCHK(c, launch_residual<double>(rhs, c->q, c->r, nullptr, c->N, 3, c->part_a, c->stream));
-        LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, c->stream));
-        CHK(read_scalars(c));
-        rr0 = c->hscal[S_RR];
+        CHK(residual_of<double>(c, rhs, x, c->r, nullptr, nullptr, &rr0));
         if (rr0 > bref * bref) {
             LCHK(c, launch_fill<double>(x, 0.0, n, c->stream));
             LCHK(c, launch_copy<double>(c->r, rhs, n, c->stream));
@@ -1513,20 +1529,14 @@ static int step_impl(nm_ctx* c, const double* U_n, int per_point, nm_step_stats*
                 CHK(solve_mixed(c, c->w, bref, &local, rr0));
             }
             if (c->opt.true_residual) {
-                CHK(apply_A<double>(c, c->w, c->q, c->mask));
-                LCHK(c, launch_residual<double>(c->b, c->q, c->r, c->mask, c->N, 3, c->part_a, s));
-                LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
-                CHK(read_scalars(c));
-                local.relres = std::sqrt(c->hscal[S_RR]) / (bref > 0 ? bref : 1.0);
+                double rr;
+                CHK(residual_of<double>(c, c->b, c->w, c->r, c->mask, nullptr, &rr));
+                local.relres = std::sqrt(rr) / (bref > 0 ? bref : 1.0);
             }
         } else {
             if (guard) {
                 // residual of the learned iterate, kept in c->r for the solve unless rejected
-                CHK(apply_A<double>(c, c->w, c->q, c->mask));
-                LCHK(c, launch_residual<double>(c->b, c->q, c->r, c->mask, c->N, 3, c->part_a, s));
-                LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
-                CHK(read_scalars(c));
-                rr0 = c->hscal[S_RR];
+                CHK(residual_of<double>(c, c->b, c->w, c->r, c->mask, nullptr, &rr0));
                 if (rr0 > bref * bref) CHK(restart_from_zero());
             }
             PcgResult r1;
@@ -1536,11 +1546,9 @@ static int step_impl(nm_ctx* c, const double* U_n, int per_point, nm_step_stats*
             local.relres = std::sqrt(r1.rr) / (bref > 0 ? bref : 1.0);
             local.relres0 = std::sqrt(r1.rr0) / (bref > 0 ? bref : 1.0);
             if (c->opt.true_residual) {
-                CHK(apply_A<double>(c, c->w, c->q, c->mask));
-                LCHK(c, launch_residual<double>(c->b, c->q, c->r, c->mask, c->N, 3, c->part_a, s));
-                LCHK(c, launch_reduce(c->part_a, vec_blocks(n), c->scal, RED_STORE_RR, 0, s));
-                CHK(read_scalars(c));
-                local.relres = std::sqrt(c->hscal[S_RR]) / (bref > 0 ? bref : 1.0);
+                double rr;
+                CHK(residual_of<double>(c, c->b, c->w, c->r, c->mask, nullptr, &rr));
+                local.relres = std::sqrt(rr) / (bref > 0 ? bref : 1.0);
             }
         }
         if (c->opt.compute_reaction && c->ng > 0) {

@@ -80,7 +80,8 @@ enum YStartMode { YS_APPLY = 0, YS_EXPLICIT = 1, YS_PCG = 2 };
 //   YE_EXPLICIT_NEXT a step with a next one behind it: this step's end and the next one's YS_EXPLICIT
 //               in one, v <- v + 2 o / rho (Gamma voxels, whose v is already the next half step's: v as it
 //               is), u <- u + dt v, D_y u into work components 0..2; a is not needed in between
-enum YEndMode { YE_OUT = 0, YE_UPDATE = 1, YE_EXPLICIT = 2, YE_EXPLICIT_NEXT = 3 };
+//   YE_RESIDUAL r = mask(b - q), also rounded to FP32 (r32, or null), with the partial sums of r.r
+enum YEndMode { YE_OUT = 0, YE_UPDATE = 1, YE_EXPLICIT = 2, YE_EXPLICIT_NEXT = 3, YE_RESIDUAL = 4 };
 
 struct PassArgs {
     Layout lay;
@@ -93,7 +94,9 @@ struct PassArgs {
     void* v = nullptr;         // explicit scheme: velocity
     void* a = nullptr;         // explicit scheme: acceleration
     void* r = nullptr;         // YE_UPDATE: y spectrum of the residual (in/out)
-    void* out = nullptr;       // YE_OUT
+    void* out = nullptr;       // YE_OUT: result; YE_RESIDUAL: the residual (real space)
+    const void* b = nullptr;   // YE_RESIDUAL: right-hand side
+    float* r32 = nullptr;      // YE_RESIDUAL
     const uint8_t* mask = nullptr;   // Gamma voxel mask or null
     const uint16_t* phase = nullptr; // grain ids
     const void* C21 = nullptr;       // per-grain stiffness

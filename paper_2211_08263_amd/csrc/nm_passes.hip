@@ -527,7 +527,8 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_yend(PassArgs
     V ro[R];
     uint16_t mk[R];
     if constexpr (SMALL && MODE == YE_UPDATE) c.template ld<NT>((const V*)a.r + fo, ro);
-    if constexpr (SMALL && (MODE == YE_UPDATE || MODE == YE_OUT)) c.ld_mask(a.mask, mk);
+    if constexpr (SMALL && MODE == YE_RESIDUAL) c.template ld<NT>((const V*)a.b + fo, ro);
+    if constexpr (SMALL && (MODE == YE_UPDATE || MODE == YE_OUT || MODE == YE_RESIDUAL)) c.ld_mask(a.mask, mk);
     double pq = 0.0;
     if constexpr (MODE == YE_UPDATE) {
         if (a.carry.action == RED_ALPHA) pq = block_total<BLK>(a.carry.part + (long)fld * a.carry.n, a.carry.n);
@@ -599,6 +600,25 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_yend(PassArgs
             c.deriv(v, lds, tws, frs);
             c.template st<NT>(src, v);
         }
+    } else if constexpr (MODE == YE_RESIDUAL) {
+        // b - q here rather than q to memory and a kernel that reads it back (6 fields: FP64, 256^3, this
+        // pass and that kernel 191 + 253 us, 295 in one)
+        if constexpr (!SMALL) c.template ld<NT>((const V*)a.b + fo, ro);
+#pragma unroll
+        for (int m = 0; m < R; m++) v[m] = V{ro[m].x - v[m].x, ro[m].y - v[m].y};
+        if constexpr (!SMALL) c.masked(a.mask, v);
+        else c.masked(mk, v);
+        c.template st<NT>((V*)a.out + fo, v);
+        double part = 0.0;
+#pragma unroll
+        for (int m = 0; m < R; m++) part += (double)v[m].x * (double)v[m].x + (double)v[m].y * (double)v[m].y;
+        if (a.r32 && c.valid) {
+            float2* const r32 = (float2*)a.r32 + fo;
+#pragma unroll
+            for (int m = 0; m < R; m++) r32[c.elem(m)] = float2{(float)v[m].x, (float)v[m].y};
+        }
+        const double s = block_sum<BLK>(c.valid ? part : 0.0);
+        if (threadIdx.x == 0) a.partials[(long)fld * (3 * ntiles) + blockIdx.x] = s;
     } else {
         if constexpr (!SMALL) c.masked(a.mask, v);
         else c.masked(mk, v);
@@ -1195,6 +1215,8 @@ template <typename T> int launch_yend(int mode, const SpecParams& sp, const Pass
         NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_yend<T, NN, BLK, MEM, YE_OUT>), a, g, f)
     } else if (mode == YE_UPDATE) {
         NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_yend<T, NN, BLK, MEM, YE_UPDATE>), a, g, f)
+    } else if (mode == YE_RESIDUAL) {
+        NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_yend<T, NN, BLK, MEM, YE_RESIDUAL>), a, g, f)
     } else if constexpr (sizeof(T) == 8) {
         if (mode == YE_EXPLICIT) {
             NM_COL_LAUNCH(a.lay.n2, a.lay, g, 0, s, (k_yend<T, NN, BLK, MEM, YE_EXPLICIT>), a, g, f)

@@ -53,6 +53,32 @@ def test_passes_at_the_edges_of_their_shapes(dim, n):
     assert err <= 1e-10
 
 
+@pytest.mark.parametrize("dim,n", CASES[:3] + CASES[5:8], ids=["x".join(map(str, n)) for _, n in CASES[:3] + CASES[5:8]])
+def test_residual_from_the_last_pass(dim, n):
+    """The operator's last pass forms b - A x and its norm: a solve of no iterations reports
+    |P (b - A x)| over its reference norm, |b| or, with the Gamma voxels masked, |P (b - A x_Gamma)|.
+    Norms of sums of some ten FP64 roundings an entry: 1e-12."""
+    import dataclasses
+    pb = random_problem(dim, n, seed=2 + sum(n))
+    N = int(np.prod(n))
+    g = np.sort(np.random.default_rng(5).choice(N, size=N // 5, replace=False)).astype(np.int64)
+    pb = dataclasses.replace(pb, gamma_idx=g)
+    op = oracle.OracleProblem.from_problem(pb)
+    x, b = W.random_field(op.field_shape, seed=8), W.random_field(op.field_shape, seed=9)
+    free = np.ones(N, bool)
+    free[g] = False
+    norm = lambda f, keep: np.linalg.norm(np.where(keep, f.reshape(f.shape[0], -1), 0.0))
+    xg = np.where(free, 0.0, x.reshape(x.shape[0], -1)).reshape(x.shape)
+    r = b - op.apply(x)
+    want = {False: norm(r, True) / norm(b, True), True: norm(r, free) / norm(b - op.apply(xg), free)}
+    with nmb.newmark_init_problem(pb, nmb.Options()) as ctx:
+        for masked, ref in want.items():
+            xd = dev(field3(x, dim)).reshape(-1)
+            it, rel = nmb.pcg_solve(ctx, dev(field3(b, dim)).reshape(-1), xd, masked=masked, fixed_iters=0)
+            print(f"residual {n} masked {masked}: {rel:.15e} want {ref:.15e}", flush=True)
+            assert it == 0 and abs(rel - ref) <= 1e-12 * ref
+
+
 EXPLICIT_CASES = [(3, (8, 8, 8), False), (3, (16, 128, 8), True), (3, (8, 256, 16), False), (3, (8, 512, 8), True),
                   (2, (8, 64), False), (2, (64, 16), True)]
 
