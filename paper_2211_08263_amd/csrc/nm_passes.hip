@@ -734,8 +734,8 @@ template <typename T, int BLK> constexpr int x_waves(int w64, int w32)
     return BLK != kBlock ? 1 : sizeof(T) == 8 ? w64 : w32;
 }
 
-// The stress pass: 16 fields and the grain ids, 256^3: 0.217 ms in FP32 (5.1 TB/s), 0.458 in FP64
-// (4.8); the x pass it replaces moved 12 fields in 0.20 and 0.36 ms.  HBM bounds it in FP32, and in FP64
+// The stress pass: 16 fields and the grain ids, 256^3: 0.204 ms in FP32 (5.4 TB/s), 0.442 in FP64
+// (4.9); the x pass it replaces moved 12 fields in 0.20 and 0.36 ms.  HBM bounds it in FP32, and in FP64
 // the registers too (two wavefronts per SIMD).  A group of N1 / 4 lanes holds the rows (y, y + 1) of one z plane as a complex
 // line of N1 points, in all three components at once (one synchronisation per stage for the three).
 template <typename T, int N1, int BLK, int MEM>
@@ -745,6 +745,10 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
     using V = cx_t<T>;
     constexpr bool SMALL = BLK != kBlock;
     constexpr int R = kXR, G = N1 / R, LPB = BLK / G, NT = NM_NT(XS, T);
+    // p is needed again for the inertia term.  FP32 holds it over the transforms (three wavefronts per SIMD
+    // instead of four, 256^3: 221 -> 204 us; the counters showed every second read to leave the compute die).
+    // FP64 has no registers for that and reads it again, the first time without the streaming hint (459 -> 442).
+    constexpr bool HOLD_P = SMALL || sizeof(T) == 4;
     // strains fetched ahead of the first transform
     constexpr int EARLY = SMALL ? 5 : sizeof(T) == 8 ? 0 : 3;
     constexpr bool WAVE = G <= 64;
@@ -781,6 +785,16 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
             v[m].y = ld_s<NT>((const T*)((const char*)q + o) + (m * G + N1));
         }
     };
+    // p: where it is read twice, the first read stays in the caches for the second
+    auto ld_p = [&](const T* q, V (&v)[R]) {
+        constexpr int NP = HOLD_P ? NT : NT & ~1;
+        const uint32_t o = lane_off();
+#pragma unroll
+        for (int m = 0; m < R; m++) {
+            v[m].x = ld_s<NP>((const T*)((const char*)q + o) + m * G);
+            v[m].y = ld_s<NP>((const T*)((const char*)q + o) + (m * G + N1));
+        }
+    };
     auto st = [&](T* q, const V (&v)[R]) {
         const uint32_t o = lane_off();
 #pragma unroll
@@ -791,7 +805,7 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
     };
     V d[3][R], w[5][R]; // displacement and its x derivative; D_y p1, D_y p2, g23, D_z p1, D_z p3
 #pragma unroll
-    for (int j = 0; j < 3; j++) ld(p + j * ps, d[j]);
+    for (int j = 0; j < 3; j++) ld_p(p + j * ps, d[j]);
 #pragma unroll
     for (int c = 0; c < EARLY; c++) {
         if (c < 3 || has_z) {
@@ -802,7 +816,7 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
         }
     }
     V po[3][R];
-    if constexpr (SMALL) {
+    if constexpr (HOLD_P) {
 #pragma unroll
         for (int j = 0; j < 3; j++)
 #pragma unroll
@@ -871,10 +885,8 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
         st(S + 3 * cs, w[3]); // s13
         st(S + 4 * cs, w[4]); // s33
     }
-    // p again for the inertia term: its second read comes from the caches, and held over the
-    // transforms it would cost a wave of occupancy
     deriv3(d, [&]() {
-        if constexpr (!SMALL) {
+        if constexpr (!HOLD_P) {
 #pragma unroll
             for (int j = 0; j < 3; j++) ld(p + j * ps, po[j]);
         }
