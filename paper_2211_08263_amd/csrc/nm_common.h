@@ -21,7 +21,6 @@ template <typename V> __device__ __forceinline__ V cmulc(V a, V b)
 {
     return V{a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y};
 }
-template <typename V> __device__ __forceinline__ V conjv(V a) { return V{a.x, -a.y}; }
 // multiply by (DIR * i): DIR = -1 -> -i, DIR = +1 -> +i
 template <int DIR, typename V> __device__ __forceinline__ V mul_di(V a)
 {
@@ -54,15 +53,6 @@ template <int NT, typename V> __device__ __forceinline__ void st_nt(V* p, V v)
     } else {
         *p = v;
     }
-}
-
-// Spatial frequency of DFT index k on an axis of n points, box length L.
-// Standard DFT order; the Nyquist bin (k = n/2) and n == 1 give 0.
-__host__ __device__ __forceinline__ double freq_of(int k, int n, double L)
-{
-    if (n == 1 || 2 * k == n) return 0.0;
-    int kk = (2 * k < n) ? k : k - n;
-    return 6.283185307179586476925286766559 * (double)kk / L;
 }
 
 // Signed DFT index of bin k on an axis of n points (0 for the Nyquist bin and n == 1);
