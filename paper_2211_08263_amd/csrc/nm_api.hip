@@ -245,12 +245,14 @@ int precond_middle(nm_ctx* c, const Layout& lay, const void* src, long sc, long 
     const void* tw = Prec<T>::tw(c);
     const int nbz = xprecond_blocks<T>(lay);
     const Carry rz{partials, nbz, scal, partials ? rz_action : (int)RED_NONE, multi};
+    Layout first = lay; // the pass that carries red, which may raise S_STOP
+    if (first.stop && red.action == RED_RR_CHECK) first.stop += S_HALT - S_STOP;
     if (c->n3 == 1) {
-        LCHK(c, launch_xprecond<T>(c->sp, lay, src, sc, sb, S2, tw, s, partials, red));
+        LCHK(c, launch_xprecond<T>(c->sp, first, src, sc, sb, S2, tw, s, partials, red));
         return NM_OK;
     }
     ColFft f{};
-    f.lay = lay;
+    f.lay = first;
     f.axis = 2;
     f.dir = -1;
     f.src = src;
@@ -262,6 +264,7 @@ int precond_middle(nm_ctx* c, const Layout& lay, const void* src, long sc, long 
     f.carry = red;
     LCHK(c, launch_colfft<T>(f, tw, s));
     LCHK(c, launch_xprecond<T>(c->sp, lay, S2, lay.cs, lay.bs, S2, tw, s, partials, Carry{}));
+    f.lay = lay;
     f.dir = +1;
     f.src = S2;
     f.sc = lay.cs;

@@ -42,10 +42,13 @@ struct Layout {
 // S_STOP .. S_MODE drive a Krylov loop that runs several iterations between host checks:
 // the residual reduction counts iterations (S_ITER) and raises S_STOP once r.r <= S_THR2
 // (S_MODE 0) or the count reaches S_LIMIT; every guarded kernel after that returns at once.
+// The pass that carries that reduction is guarded by S_HALT instead, which the first pass of an iteration
+// raises when it finds S_STOP set: no launch reads the flag that it raises, so that a block's
+// wavefronts always take the same side of the guard.
 enum ScalarSlot {
     S_ALPHA = 0, S_BETA = 1, S_FIRST = 2, S_RZ = 3, S_PQ = 4, S_RR = 5,
     S_RZ2 = 7, // r.z of the iteration under way (2D, see PassArgs::carry)
-    S_STOP = 8, S_ITER = 9, S_THR2 = 10, S_LIMIT = 11, S_MODE = 12, S_COUNT = 16
+    S_STOP = 8, S_ITER = 9, S_THR2 = 10, S_LIMIT = 11, S_MODE = 12, S_HALT = 13, S_COUNT = 16
 };
 
 // What a sum of per-block partials does to the scalar block.

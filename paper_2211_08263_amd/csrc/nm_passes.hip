@@ -91,7 +91,8 @@ namespace nm {
 constexpr int kXStressWaves64 = 2, kXStressWaves32 = 3, kXPrecondWaves64 = 2, kXPrecondWaves32 = 3, kColWaves64 = 2,
               kColWaves32 = 3;
 
-// Early exit of a guarded kernel once the Krylov loop has stopped (uniform branch).
+// Early exit of a guarded kernel once the Krylov loop has stopped: a uniform branch, as no launch writes the
+// flag that guards it (see ScalarSlot).
 __device__ __forceinline__ bool stopped(const double* stop) { return stop && *stop != 0.0; }
 
 // ---------------------------------------------------------------------------
@@ -354,14 +355,17 @@ template <typename T> __device__ __forceinline__ int col_tile(int blk, int ntile
 {
     return sizeof(T) == 4 ? blk / 3 : blk % ntiles;
 }
-// Prologue of a column kernel: the twiddles' fetch, the stop flag ...
-#define NM_COL_BEGIN(L)                                                                                                \
+// Prologue of a column kernel: the twiddles' fetch, the stop flag (and what is done where it is set) ...
+#define NM_COL_BEGIN(L, ...)                                                                                           \
     [[maybe_unused]] constexpr bool SMALL = BLK < col_block<T, L>();                                                   \
     __shared__ V lds[ColShape<T, L, BLK>::G > 1 ? BLK * ColShape<T, L, BLK>::R : 1];                             \
     __shared__ V tws[L];                                                                                               \
     TwStage<L, BLK, V> tst;                                                                            \
     if constexpr (ColShape<T, L, BLK>::G > 1) tst.fetch(tw);                                                                \
-    if (stopped(a.lay.stop)) return;
+    if (stopped(a.lay.stop)) {                                                                                         \
+        __VA_ARGS__;                                                                                                   \
+        return;                                                                                                        \
+    }
 // ... and, behind the operands' loads, the tables published to the block.
 #define NM_COL_TABLES(L)                                                                                               \
     if constexpr (ColShape<T, L, BLK>::G > 1) tst.store(tws);
@@ -379,7 +383,7 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_ystart(PassAr
                                                                   const cx_t<T>* __restrict__ tw)
 {
     using V = cx_t<T>;
-    NM_COL_BEGIN(L)
+    NM_COL_BEGIN(L, if (MODE == YS_PCG && blockIdx.x == 0 && threadIdx.x == 0) a.scal[S_HALT] = 1.0)
     constexpr int R = ColShape<T, L, BLK>::R, NT = NM_NT(YS, T);
     const int fld = blockIdx.z, j = col_comp<T>(blockIdx.x, ntiles);
     const ColTile<T, L, BLK> c(g, col_tile<T>(blockIdx.x, ntiles));

@@ -64,6 +64,7 @@ __global__ void k_loop_init(double* scal, double thr2, double limit, double mode
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         scal[S_FIRST] = 1.0;
         scal[S_STOP] = 0.0;
+        scal[S_HALT] = 0.0;
         scal[S_ITER] = 0.0;
         scal[S_THR2] = thr2;
         scal[S_LIMIT] = limit;
