@@ -883,11 +883,13 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
         asm volatile("" : "+v"(part));
         __builtin_amdgcn_sched_barrier(0); // one element's stiffness at a time in registers
     }
+    if (valid) { // (surplus pairs read row 0)
 #pragma unroll
-    for (int c = 0; c < 3; c++) st(S + c * cs, w[c]); // s12 s22 s23
-    if (has_z) {
-        st(S + 3 * cs, w[3]); // s13
-        st(S + 4 * cs, w[4]); // s33
+        for (int c = 0; c < 3; c++) st(S + c * cs, w[c]); // s12 s22 s23
+        if (has_z) {
+            st(S + 3 * cs, w[3]); // s13
+            st(S + 4 * cs, w[4]); // s33
+        }
     }
     deriv3(d, [&]() {
         if constexpr (!HOLD_P) {

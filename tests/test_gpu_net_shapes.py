@@ -42,3 +42,9 @@ def test_layer_kernels_at_the_edges_of_their_launches(n):
         wdw, wdb = oracle.conv3d_bwd_weight(cl_to_cf(x, n, cin), cl_to_cf(dy, n, cout), cin, cout, n)
         assert np.abs(dw - wdw.reshape(cout, cin, 27)).max() <= 1e-4 * np.abs(wdw).max()
         assert np.abs(db - wdb).max() <= 1e-4 * np.abs(wdb).max()
+
+
+# one voxel along y, along z, along both: a neighbour across the wrap is the voxel itself
+@pytest.mark.parametrize("n", [(32, 1, 4), (64, 1, 8), (32, 1, 2), (16, 1, 2), (32, 4, 1), (32, 1, 1), (16, 1, 1)])
+def test_layer_kernels_on_axes_of_one_voxel(n):
+    test_layer_kernels_at_the_edges_of_their_launches(n)
