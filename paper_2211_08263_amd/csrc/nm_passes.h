@@ -77,8 +77,7 @@ struct Carry {
 enum YStartMode { YS_APPLY = 0, YS_EXPLICIT = 1, YS_PCG = 2 };
 // Last pass of the operator, y columns: q_j = Q_j - beta dt^2 D_y sigma_2j.
 //   YE_OUT      q (masked) to out
-//   YE_UPDATE   R_j -= alpha y-forward(mask q_j), R the y spectrum of the residual, with the partial
-//               sums of r.r (Parseval)
+//   YE_UPDATE   r_j <- mask(r_j - alpha q_j), held and left as its y spectrum R_j, with the partial sums of r.r
 //   YE_EXPLICIT o = q, the last step of a batch: v <- v + o / rho, a <- 2 o / (dt rho)
 //   YE_EXPLICIT_NEXT a step with a next one behind it: this step's end and the next one's YS_EXPLICIT
 //               in one, v <- v + 2 o / rho (Gamma voxels, whose v is already the next half step's: v as it

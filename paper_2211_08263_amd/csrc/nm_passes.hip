@@ -527,10 +527,10 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_yend(PassArgs
     const bool zero_comp = a.lay.dim == 2 && j == 2;
     V v[R], w[R];
     c.template ld<NT>(src, v);
-    c.template ld<NT>(Q, w);
     V ro[R];
     uint16_t mk[R];
-    if constexpr (SMALL && MODE == YE_UPDATE) c.template ld<NT>((const V*)a.r + fo, ro);
+    if constexpr (SMALL || MODE != YE_UPDATE) c.template ld<NT>(Q, w);
+    if constexpr (MODE == YE_UPDATE) c.template ld<NT>((const V*)a.r + fo, ro);
     if constexpr (SMALL && MODE == YE_RESIDUAL) c.template ld<NT>((const V*)a.b + fo, ro);
     if constexpr (SMALL && (MODE == YE_UPDATE || MODE == YE_OUT || MODE == YE_RESIDUAL)) c.ld_mask(a.mask, mk);
     double pq = 0.0;
@@ -538,8 +538,53 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_yend(PassArgs
         if (a.carry.action == RED_ALPHA) pq = block_total<BLK>(a.carry.part + (long)fld * a.carry.n, a.carry.n);
     }
     NM_COL_READY_FREQ(L)
-    c.deriv(v, lds, tws, frs);
     const T cd = (T)-a.bdt2;
+    if constexpr (MODE == YE_UPDATE) {
+        // r = mask(y-inverse(R / n - alpha cd i xi / n y-forward(sigma)) - alpha Q): three transforms, like the
+        // update R -= alpha y-forward(mask q) of the spectrum alone.  That one leaves R's rounding on the Gamma
+        // voxels, where the masked q is zero, and there it stays, until the free residual is the smaller one
+        // (FP64: from some eps |r_0| on) and the iteration grows without bound.  A y line all Gamma shares its
+        // transform with the next one, so whole planes are no exception.  FP64 iteration with a Gamma plane, that
+        // update / this one: 64^3 61.7 / 61.6 us, 128^3 260.5 / 265.2, 256^3 1924 / 1933 (Q is read late instead
+        // of R); R transformed back on its own, in the tiles that have Gamma: 128^3 266.7, 256^3 1943.
+        double* const sc = a.scal + (long)fld * S_COUNT;
+        T alpha;
+        if (a.carry.action == RED_ALPHA) {
+            const double rz = sc[S_RZ2], al = a.carry.multi && sc[S_STOP] != 0.0 ? 0.0 : rz / pq;
+            alpha = (T)al;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                sc[S_PQ] = pq;
+                sc[S_ALPHA] = al;
+                sc[S_RZ] = rz;
+                sc[S_FIRST] = 0.0;
+            }
+        } else {
+            alpha = (T)sc[S_ALPHA];
+        }
+        if (zero_comp) alpha = 0; // q is zero
+        const T inv_n = (T)f.inv_n, ac = alpha * cd;
+        c.template fft<-1>(v, lds, tws);
+#pragma unroll
+        for (int m = 0; m < R; m++) {
+            const T s = ac * frs[c.t + m * ColTile<T, L, BLK>::G];
+            v[m] = V{inv_n * ro[m].x + s * v[m].y, inv_n * ro[m].y - s * v[m].x};
+        }
+        if constexpr (!SMALL) c.template ld<NT>(Q, w);
+        c.template fft<+1>(v, lds, tws);
+#pragma unroll
+        for (int m = 0; m < R; m++) v[m] = V{v[m].x - alpha * w[m].x, v[m].y - alpha * w[m].y};
+        if constexpr (!SMALL) c.masked(a.mask, v);
+        else c.masked(mk, v);
+        double part = 0.0;
+#pragma unroll
+        for (int m = 0; m < R; m++) part += (double)v[m].x * (double)v[m].x + (double)v[m].y * (double)v[m].y;
+        c.template fft<-1>(v, lds, tws);
+        c.template st<NT>((V*)a.r + fo, v);
+        const double s = block_sum<BLK>(c.valid ? part : 0.0);
+        if (threadIdx.x == 0) a.partials[(long)fld * (3 * ntiles) + blockIdx.x] = s;
+        return;
+    }
+    c.deriv(v, lds, tws, frs);
 #pragma unroll
     for (int m = 0; m < R; m++) {
         v[m] = V{w[m].x + cd * v[m].x, w[m].y + cd * v[m].y};
@@ -626,37 +671,7 @@ __global__ __launch_bounds__(BLK, (ColShape<T, L, BLK>::W)) void k_yend(PassArgs
     } else {
         if constexpr (!SMALL) c.masked(a.mask, v);
         else c.masked(mk, v);
-        if constexpr (MODE == YE_OUT) {
-            c.template st<NT>((V*)a.out + fo, v);
-        } else {
-            // the residual's y spectrum R -= alpha y-forward(q); r.r by Parseval
-            V* const rp = (V*)a.r + fo;
-            double* const sc = a.scal + (long)fld * S_COUNT;
-            T alpha;
-            if (a.carry.action == RED_ALPHA) {
-                const double rz = sc[S_RZ2], al = a.carry.multi && sc[S_STOP] != 0.0 ? 0.0 : rz / pq;
-                alpha = (T)al;
-                if (blockIdx.x == 0 && threadIdx.x == 0) {
-                    sc[S_PQ] = pq;
-                    sc[S_ALPHA] = al;
-                    sc[S_RZ] = rz;
-                    sc[S_FIRST] = 0.0;
-                }
-            } else {
-                alpha = (T)sc[S_ALPHA];
-            }
-            if constexpr (!SMALL) c.template ld<NT>(rp, ro);
-            c.template fft<-1>(v, lds, tws);
-            double part = 0.0;
-#pragma unroll
-            for (int m = 0; m < R; m++) {
-                ro[m] = V{ro[m].x - alpha * v[m].x, ro[m].y - alpha * v[m].y};
-                part += (double)ro[m].x * (double)ro[m].x + (double)ro[m].y * (double)ro[m].y;
-            }
-            c.template st<NT>(rp, ro);
-            const double s = block_sum<BLK>(c.valid ? part : 0.0);
-            if (threadIdx.x == 0) a.partials[(long)fld * (3 * ntiles) + blockIdx.x] = s * f.inv_n;
-        }
+        c.template st<NT>((V*)a.out + fo, v);
     }
 }
 
