@@ -368,16 +368,21 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
     const long t0 = wave * tiles_per_wave;
     const long t1 = t0 + tiles_per_wave < ntiles ? t0 + tiles_per_wave : ntiles;
     // Voxel indices as bit fields (x lowest; the sizes are powers of two): a source voxel is the tile's first
-    // plus a displacement, wrapped field by field.  x and z are added in one word with y's field empty
-    // between them, where x's carry ends, y in another.
+    // plus a displacement, wrapped field by field, in two words: x and z in one, with y's field empty
+    // between them, where x's carry ends, y in the other; one voxel along y has no such field, and z takes
+    // y's place.
+    const bool flat = g.n2 == 1;
     const uint32_t mx = g.n1 - 1, my = (uint32_t)(g.n2 - 1) * g.n1, mz = (uint32_t)(g.n3 - 1) * g.n1 * g.n2;
-    uint32_t dxz[NCH], dy[NCH];
+    const uint32_t ma = flat ? mx : mx | mz, mb = flat ? mz : my;
+    uint32_t da[NCH], db[NCH];
 #pragma unroll
     for (int k = 0; k < NCH; k++) {
         // chunks past the source voxels re-read chunk 0 here
         const int c = lane + 64 * k, vox = c < XCH ? c / CPV : 0, row = vox / 18, j = vox % 18;
-        dxz[k] = ((uint32_t)(g.n1 + j - 1) & mx) | ((uint32_t)(g.n3 + row / 3 - 1) * g.n1 * g.n2 & mz);
-        dy[k] = (uint32_t)(g.n2 + row % 3 - 1) * g.n1 & my;
+        const uint32_t d = ((uint32_t)(g.n1 + j - 1) & mx) | ((uint32_t)(g.n2 + row % 3 - 1) * g.n1 & my) |
+                           ((uint32_t)(g.n3 + row / 3 - 1) * g.n1 * g.n2 & mz);
+        da[k] = d & ma;
+        db[k] = d & mb;
     }
     const uint16_t* const Xq = X + lane % CPV * 8;
     u32x4 pre[NCH];
@@ -385,7 +390,7 @@ __global__ __launch_bounds__(256) void k_conv_bwdw(const uint16_t* __restrict__ 
         const uint32_t v0 = (uint32_t)(tile * 16);
 #pragma unroll
         for (int k = 0; k < NCH; k++) {
-            const uint32_t v = (((v0 & (mx | mz)) + dxz[k]) & (mx | mz)) | (((v0 & my) + dy[k]) & my);
+            const uint32_t v = (((v0 & ma) + da[k]) & ma) | (((v0 & mb) + db[k]) & mb);
             const uint16_t* src = Xq + (size_t)v * CINP;
             // dZ: 32 chunks, those past them re-read its first
             const int c = lane + 64 * k;
