@@ -884,7 +884,11 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
                       at(w[0][m]) + at(d[1][m])};
             T s[6];
             voigt_stress(cg, e, s);
-            part += (double)(b2 * (e[0] * s[0] + e[1] * s[1] + e[2] * s[2] + e[3] * s[3] + e[4] * s[4] + e[5] * s[5]));
+            // (widened before the products: strain times stress can leave FP32's range where neither does)
+            double es = 0.0;
+#pragma unroll
+            for (int q = 0; q < 6; q++) es += (double)e[q] * (double)s[q];
+            part += a.bdt2 * es;
             put(d[0][m], s[0]);
             put(d[1][m], s[5]);
             put(d[2][m], s[4]);
@@ -927,7 +931,7 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
 #pragma unroll
         for (int m = 0; m < R; m++) {
             const V q = V{rh[m][0] * po[j][m].x, rh[m][1] * po[j][m].y};
-            part += (double)(q.x * po[j][m].x + q.y * po[j][m].y);
+            part += (double)q.x * (double)po[j][m].x + (double)q.y * (double)po[j][m].y;
             d[j][m] = V{q.x - b2 * d[j][m].x, q.y - b2 * d[j][m].y};
         }
         asm volatile("" : "+v"(part));
