@@ -215,8 +215,8 @@ int nm_green_solve(nm_ctx* ctx, const double* V, double* X);
 /* Measurement: run the passes of one operator apply (which == 0: five passes, y z x z y)
  * or one preconditioner apply (which == 1: five passes, y z x z y) reps times on the
  * context stream, with a HIP event pair around every pass; ms[i] receives the
- * average duration of pass i in chain order (ms needs 9 entries; in 2D the two z passes do
- * not exist and their entries hold no kernel).  Buffers as for nm_apply_operator.  Synchronous. */
+ * average duration of pass i in chain order (ms has 9 entries, those behind the passes become
+ * zero; in 2D the two z passes do not exist and their entries hold no kernel).  Buffers as for nm_apply_operator.  Synchronous. */
 int nm_profile_passes(nm_ctx* ctx, int which, const void* u_dev, void* out_dev, int dtype, int reps, double* ms);
 
 /* ------------------------------------------------------------------------

@@ -1076,7 +1076,7 @@ template <typename T> int profile_impl(nm_ctx* c, int which, const T* in, T* out
     }
     for (int i = 0; i <= np; i++) (void)hipEventDestroy(ev[i]);
     if (rc != 0) return fail(c, NM_EHIP, "pass launch failed during profiling");
-    for (int i = 0; i < np; i++) ms[i] = acc[i] / reps;
+    for (int i = 0; i < 9; i++) ms[i] = i < np ? acc[i] / reps : 0.0;
     return NM_OK;
 }
 

@@ -113,3 +113,19 @@ def test_explicit_batch_is_its_steps_one_by_one(dim, n, per_point):
         err = rel_max(x, y)
         print(f"explicit {n} {q}: {err:.2e}", flush=True)
         assert np.isfinite(x).all() and err <= 1e-12
+
+
+@pytest.mark.parametrize("which", [0, 1])
+def test_profile_fills_every_entry(which):
+    """The nine durations that nm_profile_passes asks room for: its passes', then zeros, so that a sum
+    over them is the chain whatever its number of passes."""
+    import ctypes as C
+    import torch
+    pb = random_problem(3, (16, 16, 16))
+    with nmb.newmark_init_problem(pb, nmb.Options()) as ctx:
+        u = torch.zeros(3 * ctx.N, dtype=torch.float64, device="cuda")
+        out = torch.zeros_like(u)
+        ms = (C.c_double * 9)(*[float("nan")] * 9)
+        ctx.check(nmb.load_library().nm_profile_passes(ctx.handle, which, u.data_ptr(), out.data_ptr(), nmb.NM_FP64, 3, ms))
+    n = len(nmb.OPERATOR_PASSES if which == 0 else nmb.PRECOND_PASSES)
+    assert all(0 < t < 1e3 for t in ms[:n]) and all(t == 0 for t in ms[n:])
