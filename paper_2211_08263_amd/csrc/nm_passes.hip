@@ -949,19 +949,22 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXStressWaves64, kXStressWave
 // so a group takes the rows k = (ky, kz) and -k together: one complex line of N1 points whose
 // x transform, multiplier and inverse serve both rows (z^(-k) = conj z^(k) in real space).  Rows
 // that are their own mirror are done once.
-// The multiplier beta dt^2 K(xi) + rhobar I in working precision: K[q][v] xi xi sums entry q (00 01 02
-// 11 12 22) over the products v = 11 22 33 23 13 12 of the frequencies.
-template <typename T> struct PrecondParams {
-    T K[6][6];
-    T rhobar, inv_ntot;
+// The multiplier beta dt^2 K(xi) + rhobar I: K[q][v] xi xi sums entry q (00 01 02 11 12 22) over the
+// products v = 11 22 33 23 13 12 of the frequencies.  It and its inverse are formed in FP64 for FP32
+// fields too, as its cofactors cancel: error of the FP32 preconditioner against 64 bits with an FP32
+// inverse / with this, copper 256^3 2.91e-7 / 2.79e-7, 64^3 2.42e-7 / 2.32e-7, a Poisson ratio of 0.49999
+// 16^3 2.3 / 2.1e-7.  x pass at 256^3 89 / 91 us, mixed step 29.86 / 30.00 ms.
+struct PrecondParams {
+    double K[6][6];
+    double rhobar, inv_ntot;
     double k1, k2, k3;
     const double* mfreq;
     int n1, n2, n3, dim;
 };
 
-template <typename T> static PrecondParams<T> precond_params(const SpecParams& sp)
+static PrecondParams precond_params(const SpecParams& sp)
 {
-    PrecondParams<T> p;
+    PrecondParams p;
     double C[6][6];
     for (int a = 0, o = 0; a < 6; a++)
         for (int b = a; b < 6; b++, o++) C[a][b] = C[b][a] = sp.Cbar[o];
@@ -973,10 +976,10 @@ template <typename T> static PrecondParams<T> precond_params(const SpecParams& s
                 // K_ij = Cbar_ikjm xi_k xi_m (eq. acous)
                 const int k = P[v][0], m = P[v][1];
                 const double c = C[V[i][k]][V[j][m]] + (k != m ? C[V[i][m]][V[j][k]] : 0.0);
-                p.K[q][v] = (T)(sp.bdt2 * c);
+                p.K[q][v] = sp.bdt2 * c;
             }
-    p.rhobar = (T)sp.rhobar;
-    p.inv_ntot = (T)sp.inv_ntot;
+    p.rhobar = sp.rhobar;
+    p.inv_ntot = sp.inv_ntot;
     p.k1 = sp.k1;
     p.k2 = sp.k2;
     p.k3 = sp.k3;
@@ -994,7 +997,7 @@ template <typename T, int N1> struct XPShape {
 
 template <typename T, int N1, int BLK, int MEM>
 __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXPrecondWaves64, kXPrecondWaves32)))
-    void k_xprecond(PrecondParams<T> sp, Layout lay, const cx_t<T>* __restrict__ src,
+    void k_xprecond(PrecondParams sp, Layout lay, const cx_t<T>* __restrict__ src,
                                                                     long sc, long sb, cx_t<T>* __restrict__ dst, int nlines,
                                                                     int nfull, const cx_t<T>* __restrict__ tw,
                                                                     double* __restrict__ partials, Carry carry)
@@ -1072,10 +1075,10 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXPrecondWaves64, kXPrecondWa
     for (int j = 0; j < 3; j++) group_fft<N1, R, -1, true, FFT_PAIR_IN, 1>((V(&)[1][R])v[j], t, lds, addr, tws);
     // beta dt^2 K(xi) + rhobar I at fixed (xi2, xi3) is quadratic in xi1: A0 + xi1 (A1 + xi1 A2), formed
     // once per thread (symmetric; upper triangles kept, order 00 01 02 11 12 22)
-    T A0[6], A1[6];
+    double A0[6], A1[6];
     {
-        const T x2 = (T)(sp.mfreq ? sp.mfreq[sp.n1 + ky] : sp.k2 * freq_index(ky, sp.n2));
-        const T x3 = (T)(sp.mfreq ? sp.mfreq[sp.n1 + sp.n2 + kz] : sp.k3 * freq_index(kz, sp.n3));
+        const double x2 = sp.mfreq ? sp.mfreq[sp.n1 + ky] : sp.k2 * freq_index(ky, sp.n2);
+        const double x3 = sp.mfreq ? sp.mfreq[sp.n1 + sp.n2 + kz] : sp.k3 * freq_index(kz, sp.n3);
 #pragma unroll
         for (int q = 0; q < 6; q++) {
             A0[q] = x2 * (sp.K[q][1] * x2 + sp.K[q][3] * x3) + sp.K[q][2] * x3 * x3;
@@ -1090,30 +1093,33 @@ __global__ __launch_bounds__(BLK, (x_waves<T, BLK>(kXPrecondWaves64, kXPrecondWa
 #pragma unroll
     for (int m = 0; m < R; m++) {
         const int kx = t + m * G;
-        const T x1 = (T)(sp.mfreq ? sp.mfreq[kx] : sp.k1 * freq_index(kx, N1));
-        T Kx[6];
+        const double x1 = sp.mfreq ? sp.mfreq[kx] : sp.k1 * freq_index(kx, N1);
+        double Kx[6];
 #pragma unroll
         for (int q = 0; q < 6; q++) Kx[q] = A0[q] + x1 * (A1[q] + x1 * sp.K[q][0]);
-        const T k00 = Kx[0], k01 = Kx[1], k02 = Kx[2], k11 = Kx[3], k12 = Kx[4], k22 = Kx[5];
+        const double k00 = Kx[0], k01 = Kx[1], k02 = Kx[2], k11 = Kx[3], k12 = Kx[4], k22 = Kx[5];
         const V r0 = v[0][m], r1 = v[1][m], r2 = v[2][m];
         V z0, z1, z2;
         if (sp.dim == 2) {
-            const T id = sp.inv_ntot / (k00 * k11 - k01 * k01);
-            z0 = cscale(csub(cscale(r0, k11), cscale(r1, k01)), id);
-            z1 = cscale(csub(cscale(r1, k00), cscale(r0, k01)), id);
+            const double id = sp.inv_ntot / (k00 * k11 - k01 * k01);
+            const T d00 = (T)(k11 * id), d01 = (T)(k01 * id), d11 = (T)(k00 * id);
+            z0 = csub(cscale(r0, d00), cscale(r1, d01));
+            z1 = csub(cscale(r1, d11), cscale(r0, d01));
             z2 = V{0, 0};
         } else {
             // inverse of the symmetric 3x3 by cofactors
-            const T c00 = k11 * k22 - k12 * k12;
-            const T c01 = k02 * k12 - k01 * k22;
-            const T c02 = k01 * k12 - k02 * k11;
-            const T c11 = k00 * k22 - k02 * k02;
-            const T c12 = k02 * k01 - k00 * k12;
-            const T c22 = k00 * k11 - k01 * k01;
-            const T id = sp.inv_ntot / (k00 * c00 + k01 * c01 + k02 * c02);
-            z0 = cscale(cadd(cadd(cscale(r0, c00), cscale(r1, c01)), cscale(r2, c02)), id);
-            z1 = cscale(cadd(cadd(cscale(r0, c01), cscale(r1, c11)), cscale(r2, c12)), id);
-            z2 = cscale(cadd(cadd(cscale(r0, c02), cscale(r1, c12)), cscale(r2, c22)), id);
+            const double c00 = k11 * k22 - k12 * k12;
+            const double c01 = k02 * k12 - k01 * k22;
+            const double c02 = k01 * k12 - k02 * k11;
+            const double c11 = k00 * k22 - k02 * k02;
+            const double c12 = k02 * k01 - k00 * k12;
+            const double c22 = k00 * k11 - k01 * k01;
+            const double id = sp.inv_ntot / (k00 * c00 + k01 * c01 + k02 * c02);
+            const T d00 = (T)(c00 * id), d01 = (T)(c01 * id), d02 = (T)(c02 * id), d11 = (T)(c11 * id),
+                    d12 = (T)(c12 * id), d22 = (T)(c22 * id);
+            z0 = cadd(cadd(cscale(r0, d00), cscale(r1, d01)), cscale(r2, d02));
+            z1 = cadd(cadd(cscale(r0, d01), cscale(r1, d11)), cscale(r2, d12));
+            z2 = cadd(cadd(cscale(r0, d02), cscale(r1, d12)), cscale(r2, d22));
         }
         part += (double)(r0.x * z0.x + r0.y * z0.y + r1.x * z1.x + r1.y * z1.y + r2.x * z2.x + r2.y * z2.y);
         asm volatile("" : "+v"(part)); // due here, not where it is used
@@ -1342,7 +1348,7 @@ int launch_xprecond(const SpecParams& sp, const Layout& lay, const void* src, lo
     int full, threads;
     const int rows = mirror_rows(lay, &full);
     const dim3 grid(x_blocks(lay.n1, XPShape<T, 8>::R, rows, &threads) + (carry.action != RED_NONE), 1, lay.nb);
-    const PrecondParams<T> pp = precond_params<T>(sp);
+    const PrecondParams pp = precond_params(sp);
     NM_SIZE_SWITCH(lay.n1, {
         NM_X_LAUNCH((k_xprecond<T, NN, BLK, MEM>), (XPShape<T, NN>::R), lay, pp, lay, (const cx_t<T>*)src, sc, sb,
                     (cx_t<T>*)S2, rows, full, (const cx_t<T>*)tw, partials, carry);

@@ -129,3 +129,34 @@ def test_profile_fills_every_entry(which):
         ctx.check(nmb.load_library().nm_profile_passes(ctx.handle, which, u.data_ptr(), out.data_ptr(), nmb.NM_FP64, 3, ms))
     n = len(nmb.OPERATOR_PASSES if which == 0 else nmb.PRECOND_PASSES)
     assert all(0 < t < 1e3 for t in ms[:n]) and all(t == 0 for t in ms[n:])
+
+
+@pytest.mark.parametrize("dim,n", [(3, (16, 16, 16)), (3, (32, 8, 8)), (3, (128, 64, 128)), (2, (64, 32))],
+                         ids=["16x16x16", "32x8x8", "128x64x128", "64x32"])
+def test_fp32_preconditioner_on_a_nearly_incompressible_medium(dim, n):
+    """The multiplier's inverse is formed in FP64 for FP32 fields too.  At a Poisson ratio of 0.49999 its
+    cofactors cancel by the ratio of the moduli, 5e4: in FP32 that would leave 5e4 eps = 3e-3 of
+    them.  Bar: 1e-5 of the largest entry, as for the other FP32 checks here."""
+    import dataclasses
+    import torch
+    pb = random_problem(dim, n, seed=8, dt=2.0)
+    C21 = np.stack([W.voigt_to21(W.isotropic_voigt66(1.0, 0.49999))] * 3)
+    pb = dataclasses.replace(pb, C21=C21)
+    N = int(np.prod(n))
+    nn = tuple(n) + (1,) * (3 - len(n))
+    r = W.random_field((dim, nn[2], nn[1], nn[0]), seed=3).astype(np.float32).astype(np.float64)
+    with nmb.newmark_init_problem(pb, nmb.Options()) as ctx:
+        got = {}
+        for dtype in (torch.float64, torch.float32):
+            z = torch.empty(3, N, dtype=dtype, device="cuda")
+            rd = dev(field3(r, dim), dtype)
+            torch.cuda.synchronize()
+            nmb.precond_apply(ctx, rd, z)
+            torch.cuda.synchronize()
+            got[dtype] = z.double().cpu().numpy()
+    want = got[torch.float64]
+    if N <= 1 << 12:
+        want = field3(oracle.OracleProblem.from_problem(pb).precond(r), dim)
+    err = rel_max(got[torch.float32], want)
+    print(f"precond nu 0.49999 {n}: {err:.2e}", flush=True)
+    assert err <= 1e-5
