@@ -269,7 +269,7 @@ int nm_conv3d_bf16(void* hip_stream, int mode, const int* grid, int cinp, int ci
  * kernels and results, with every device buffer of the call (FP32 and packed BF16 weights,
  * bias, weight-gradient partial sums) taken from one file-scope device array of 16 MiB
  * that each device holds until the process ends.  It calls no hipMalloc or hipFree.  The
- * weight-gradient pass (mode 2) uses at most 256 partial-sum slots, so the array does not
+ * weight-gradient pass (mode 2) uses at most 256 wavefronts (64 partial-sum slots), so the array does not
  * grow with the grid and no grid accepted by nm_conv3d_bf16 is too large; its sums are
  * grouped differently from nm_conv3d_bf16's (FP32 rounding differs, modes 0 and 1 are
  * identical).  Every call on a device shares that device's array and leaves its contents

@@ -81,7 +81,9 @@
 // (kPlainBytes), nothing streams: FP64 PCG iteration at 128^3 270.9 us with the settings above, 260.7 all
 // plain.  Blocks of small grids (see kColSmallBlocks, kXSmallBlocks) stream everything, as stores that
 // wait in the L2 are written back at the kernel's end, where nothing covers them: 64^3 66.2 us with the
-// settings above, 68.4 all plain, 59.8 all streaming (32^3: 43.1, 42.4, 43.8).
+// settings above, 69.5 all plain, 59.8 all streaming.  The smallest grids would be 5-10% faster plain
+// (streaming / plain: 16^3 44.0 / 39.3 us, 32^3 43.4 / 41.1, 512x8x8 51.7 / 49.5); there is one setting
+// for all that take those blocks.
 enum Mem { MEM_PLAIN = 0, MEM_STREAM = 1 };
 #define NM_NT(FAM, T) (SMALL ? 3 : MEM == MEM_PLAIN ? 0 : sizeof(T) == 8 ? NM_NT_##FAM##64 : NM_NT_##FAM##32)
 
@@ -1175,7 +1177,9 @@ static AxisFreq axis_freq(const SpecParams& sp, int axis)
 }
 // Whether the fields of a conjugate-gradient iteration (work buffers 8, direction, iterate, residual) about fit
 // the 256 MB last-level cache.
-constexpr long kPlainBytes = 320L << 20; // (FP64 iteration plain / streaming: 285 MB 260.7 / 270.9 us, 1.14 GB 1045 / 945)
+// FP64 iteration plain / streaming: 285 MB 258.5 / 264.5 us, 570 MB (256x128x128) 489.8 / 481.5,
+// 1.14 GB 1049 / 933; mixed step 285 MB 4.70 / 4.80 ms, 570 MB 8.96 / 8.69.
+constexpr long kPlainBytes = 320L << 20;
 template <typename T> static bool plain_memory(const Layout& l)
 {
     return 17 * l.ns * l.nb * (long)sizeof(cx_t<T>) <= kPlainBytes;

@@ -5,7 +5,6 @@
 
 namespace nm {
 
-// Deterministic sum of n per-block partials into the scalar block, then the action.
 // x += alpha p, alpha read from the device (the deferred last update of a Krylov loop).
 template <typename T> int launch_axpy_scal(T* x, const T* p, const double* alpha, long n, hipStream_t s);
 // Arm a batched Krylov loop: clear S_STOP, S_HALT and S_ITER, set S_THR2, S_LIMIT, S_MODE (1: run
