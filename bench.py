@@ -53,11 +53,22 @@ OPERATOR_PASS_FIELDS = {"x_fwd": 6, "y_deriv": 6, "z_strain": 12, "x_stress": 12
 OPERATOR_PASS_ID_BYTES = {"x_stress": 2, "x_inv_inertia": 2}
 
 
-# HBM bytes per dispatch of the x_stress pass of the seven-pass operator at 256^3 from two rocprofv3 counter runs
-# (profiles/hbm_traffic_256cube.md): FETCH_SIZE x 2.000 and WRITE_SIZE x 1.000, the factors a
-# 512 MiB device copy reads for those counters.  Valid only for the kernel sources they were
-# taken on (hash below); otherwise the traffic is reported as null.
-PMC_TRAFFIC = {("x_stress", "fp64"): {"fetch_kib": 410158.5, "write_kib": 786436.8},
+# The same of one step of a batch of explicit steps: a first pass of 18 fields, per step the three
+# middle passes (32, grain id) and the pass that ends it (grain id), 21 and the Gamma mask where it
+# begins the next step as well, 15 for the batch's last.
+def explicit_bytes_per_voxel(steps):
+    return (8 * (18 + 32 * steps + 21 * (steps - 1) + 15) + 4 * steps + (steps - 1)) / steps
+
+
+# HBM bytes per dispatch of the stress pass (x_sigma; x_stress in the seven-pass operator) at 256^3 from
+# two rocprofv3 counter runs (profiles/hbm_traffic_256cube.md): FETCH_SIZE x 2.000 and WRITE_SIZE x 1.000,
+# the factors a 512 MiB device copy reads for those counters.  Valid only for the kernel sources they
+# were taken on (their hash, PMC_SOURCES_SHA16 where an entry names none); otherwise the traffic is
+# reported as null.
+X_SIGMA_SOURCES = "762454f5f056c1e8"
+PMC_TRAFFIC = {("x_sigma", "fp64"): {"fetch_kib": 550388.2, "write_kib": 1048628.2, "sources": X_SIGMA_SOURCES},
+               ("x_sigma", "fp32"): {"fetch_kib": 279605.9, "write_kib": 526114.6, "sources": X_SIGMA_SOURCES},
+               ("x_stress", "fp64"): {"fetch_kib": 410158.5, "write_kib": 786436.8},
                ("x_stress", "fp32"): {"fetch_kib": 213319.0, "write_kib": 393216.5}}
 PMC_N = 256
 PMC_SCALE = {"fetch": 2.000, "write": 1.000}
@@ -76,7 +87,7 @@ def sources_sha16():
 
 def pmc_traffic(kernel, label, n):
     t = PMC_TRAFFIC.get((kernel, label))
-    if t is None or n != PMC_N or sources_sha16() != PMC_SOURCES_SHA16:
+    if t is None or n != PMC_N or sources_sha16() != t.get("sources", PMC_SOURCES_SHA16):
         return None
     return round(1024 * (t["fetch_kib"] * PMC_SCALE["fetch"] + t["write_kib"] * PMC_SCALE["write"]))
 
@@ -301,7 +312,7 @@ def explicit_rates(pb, steps, warmup):
     finally:
         ctx.close()
     assert np.isfinite(u).all()
-    bpv = 65 * 8 + 4  # first pass with the displacement update 15F, three middle passes 32F + 2 B, last 18F + 2 B
+    bpv = explicit_bytes_per_voxel(steps)
     log(f"[explicit] omega_max^2 {w2:.4f} (power iteration {w2_est:.4f}, grain bound {w2_bound:.4f}); "
         f"dt {dt:.4f} vs implicit {pb.dt:.4f}; {steps} steps in {el:.3f}s -> {steps / el:.1f} steps/s")
     return {"steps_per_s": steps / el, "ms_per_step": 1e3 * el / steps, "dt": dt, "omega2_max_power_iter": w2_est,
